@@ -496,9 +496,16 @@ enum {
                                     named by FCRKPM_AUTOTUNE_CACHE (keyed by device, box, basis
                                     and support) instead of timing; new choices are appended to
                                     that file */
-    FCRKPM_OPT_KN_REGPATH = 12   /* read only: 1 if fcrkpm_gradient_force (and the gradients of
+    FCRKPM_OPT_KN_REGPATH = 12,  /* read only: 1 if fcrkpm_gradient_force (and the gradients of
                                     fcrkpm_solve_nonlinear_cg) run on the FP64 register path;
                                     the first read builds that path's records (synchronous) */
+    FCRKPM_OPT_TAPS = 13         /* 1 (default): products whose kernel reaches at most 3 nodes
+                                    (ceil(support) - 1 <= 3) sum their convolutions directly,
+                                    in one launch, instead of by FFT passes.  0, and any option
+                                    above that asks for FFT passes other than setup's choice
+                                    (OPT_REGPATH 0, OPT_LINECONST 0, another OPT_REGLAYOUT or
+                                    OPT_SEP_LINES*), run the FFT passes; reads 1 if direct sums
+                                    serve this context's K products */
 };
 /* Set an option; FCRKPM_ERR_ARG for an unknown option or a value out of range. */
 fcrkpm_status fcrkpm_set_option(fcrkpm_ctx* ctx, int32_t option, int64_t value);

@@ -87,12 +87,13 @@ void* scratch_address()
 // sizes).
 enum Kind {
     KD_P1_X, KD_P1_Y, KD_P1_Z, KD_MID_K, KD_MID_UH, KD_MID_LOAD, KD_P2_X, KD_P2_Y, KD_P2_Z,
-    KD_SETUP_PASS, KD_STAGES
+    KD_SETUP_PASS, KD_TAP_K, KD_STAGES
 };
 constexpr int KD_NKINDS = 2 * KD_STAGES;  // FP64 kinds, then FP32 kinds
 const char* const kStageNames[KD_STAGES] = {
     "sep_part1_x", "sep_part1_y", "sep_part1_z", "sep_mid_k", "sep_mid_uh", "sep_mid_load",
-    "sep_part2_x", "sep_part2_y", "sep_part2_z", "sep_setup_pass"};
+    "sep_part2_x", "sep_part2_y", "sep_part2_z", "sep_setup_pass",
+    "tap_k"};
 std::string kind_name(int k)
 {
     return std::string(kStageNames[k % KD_STAGES]) + (k >= KD_STAGES ? "_f32" : "_f64");
@@ -165,6 +166,7 @@ void free_set(OpSet*& s)
         dfree(s->nrec[l]);
     }
     sym_release_state(s->sym);
+    tap_release_set(s->tap);
     delete s;
     s = nullptr;
 }
@@ -172,6 +174,7 @@ void free_set(OpSet*& s)
 void release(Ctx& c)
 {
     sym_release(c);
+    tap_release(c);
     free_set(c.mass_set);
     free_set(c.shift_set);
     free_set(c.jac_set);
@@ -595,6 +598,21 @@ void reg_k(Ctx& c, const float* in, float* out, const uint8_t* mask, int nrhs, h
     launch_reg_k(c, in, out, mask, nrhs, dot_part, dot_with, st, rp, pu);
 }
 
+// The K-type product on the direct tap kernels, with the partials of
+// out . dot_with where dot_part is given.
+template <typename T, typename Tio>
+void tap_k(Ctx& c, const Tio* in, Tio* out, const uint8_t* mask, int nrhs, hipStream_t st,
+           double* dot_part = nullptr, const Tio* dot_with = nullptr, long dot_stride = 0)
+{
+    const double bytes = (double)c.nn * (2 * sizeof(Tio) + 2 + (dot_part ? sizeof(Tio) : 0));
+    ProfScope ps(c, kind_of<T>(KD_TAP_K), bytes * nrhs, st);
+    launch_tap<T, Tio>(c, 0, in, out, mask, mask, nullptr, nrhs, dot_part, dot_with, dot_stride, st);
+}
+
+// slots per right-hand side of the p.q partials of a last pass or a direct
+// product with more workgroups than kRedBlocks
+long wide_slots(const Ctx& c) { return std::max(reg_dot_slots(c), tap_dot_slots(c)); }
+
 void build_pointwise(Ctx& c, hipStream_t st);
 
 // Exchanges the pointwise data of the K-type product in use with `s`.
@@ -614,6 +632,7 @@ void swap_set(Ctx& c, OpSet& s)
     std::swap(c.nload, s.nload);
     std::swap(c.nconst, s.nconst);
     std::swap(c.sym, s.sym);
+    std::swap(c.tap, s.tap);
 }
 
 // The products of a scope use the set `s` (kernels take their arguments at
@@ -699,6 +718,11 @@ void apply_one(Ctx& c, int op, const Tio* in, Tio* out, int nrhs, hipStream_t st
         case OP_KN: {
             const uint8_t* mk = (op == FCRKPM_OP_K) ? c.freem : c.chi;
             const int pwk = (op == OP_KN) ? SEP_PW_KN : SEP_PW_K;
+            // (without its nonlinear term the gradient force is K d)
+            if (tap_active(c) && (op != OP_KN || c.pw_kappa == 0.0)) {
+                tap_k<T, Tio>(c, in, out, mk, nrhs, st);
+                break;
+            }
             if constexpr (std::is_same_v<T, float> && std::is_same_v<Tio, float>) {
                 if (op != OP_KN && use_reg_path(c, nrhs)) {
                     reg_k(c, in, out, mk, nrhs, st);
@@ -825,7 +849,7 @@ void ensure_rhs(Ctx& c, int nrhs)
     c.v32 = dalloc<float>(5 * nn * nrhs);
     c.partial = dalloc<double>((size_t)2 * kRedBlocks * nrhs);
     dfree(c.partial_wide);
-    if (reg_dot_slots(c) > kRedBlocks) c.partial_wide = dalloc<double>((size_t)reg_dot_slots(c) * nrhs);
+    if (wide_slots(c) > kRedBlocks) c.partial_wide = dalloc<double>((size_t)wide_slots(c) * nrhs);
     c.scal = dalloc<double>((size_t)kScal * nrhs);
     c.act = dalloc<int>(nrhs);
     HIPCHK(hipMemset(c.scal, 0, sizeof(double) * kScal * nrhs));
@@ -861,7 +885,7 @@ template <typename T, typename TP>
 bool fused_cg(Ctx& c, int nrhs)
 {
     if constexpr (std::is_same_v<T, float> && std::is_same_v<TP, float>)
-        return use_reg_path(c, nrhs);
+        return !tap_active(c) && use_reg_path(c, nrhs);
     else
         return false;
 }
@@ -877,7 +901,16 @@ void cg_iteration(Ctx& c, T* x, T* r, T* p, T* q, int nrhs, int parity, hipStrea
     double* pq_part = c.partial;
     double* rr_part = c.partial + (size_t)kRedBlocks * c.cap_rhs;
     int npq = red_blocks(c.nn);
-    if constexpr (std::is_same_v<T, float> && std::is_same_v<TP, float>) {
+    if (tap_active(c)) {
+        // the direct product leaves the p.q partials of its workgroups (in the
+        // wide slots, summed to one, when they outnumber kRedBlocks)
+        const long nb = tap_blocks(c, nrhs, sizeof(TP));
+        const bool wide = nb > kRedBlocks;
+        tap_k<TP, T>(c, p, q, c.freem, nrhs, st, wide ? c.partial_wide : pq_part, p,
+                     wide ? wide_slots(c) : kRedBlocks);
+        npq = wide ? 1 : (int)nb;
+        if (wide) launch_reduce_wide(c.partial_wide, (int)nb, wide_slots(c), nrhs, pq_part, st);
+    } else if constexpr (std::is_same_v<T, float> && std::is_same_v<TP, float>) {
         if (fused) {
             // the last pass of the product also leaves the p.q partials (in
             // the wide slots, summed to one, when its workgroups outnumber
@@ -1496,6 +1529,12 @@ void run_solvers_on(const std::vector<Solver*>& all, bool graphs, hipStream_t st
 
 [[noreturn]] void fcrkpm::raise_unsupported(const char* msg) { fail(FCRKPM_ERR_UNSUPPORTED, msg); }
 
+[[noreturn]] void fcrkpm::raise_hip(hipError_t e, const char* what)
+{
+    if (e == hipErrorOutOfMemory) fail(FCRKPM_ERR_OOM, std::string("device allocation failed: ") + what);
+    throw HipFail{e, what};
+}
+
 // ========================================================================= ABI
 
 namespace {
@@ -1615,6 +1654,7 @@ void build_pointwise(Ctx& c, hipStream_t st)
             HIPCHK(hipStreamSynchronize(st));
         }
     }
+    tap_build(c, st);
 }
 
 void set_reg_variant(Ctx& c, int v)
@@ -1739,6 +1779,13 @@ std::string tune_key(const Ctx& c)
 // "<key> <register variant> <FP32 lines> <FP64 lines> <4 variant times, us>".
 void autotune(Ctx& c, hipStream_t st)
 {
+    // the choices below concern the FFT passes
+    struct FftPasses {
+        Ctx& c;
+        bool taps;
+        explicit FftPasses(Ctx& c_) : c(c_), taps(c_.use_taps) { c.use_taps = false; }
+        ~FftPasses() { c.use_taps = taps; }
+    } fft(c);
     const char* path = getenv("FCRKPM_AUTOTUNE_CACHE");
     const std::string key = (path && *path) ? tune_key(c) : std::string();
     if (!key.empty()) {
@@ -1893,6 +1940,17 @@ extern "C" fcrkpm_status fcrkpm_setup(const fcrkpm_grid* grid, const uint8_t* ma
             off += c.n[a];
         }
 
+        // taps of the direct kernels: t_e(o) = o^e phi(o / a~)
+        double taps[3][5][4] = {};
+        for (int a = 0; a < c.dim; ++a) {
+            c.tap_r = std::max(c.tap_r, (int)ceil(c.at[a]) - 1);
+            for (int o = 0; o < 4; ++o) {
+                long double mo = bspline((long double)o / (long double)c.at[a]);
+                for (int e = 0; e < 5; ++e, mo *= (long double)o) taps[a][e][o] = (double)mo;
+            }
+        }
+        tap_setup(c, taps, st);
+
         // twiddles and separable kernel spectra (Sec 5.2-5.3, Eq 68-79)
         const long double twopi = 6.283185307179586476925286766559005768L;
         for (int a = 0; a < 3; ++a) {
@@ -2039,6 +2097,9 @@ extern "C" fcrkpm_status fcrkpm_setup(const fcrkpm_grid* grid, const uint8_t* ma
         ensure_work(c, 1);
         ensure_rhs(c, 1);
         autotune(c, st);
+        c.tuned[0] = c.reg_layout + 2 * (c.reg_tpw - 1);
+        c.tuned[1] = c.sep_wcap[0];
+        c.tuned[2] = c.sep_wcap[1];
         HIPCHK(hipGetLastError());
         *out = h;
         h = nullptr;
@@ -2859,12 +2920,19 @@ extern "C" fcrkpm_status fcrkpm_get_option(fcrkpm_ctx* ctx, int32_t option, int6
             case FCRKPM_OPT_SEP_LINES32: *value = c.sep_wcap[0]; break;
             case FCRKPM_OPT_SEP_LINES64: *value = c.sep_wcap[1]; break;
             case FCRKPM_OPT_TUNE_CACHED: *value = c.tune_cached ? 1 : 0; break;
+            case FCRKPM_OPT_TAPS: *value = tap_active(c) ? 1 : 0; break;
             case FCRKPM_OPT_KN_REGPATH: *value = (use_reg_path64(c) && reg_kn_ok(c, nullptr)) ? 1 : 0; break;
             default: fail(FCRKPM_ERR_ARG, "unknown option");
         }
         return FCRKPM_OK;
     });
 }
+
+namespace {
+// An option that asks for FFT passes other than setup's choice selects them
+// instead of the direct kernels; its default gives the choice back.
+void pin_fft(Ctx& c, int bit, bool on) { c.fft_pins = on ? c.fft_pins | bit : c.fft_pins & ~bit; }
+}  // namespace
 
 extern "C" fcrkpm_status fcrkpm_set_option(fcrkpm_ctx* ctx, int32_t option, int64_t value)
 {
@@ -2879,21 +2947,34 @@ extern "C" fcrkpm_status fcrkpm_set_option(fcrkpm_ctx* ctx, int32_t option, int6
             case FCRKPM_OPT_REGPATH:
                 if (value != 0 && value != 1) fail(FCRKPM_ERR_ARG, "FCRKPM_OPT_REGPATH takes 0 or 1");
                 c.use_regpath = value == 1;
+                pin_fft(c, 1, value == 0);
+                break;
+            case FCRKPM_OPT_TAPS:
+                if (value != 0 && value != 1) fail(FCRKPM_ERR_ARG, "FCRKPM_OPT_TAPS takes 0 or 1");
+                c.use_taps = value == 1;
                 break;
             case FCRKPM_OPT_REGLAYOUT:
                 if (!((reg_path_ok(c) || reg_gpq_ok(c)) ? reg_variant_ok(c, (int)value) : value == 0))
                     fail(FCRKPM_ERR_ARG, "FCRKPM_OPT_REGLAYOUT out of range for this box");
                 set_reg_variant(c, (int)value);
+                pin_fft(c, 2, value != c.tuned[0]);
                 break;
             case FCRKPM_OPT_LINECONST:
                 if (value != 0 && value != 1) fail(FCRKPM_ERR_ARG, "FCRKPM_OPT_LINECONST takes 0 or 1");
                 c.use_sym = value == 1;
+                pin_fft(c, 4, value == 0);
                 break;
             case FCRKPM_OPT_SEP_LINES32:
             case FCRKPM_OPT_SEP_LINES64:
                 if (value != 16 && value != 8 && value != 4)
                     fail(FCRKPM_ERR_ARG, "lines per workgroup of the LDS-tiled passes: 16, 8 or 4");
-                c.sep_wcap[option == FCRKPM_OPT_SEP_LINES64 ? 1 : 0] = (int)value;
+                if (option == FCRKPM_OPT_SEP_LINES32) {
+                    c.sep_wcap[0] = (int)value;
+                    pin_fft(c, 8, value != c.tuned[1]);
+                } else {
+                    c.sep_wcap[1] = (int)value;
+                    pin_fft(c, 16, value != c.tuned[2]);
+                }
                 break;
             default:
                 fail(FCRKPM_ERR_ARG, "unknown option");

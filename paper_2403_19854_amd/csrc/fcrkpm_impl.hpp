@@ -83,6 +83,7 @@ struct OpSet {
     long nload[2] = {-1, -1};
     NodeConst nconst = {};
     void* sym = nullptr;                // line-constant records of this set's rows
+    void* tap = nullptr;                // direct tap kernels: class words and records of this set's rows
 };
 
 struct Ctx {
@@ -175,6 +176,16 @@ struct Ctx {
     void* sym = nullptr;                // register path: line-constant middle pass of K (regpass.hip)
     bool use_sym = true;                // use it where it applies
     double* rtab64[3] = {};             // per axis [3][n]: Re T_0 / n, Im T_1 / n, Re T_2 / n (FP64)
+    // direct tap kernels (tapconv.hip)
+    bool use_taps = true;               // use them where they apply
+    int fft_pins = 0;                   // options that ask for FFT passes (bits)
+    int tuned[3] = {0, 16, 16};         // setup's register variant and lines per workgroup (FP32, FP64)
+    int tap_r = 0;                      // tap radius: the largest ceil(a~) - 1 of the axes
+    double tap_t[3][5][4] = {};         // taps t_e(o) of each axis, o = 0..3
+    int tap_nt[2] = {0, 0};             // tiles along x and y
+    int tap_cus = 256;                  // compute units of the device
+    int2* tap_zr = nullptr;             // first and last domain plane of each tile column
+    void* tap = nullptr;                // class words and records of the K-type product in use
 };
 
 constexpr int kRedBlocks = 1024;   // reduction partials per right-hand side (at most)
@@ -290,8 +301,28 @@ void launch_reg_k(const Ctx& c, const float* in, float* out, const uint8_t* mask
                   double* dot_part, const float* dot_with, hipStream_t st, const RegProf& prof,
                   const RegPupd* pu = nullptr);
 
+// Direct tap kernels (tapconv.hip): the operators of Alg 2-4 in one launch for
+// kernels of short support.  tap_setup (once) keeps the taps t[axis][e][o] and
+// the domain's extent per tile; tap_build makes the words and records of the
+// coefficient rows in use; tap_active tells whether the current product can
+// run on them; tap_blocks is the number of workgroups (and so of dot partials)
+// per right-hand side, at most tap_dot_slots.
+void tap_setup(Ctx& c, const double (*taps)[5][4], hipStream_t st);
+void tap_build(Ctx& c, hipStream_t st);
+bool tap_active(const Ctx& c);
+long tap_blocks(const Ctx& c, int nrhs, int elem_bytes);
+long tap_dot_slots(const Ctx& c);
+void tap_release(Ctx& c);
+void tap_release_set(void*& s);
+template <typename T, typename Tio>
+void launch_tap(const Ctx& c, int mode, const Tio* in, Tio* out, const uint8_t* mask_in,
+                const uint8_t* mask_out, const T* vol, int nrhs, double* dot_part, const void* dot_with,
+                long dot_stride, hipStream_t st);
+
 // throws the library's FCRKPM_ERR_UNSUPPORTED status with this message
 [[noreturn]] void raise_unsupported(const char* msg);
+// throws FCRKPM_ERR_HIP (FCRKPM_ERR_OOM for an allocation) with this message
+[[noreturn]] void raise_hip(hipError_t e, const char* what);
 
 // LDS bytes the passes of a plan need at the tile widths they will use
 size_t sep_lds_need(const Ctx& c, const SepPlan& sp, int elem_bytes);

@@ -1,0 +1,382 @@
+// tapconv.hip -- setup and dispatch of the direct tap kernels (tapconv.hpp).
+#include <hip/hip_ext.h>
+#include <hip/hip_runtime.h>
+
+#include <math.h>
+#include <string.h>
+
+#include <algorithm>
+
+#include "tap_list.hpp"
+
+namespace fcrkpm {
+
+namespace {
+
+struct TapSet {
+    uint32_t* words = nullptr;
+    float* rec32 = nullptr;
+    double* rec64 = nullptr;
+    float m32[kTapMint] = {};
+    double m64[kTapMint] = {};
+};
+
+void tap_check(hipError_t e)
+{
+    if (e != hipSuccess) raise_hip(e, "direct tap records");
+}
+
+template <typename U>
+U* tap_alloc(size_t n)
+{
+    void* p = nullptr;
+    tap_check(hipMalloc(&p, std::max<size_t>(n, 1) * sizeof(U)));
+    return reinterpret_cast<U*>(p);
+}
+
+void tap_free(TapSet* s)
+{
+    if (!s) return;
+    if (s->words) (void)hipFree(s->words);
+    if (s->rec32) (void)hipFree(s->rec32);
+    if (s->rec64) (void)hipFree(s->rec64);
+    delete s;
+}
+
+int tile_x(const Ctx& c) { return c.dim == 1 ? TapTile<1>::TX : TapTile<3>::TX; }
+int tile_y(const Ctx& c) { return c.dim == 1 ? TapTile<1>::TY : TapTile<3>::TY; }
+int tap_gx(const Ctx& c)
+{
+    const int tx = tile_x(c);
+    return (c.n[0] + tx - 1) / tx * (tx / 2) + c.tap_r;
+}
+
+// first and last plane with a domain node per tile column
+__global__ __launch_bounds__(256) void k_tap_extent(const uint8_t* __restrict__ chi, int nx, int ny, int nz,
+                                                    int ntx, int tx, int ty, int2* __restrict__ zr)
+{
+    __shared__ int lo, hi;
+    if (threadIdx.x == 0) {
+        lo = nz;
+        hi = -1;
+    }
+    __syncthreads();
+    const int x0 = (blockIdx.x % ntx) * tx, y0 = (blockIdx.x / ntx) * ty;
+    const int w = min(tx, nx - x0), h = min(ty, ny - y0);
+    int l = nz, u = -1;
+    for (long i = threadIdx.x; i < (long)w * h * nz; i += blockDim.x) {
+        const int z = (int)(i / (w * h)), k = (int)(i % (w * h));
+        if (chi[((long)z * ny + y0 + k / w) * nx + x0 + k % w]) {
+            l = min(l, z);
+            u = max(u, z);
+        }
+    }
+    atomicMin(&lo, l);
+    atomicMax(&hi, u);
+    __syncthreads();
+    if (threadIdx.x == 0) zr[blockIdx.x] = int2{lo, hi};
+}
+
+// Class words and records.  A word covers two nodes along x: two bits of class
+// each (0 outside the domain, 1 interior, 2 with a record of its own) and the
+// index of the first record.  FILL = false counts the records, FILL = true
+// hands out their places block by block and writes them.
+template <bool FILL>
+__global__ __launch_bounds__(256) void k_tap_words(const uint8_t* __restrict__ cls,
+                                                   const uint8_t* __restrict__ chi, int nx, int ny, int nz,
+                                                   int gx, int r, const double* __restrict__ ba,
+                                                   const double* __restrict__ vol, int rows, int s, int mform,
+                                                   int rp32, int rp64, unsigned long long* __restrict__ count,
+                                                   uint32_t* __restrict__ words, float* __restrict__ rec32,
+                                                   double* __restrict__ rec64)
+{
+    const long total = (long)nz * ny * gx, nn = (long)nx * ny * nz;
+    __shared__ unsigned int wsum[4];
+    __shared__ unsigned long long base;
+    for (long b0 = (long)blockIdx.x * 256; b0 < total; b0 += (long)gridDim.x * 256) {
+        const long i = b0 + threadIdx.x;
+        int k[2] = {0, 0};
+        long g[2] = {0, 0};
+        if (i < total) {
+            const int gi = (int)(i % gx);
+            const long row = i / gx * nx;
+            for (int j = 0; j < 2; ++j) {
+                int x = (2 * gi - r + j) % nx;
+                if (x < 0) x += nx;
+                g[j] = row + x;
+                k[j] = cls ? cls[g[j]] : (chi[g[j]] ? 2 : 0);
+            }
+        }
+        const unsigned int n2 = (k[0] == 2) + (k[1] == 2);
+        unsigned int scan = n2;
+        for (int o = 1; o < 64; o <<= 1) {
+            const unsigned int v = __shfl_up(scan, o, 64);
+            if ((threadIdx.x & 63) >= (unsigned)o) scan += v;
+        }
+        if ((threadIdx.x & 63) == 63) wsum[threadIdx.x >> 6] = scan;
+        __syncthreads();
+        if (threadIdx.x == 0) base = atomicAdd(count, (unsigned long long)(wsum[0] + wsum[1] + wsum[2] + wsum[3]));
+        __syncthreads();
+        if constexpr (FILL) {
+            unsigned long long at = base + scan - n2;
+            for (unsigned w = 0; w < threadIdx.x >> 6; ++w) at += wsum[w];
+            if (i < total) {
+                words[i] = (uint32_t)k[0] | (uint32_t)k[1] << 2 | (uint32_t)at << 4;
+                for (int j = 0; j < 2; ++j) {
+                    if (k[j] != 2) continue;
+                    float* f = rec32 + (size_t)at * rp32;
+                    double* d = rec64 + (size_t)at * rp64;
+                    int n = 0;
+                    if (mform) {
+                        for (int p = 0; p < s; ++p)
+                            for (int q = p; q < s; ++q) {
+                                double acc = 0.0;
+                                for (int a = 0; a < rows; ++a)
+                                    acc += ba[(long)(a * s + p) * nn + g[j]] * ba[(long)(a * s + q) * nn + g[j]];
+                                d[n++] = vol[g[j]] * acc;
+                            }
+                    } else {
+                        for (int q = 0; q < rows * s; ++q) d[n++] = ba[(long)q * nn + g[j]];
+                        d[n++] = vol[g[j]];
+                    }
+                    for (int q = 0; q < n; ++q) f[q] = (float)d[q];
+                    for (int q = n; q < rp32; ++q) f[q] = 0.0f;
+                    for (int q = n; q < rp64; ++q) d[q] = 0.0;
+                    ++at;
+                }
+            }
+        }
+        __syncthreads();
+    }
+}
+
+// values one workgroup keeps in LDS (TapGeom of a K product)
+int tap_lds(const Ctx& c)
+{
+    const int r = c.tap_r, d = c.degree, dim = c.dim, tx = tile_x(c), ty = tile_y(c);
+    const int ry = dim > 1 ? r : 0;
+    const int nz = dim > 2 ? d + 1 : 1;
+    const int ny = dim > 2 ? (d + 1) * (d + 2) / 2 : dim > 1 ? d + 1 : 1;
+    const int xe = tx + 2 * r, ye = ty + 2 * ry, xl = xe + 2 * r, yl = ye + 2 * ry;
+    return nz * yl * xl + ny * ye * xl + c.s * ye * xe + ny * ye * tx;
+}
+
+// Planes per chunk.  A chunk of cz planes takes cz + 4R + 2 steps, so few long
+// chunks do the least work, but the workgroups have to fill the chip evenly: a
+// step with r workgroups on a CU takes about 0.9 + 0.6 r (us at R = 2 in FP32;
+// measured 1.6, 2.0 and 2.7 for r = 1, 2, 3), and a last round that fills a
+// few CUs takes as long as a full one.
+int tap_planes_for(const Ctx& c, int nrhs, int elem)
+{
+    if (c.dim < 3) return 1;
+    const long tiles = (long)c.tap_nt[0] * c.tap_nt[1] * nrhs;
+    const int occ = tap_residents(elem, tap_lds(c), tap_cap(elem, c.s, c.tap_r)), nz = c.n[2];
+    const double slots = (double)c.tap_cus * occ;
+    int best = nz;
+    double cost = 1e300;
+    for (int k = 1; k <= nz; ++k) {
+        const int cz = (nz + k - 1) / k;
+        if ((nz + cz - 1) / cz != k) continue;
+        const double wg = (double)tiles * k, full = floor(wg / slots), rem = wg - full * slots;
+        const double t = (cz + 4 * c.tap_r + 2) *
+                         (full * (0.9 + 0.6 * occ) +
+                          (rem > 0.0 ? 0.9 + 0.6 * std::max(1.0, rem / c.tap_cus) : 0.0));
+        if (t < cost) {
+            cost = t;
+            best = cz;
+        }
+    }
+    return best;
+}
+
+// more right-hand sides never cut finer than one (the dot partials of one fit
+// the slots of any)
+int tap_planes(const Ctx& c, int nrhs, int elem)
+{
+    const int cz = tap_planes_for(c, nrhs, elem);
+    return nrhs > 1 ? std::max(cz, tap_planes_for(c, 1, elem)) : cz;
+}
+
+}  // namespace
+
+// The direct kernels serve taps of radius 1 to 3 for the linear bases, and for
+// the higher ones the radii that their moment matrices need.
+static bool tap_radius_ok(int dim, int degree, int r)
+{
+    if (r < 1 || r > kTapR) return false;
+    if (dim < 3 || degree > 1) return false;
+    if (degree == 1) return true;
+    if (degree == 2) return r >= 2;
+    return dim < 3 && r == 3;
+}
+
+bool tap_active(const Ctx& c) { return c.use_taps && !c.fft_pins && c.tap; }
+
+long tap_blocks(const Ctx& c, int nrhs, int elem)
+{
+    const int cz = tap_planes(c, nrhs, elem);
+    return (long)c.tap_nt[0] * c.tap_nt[1] * ((c.n[2] + cz - 1) / cz);
+}
+
+long tap_dot_slots(const Ctx& c) { return c.tap ? std::max(tap_blocks(c, 1, 4), tap_blocks(c, 1, 8)) : 0; }
+
+void tap_release_set(void*& s)
+{
+    tap_free((TapSet*)s);
+    s = nullptr;
+}
+
+void tap_release(Ctx& c)
+{
+    tap_release_set(c.tap);
+    if (c.tap_zr) (void)hipFree(c.tap_zr);
+    c.tap_zr = nullptr;
+}
+
+// taps and the domain's extent per tile column (once per context)
+void tap_setup(Ctx& c, const double (*taps)[kTapE][kTapR + 1], hipStream_t st)
+{
+    memcpy(c.tap_t, taps, sizeof(c.tap_t));
+    int dev = 0;
+    tap_check(hipGetDevice(&dev));
+    tap_check(hipDeviceGetAttribute(&c.tap_cus, hipDeviceAttributeMultiprocessorCount, dev));
+    const int tx = tile_x(c), ty = tile_y(c);
+    c.tap_nt[0] = (c.n[0] + tx - 1) / tx;
+    c.tap_nt[1] = (c.n[1] + ty - 1) / ty;
+    c.tap_zr = tap_alloc<int2>((size_t)c.tap_nt[0] * c.tap_nt[1]);
+    hipLaunchKernelGGL(k_tap_extent, dim3(c.tap_nt[0] * c.tap_nt[1]), dim3(256), 0, st, c.chi, c.n[0], c.n[1],
+                       c.n[2], c.tap_nt[0], tx, ty, c.tap_zr);
+    tap_check(hipGetLastError());
+}
+
+// words and records of the coefficient rows in use (c.ba_64, c.krows, c.cls)
+void tap_build(Ctx& c, hipStream_t st)
+{
+    if (!tap_radius_ok(c.dim, c.degree, c.tap_r)) return;
+    TapSet* s = new TapSet();
+    c.tap = s;
+    const bool mf = c.degree == 1;
+    const int nv = tap_rec_values(mf, c.s, c.krows);
+    if (nv > kTapMint) {
+        tap_release_set(c.tap);
+        return;
+    }
+    const int rp32 = tap_rec_pitch(mf, c.s, c.krows, 4), rp64 = tap_rec_pitch(mf, c.s, c.krows, 8);
+    if (c.cls && c.nconst.bmax >= 0.0) {
+        const NodeConst& nc = c.nconst;
+        int n = 0;
+        if (mf) {
+            for (int p = 0; p < c.s; ++p)
+                for (int q = p; q < c.s; ++q) {
+                    double acc = 0.0;
+                    for (int a = 0; a < c.krows; ++a) acc += nc.b[a * c.s + p] * nc.b[a * c.s + q];
+                    s->m64[n++] = nc.v * acc;
+                }
+        } else {
+            for (int q = 0; q < c.krows * c.s; ++q) s->m64[n++] = nc.b[q];
+            s->m64[n++] = nc.v;
+        }
+        for (int q = 0; q < n; ++q) s->m32[q] = (float)s->m64[q];
+    }
+    const int gx = tap_gx(c);
+    const size_t total = (size_t)c.n[2] * c.n[1] * gx;
+    s->words = tap_alloc<uint32_t>(total);
+    unsigned long long* cnt = reinterpret_cast<unsigned long long*>(c.dflag + 4);
+    const unsigned blocks = (unsigned)std::min<size_t>((total + 255) / 256, 4096);
+    const unsigned long long zero = 0;
+    unsigned long long n = 0;
+    tap_check(hipMemcpyAsync(cnt, &zero, sizeof(zero), hipMemcpyHostToDevice, st));
+    hipLaunchKernelGGL(k_tap_words<false>, dim3(blocks), dim3(256), 0, st, c.cls, c.chi, c.n[0], c.n[1], c.n[2],
+                       gx, c.tap_r, c.ba_64, c.vol64, c.krows, c.s, mf ? 1 : 0, rp32, rp64, cnt, s->words,
+                       (float*)nullptr, (double*)nullptr);
+    tap_check(hipMemcpyAsync(&n, cnt, sizeof(n), hipMemcpyDeviceToHost, st));
+    tap_check(hipStreamSynchronize(st));
+    if (n + 2 >= (1ull << 28)) {  // a word holds 28 bits of record index
+        tap_release_set(c.tap);
+        return;
+    }
+    n += 2;  // records 0 and 1: a node outside the domain (zero) and the interior nodes'
+    s->rec32 = tap_alloc<float>((size_t)n * rp32);
+    s->rec64 = tap_alloc<double>((size_t)n * rp64);
+    std::vector<float> h32((size_t)2 * rp32, 0.0f);
+    std::vector<double> h64((size_t)2 * rp64, 0.0);
+    std::copy(s->m32, s->m32 + nv, h32.begin() + rp32);
+    std::copy(s->m64, s->m64 + nv, h64.begin() + rp64);
+    tap_check(hipMemcpyAsync(s->rec32, h32.data(), h32.size() * sizeof(float), hipMemcpyHostToDevice, st));
+    tap_check(hipMemcpyAsync(s->rec64, h64.data(), h64.size() * sizeof(double), hipMemcpyHostToDevice, st));
+    const unsigned long long first = 2;
+    tap_check(hipMemcpyAsync(cnt, &first, sizeof(first), hipMemcpyHostToDevice, st));
+    hipLaunchKernelGGL(k_tap_words<true>, dim3(blocks), dim3(256), 0, st, c.cls, c.chi, c.n[0], c.n[1], c.n[2],
+                       gx, c.tap_r, c.ba_64, c.vol64, c.krows, c.s, mf ? 1 : 0, rp32, rp64, cnt, s->words,
+                       s->rec32, s->rec64);
+    tap_check(hipGetLastError());
+    tap_check(hipStreamSynchronize(st));
+}
+
+template <typename T, typename Tio>
+void launch_tap(const Ctx& c, int mode, const Tio* in, Tio* out, const uint8_t* mask_in,
+                const uint8_t* mask_out, const T* vol, int nrhs, double* dot_part, const void* dot_with,
+                long dot_stride, hipStream_t st)
+{
+    const TapSet& s = *(const TapSet*)c.tap;
+    TapArgs<T> a = {};
+    a.in = in;
+    a.out = out;
+    a.mask_in = mask_in;
+    a.mask_out = mask_out;
+    for (int k = 0; k < 3; ++k) {
+        a.n[k] = c.n[k];
+        for (int e = 0; e < kTapE; ++e)
+            for (int o = 0; o <= kTapR; ++o) a.t[k][e][o] = (T)c.tap_t[k][e][o];
+    }
+    a.ntx = c.tap_nt[0];
+    a.nty = c.tap_nt[1];
+    a.cz = tap_planes(c, nrhs, sizeof(T));
+    a.zr = c.tap_zr;
+    a.words = s.words;
+    a.gx = tap_gx(c);
+    if constexpr (sizeof(T) == 8) {
+        a.rec = s.rec64;
+        memcpy(a.mint, s.m64, sizeof(a.mint));
+        a.b0 = c.b0_64;
+    } else {
+        a.rec = s.rec32;
+        memcpy(a.mint, s.m32, sizeof(a.mint));
+        a.b0 = c.b0_32;
+    }
+    a.vol = vol;
+    a.kappa = (T)c.pw_kappa;
+    a.dot_part = dot_part;
+    a.dot_with = dot_with;
+    a.dot_stride = dot_stride;
+    a.nn = c.nn;
+    a.rb = c.nn * (long)sizeof(Tio);
+    const dim3 grid((unsigned)tap_blocks(c, nrhs, sizeof(T)), (unsigned)nrhs);
+    const int rows = (mode == TAP_K && c.degree > 1) ? c.krows : c.dim;
+    bool done = false;
+#define FC_TAP_CASE(T_, TIO_, DIM, DEG, R, MODE, ROWS)                                              \
+    if (!done && c.dim == DIM && c.degree == DEG && c.tap_r == R && mode == MODE && rows == ROWS) { \
+        tap_go<T_, TIO_, TapBasis<DIM, DEG>, R, MODE, ROWS>(a, grid, st);                       \
+        done = true;                                                                                \
+    }
+    if constexpr (sizeof(T) == 8) {
+        FC_TAP_F64(FC_TAP_CASE)
+    } else if constexpr (sizeof(Tio) == 4) {
+        FC_TAP_F32(FC_TAP_CASE)
+    } else {
+        FC_TAP_MIX(FC_TAP_CASE)
+    }
+#undef FC_TAP_CASE
+    if (!done) raise_unsupported("internal: no direct kernel for this basis");
+}
+
+template void launch_tap<float, float>(const Ctx&, int, const float*, float*, const uint8_t*, const uint8_t*,
+                                       const float*, int, double*, const void*, long, hipStream_t);
+template void launch_tap<double, double>(const Ctx&, int, const double*, double*, const uint8_t*,
+                                         const uint8_t*, const double*, int, double*, const void*, long,
+                                         hipStream_t);
+template void launch_tap<float, double>(const Ctx&, int, const double*, double*, const uint8_t*,
+                                        const uint8_t*, const float*, int, double*, const void*, long,
+                                        hipStream_t);
+
+}  // namespace fcrkpm

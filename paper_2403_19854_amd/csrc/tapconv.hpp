@@ -1,0 +1,701 @@
+// tapconv.hpp -- the operators of Alg 2-4 in one launch, for short supports.
+//
+// A convolving array of the method is a monomial times a tensor-product kernel
+// of compact support (Eq 6, 44, 77): along an axis it has 2R + 1 taps,
+// t_e(o) = o^e phi(o / a~) for |o| <= R = ceil(a~) - 1.  The circular
+// convolutions of Eq 34 can then be summed directly, axis by axis; with R <= 3
+// that is 5 to 7 multiply-adds per value, and because a direct sum needs only
+// R neighbours, both halves of a product and the pointwise stage between them
+// fit one kernel that reads d and writes f once:
+//
+//   part 1   u -> z-convolutions -> y-convolutions -> D_q (x-convolutions)
+//   point    E = M D, M = V B^T B   (rows of b^a; Eq 90-91, Alg 2)
+//   part 2   E_p -> x -> y -> z with the reflected taps (Eq 55, 91)
+//
+// A workgroup owns TX x TY columns of the result and marches through a chunk
+// of planes.  z is the first axis of part 1 and the last of part 2, so both z
+// convolutions run in registers: an incoming plane is kept for 2R
+// more steps, a plane of part 2 is added to the 2R + 1 pending sums of its
+// column, and only the x and y convolutions exchange values through LDS.  The work of one
+// plane is cut into five phases that run as a software pipeline over three
+// planes, in two halves per step:
+//
+//   half A   Z -> sZ (plane p)     sY -> D, E -> sE (p - 1)   sF -> y, z, store (p - 2)
+//   half B   sZ -> sY (plane p)    sE -> sF (p - 1)
+//
+// Every buffer is written in one half and read in the other, so one copy of
+// each and two barriers per plane suffice.
+#pragma once
+#include <hip/hip_runtime.h>
+
+#include <type_traits>
+
+#include "fcrkpm_impl.hpp"
+
+namespace fcrkpm {
+
+constexpr int kTapR = 3;          // largest tap radius
+constexpr int kTapE = 5;          // exponents 0..4 (moments of the quadratic basis)
+constexpr int kTapMint = 41;      // interior constants: rows (dim + 1) * s of the quadratic basis, and V
+
+enum { TAP_K = 0, TAP_UH = 1, TAP_LOAD = 2, TAP_KN = 3 };
+
+// Monomials of degree <= DEG in DIM variables (the library's basis order), as
+// the tree the passes walk: fields after z (exponent ez), after y (ey, ez),
+// and the basis itself (ex on y field yf).
+template <int DIM_, int DEG_>
+struct TapBasis {
+    static constexpr int DIM = DIM_, DEG = DEG_;
+    static constexpr int NZ = DIM > 2 ? DEG + 1 : 1;
+    static constexpr int NY = DIM > 2 ? (DEG + 1) * (DEG + 2) / 2 : DIM > 1 ? DEG + 1 : 1;
+    static constexpr int S = DIM == 1   ? DEG + 1
+                             : DIM == 2 ? (DEG + 1) * (DEG + 2) / 2
+                                        : (DEG + 1) * (DEG + 2) * (DEG + 3) / 6;
+    struct Tab {
+        int yey[NY], yez[NY];
+        int xex[S], xyf[S];
+    };
+    static constexpr Tab make()
+    {
+        Tab t{};
+        int n = 0;
+        for (int d = 0; d <= DEG; ++d)
+            for (int b = d; b >= 0; --b) {
+                const int c = d - b;
+                if (DIM < 2 && b != 0) continue;
+                if (DIM < 3 && c != 0) continue;
+                t.yey[n] = b;
+                t.yez[n] = c;
+                ++n;
+            }
+        int k = 0;
+        for (int d = 0; d <= DEG; ++d)
+            for (int a = d; a >= 0; --a)
+                for (int b = d - a; b >= 0; --b) {
+                    const int c = d - a - b;
+                    if (DIM < 2 && b != 0) continue;
+                    if (DIM < 3 && c != 0) continue;
+                    t.xex[k] = a;
+                    for (int f = 0; f < NY; ++f)
+                        if (t.yey[f] == b && t.yez[f] == c) t.xyf[k] = f;
+                    ++k;
+                }
+        return t;
+    }
+    static constexpr Tab tab = make();
+};
+
+template <typename T>
+struct TapArgs {
+    const void* in;            // field (Tio)
+    void* out;                 // field (Tio)
+    const uint8_t* mask_in;
+    const uint8_t* mask_out;
+    T t[3][kTapE][kTapR + 1];  // t[axis][e][o], o = 0..R
+    int n[3];
+    int ntx, nty;              // tiles along x and y
+    int cz;                    // planes per chunk
+    const int2* zr;            // per tile column: first and last plane with a domain node
+    const uint32_t* words;     // [nz][ny][gx]: classes and first record of two nodes
+    int gx;                    // words per row (the row starts R nodes before x = 0)
+    const T* rec;              // records of the class-2 nodes
+    T mint[kTapMint];          // record of the interior nodes
+    const T* b0;               // [s][nn] (UH, LOAD)
+    const T* vol;              // [nn] or NULL (UH, LOAD)
+    T kappa;                   // KN
+    double* dot_part;          // per-workgroup partials of out . dot_with, or NULL
+    const void* dot_with;
+    long dot_stride;           // partial slots between right-hand sides
+    long nn;
+    long rb;                   // bytes between right-hand sides of in and out
+};
+
+// A record holds M = V B^T B (upper triangle) for the linear bases, where the
+// product with M costs no more than the two with B; the others keep the rows
+// of B and V.  Padded to whole 16-byte loads.
+template <class B, int MODE>
+constexpr bool tap_mform() { return B::DEG == 1 && MODE != TAP_KN; }
+constexpr int tap_rec_values(bool mform, int s, int rows) { return mform ? s * (s + 1) / 2 : rows * s + 1; }
+constexpr int tap_rec_pitch(bool mform, int s, int rows, int elem)
+{
+    const int per = 16 / elem;
+    return (tap_rec_values(mform, s, rows) + per - 1) / per * per;
+}
+
+// LDS traffic alone is ordered here: global loads in flight stay in flight.
+__device__ __forceinline__ void tap_barrier()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+template <typename T>
+struct alignas(2 * sizeof(T)) TapPair {
+    T x, y;
+};
+
+// f(0), f(1), ... with the index as a constant: the basis tables and the taps
+// they pick are resolved when the kernel is compiled
+template <int N, int I = 0, typename F>
+__device__ __forceinline__ void tap_for(F&& f)
+{
+    if constexpr (I < N) {
+        f(std::integral_constant<int, I>{});
+        tap_for<N, I + 1>(f);
+    }
+}
+
+// sum over the taps of exponent E at the window centre w[R]: the convolution
+// sum_o t_e(o) u(I - o), or with REFL its reflection sum_o t_e(o) u(I + o).
+// t_e is even or odd with e, so two neighbours share a tap.
+template <int R, bool REFL, int E, typename T, typename TP>
+__device__ __forceinline__ T tap_conv(const T* w, const TP& t)
+{
+    if constexpr (R == 0) {
+        return w[0];
+    } else {
+        T acc = (E == 0) ? t[0] * w[R] : T(0);
+#pragma unroll
+        for (int o = 1; o <= R; ++o) {
+            const T lo = w[R - o], hi = w[R + o];
+            const T v = (E & 1) ? (REFL ? hi - lo : lo - hi) : lo + hi;
+            acc = (E > 0 && o == 1) ? t[o] * v : acc + t[o] * v;
+        }
+        return acc;
+    }
+}
+
+__device__ __forceinline__ int tap_wrap(int i, int n)
+{
+    i %= n;
+    return i < 0 ? i + n : i;
+}
+
+__device__ __forceinline__ long tap_xcd(long b, long nblocks)
+{
+    if (nblocks % 8 != 0) return b;
+    return (b & 7) * (nblocks >> 3) + (b >> 3);
+}
+
+// Sizes of one variant.
+template <class B, int R, int MODE, int TX, int TY>
+struct TapGeom {
+    static constexpr bool P1 = MODE != TAP_LOAD, P2 = MODE != TAP_UH;
+    static constexpr int RX = R, RY = B::DIM > 1 ? R : 0, RZ = B::DIM > 2 ? R : 0;
+    static constexpr int HX = P2 ? RX : 0, HY = P2 ? RY : 0, HZ = P2 ? RZ : 0;
+    static constexpr int XE = TX + 2 * HX, YE = TY + 2 * HY;  // where D and E are formed
+    static constexpr int XL = XE + 2 * RX, YL = YE + 2 * RY;  // where u is read
+    static constexpr int NSZ = P1 ? B::NZ * YL * XL : 0, NSY = P1 ? B::NY * YE * XL : 0;
+    static constexpr int NSE = P2 ? B::S * YE * XE : 0, NSF = P2 ? B::NY * YE * TX : 0;
+    static constexpr int LDS = NSZ + NSY + NSE + NSF;
+};
+
+template <class B, int R, int MODE, int TX, int TY>
+constexpr int tap_lds_of = TapGeom<B, R, MODE, TX, TY>::LDS;
+// Workgroups that the LDS of a CU (160 KB) holds, at most `cap`; the registers are
+// held to what that needs (waves per SIMD).
+constexpr int tap_residents(int elem, int lds, int cap)
+{
+    const int n = 160 * 1024 / (elem * lds + 64);
+    return n < 1 ? 1 : n > cap ? cap : n;
+}
+constexpr int tap_cap(int elem, int s, int r) { return elem == 4 && s <= 4 && r <= 2 ? 3 : 2; }
+constexpr int tap_min_waves(int elem, int lds, int nt, int cap) { return tap_residents(elem, lds, cap) * (nt / 64) / 4; }
+
+// The arguments live in the kernel-argument segment.  Every phase reads the
+// taps it needs from there again (scalar loads that hit the constant cache):
+// held in scalar registers all at once they would not fit.
+template <typename T>
+using TapArgPtr = const __attribute__((address_space(4))) TapArgs<T>*;
+
+template <typename P>
+__device__ __forceinline__ P tap_fresh(P p)
+{
+    asm volatile("" : "+s"(p));
+    return p;
+}
+
+// Threads of one variant.  Half A gives D and E to the first NA threads and
+// the y and z reflections to the other NB; half B gives the y convolutions to
+// the first N2 threads and the x reflections to the rest.  SPLIT = false (1D)
+// lets every thread do everything.
+template <int DIM, int NT>
+struct TapRoles {
+    static constexpr bool SPLIT = DIM > 1;
+    static constexpr int NA = SPLIT ? NT * 3 / 4 : NT, NB = SPLIT ? NT - NA : NT;
+    static constexpr int N2 = SPLIT ? NT / 2 : NT, N4 = SPLIT ? NT - N2 : NT;
+};
+
+// One workgroup's march; ROLE bit 0: D and E, bit 1: the reflections along y and z.
+template <typename T, typename Tio, class B, int R, int MODE, int ROWS, int TX, int TY, int NT, int ROLE>
+struct TapMarch {
+    using G = TapGeom<B, R, MODE, TX, TY>;
+    using RO = TapRoles<B::DIM, NT>;
+    using KP = TapArgPtr<T>;
+    static constexpr int S = B::S, NZ = B::NZ, NY = B::NY;
+    static constexpr int RY = G::RY, RZ = G::RZ, HX = G::HX, HY = G::HY, HZ = G::HZ;
+    static constexpr int XE = G::XE, YE = G::YE, XL = G::XL, YL = G::YL;
+    static constexpr bool KMODE = MODE == TAP_K || MODE == TAP_KN;
+    static constexpr int NC = G::P1 ? (XL * YL + NT - 1) / NT : 1;          // input columns per thread
+    static constexpr int NB2 = YE % 4 == 0 ? 4 : YE % 2 == 0 ? 2 : 1;       // rows per item, y convolution
+    static constexpr int XB4 = 4;                                           // nodes per item, x reflection
+    static constexpr int NB5 = TY % 4 == 0 ? 4 : 1;                         // rows per item, y reflection
+    static constexpr int N3 = XE / 2 * YE, NP3 = (N3 + RO::NA - 1) / RO::NA;
+    static constexpr int N5 = TX * (TY / NB5);
+    static_assert((!G::P2 || N5 <= RO::NB) && XE % 2 == 0 && TX % XB4 == 0);
+    static constexpr bool MF = tap_mform<B, MODE>();
+    static constexpr int RP = tap_rec_pitch(MF, S, ROWS, sizeof(T));
+    static constexpr bool A = (ROLE & 1) != 0, Bq = (ROLE & 2) != 0 && G::P2;
+
+    // x convolutions of two nodes: D[i][q] from the y-level fields
+    static __device__ __forceinline__ void x_conv(const T* sY, int yy, int gi, KP k, T (&D)[2][S])
+    {
+        tap_for<NY>([&](auto fc) {
+            constexpr int f = decltype(fc)::value;
+            T w[2 + 2 * R];
+            const TapPair<T>* src = reinterpret_cast<const TapPair<T>*>(sY + (f * YE + yy) * XL + 2 * gi);
+#pragma unroll
+            for (int j = 0; j <= R; ++j) {
+                const TapPair<T> v = src[j];
+                w[2 * j] = v.x;
+                w[2 * j + 1] = v.y;
+            }
+            tap_for<S>([&](auto qc) {
+                constexpr int q = decltype(qc)::value;
+                if constexpr (B::tab.xyf[q] == f) {
+                    constexpr int e = B::tab.xex[q];
+                    D[0][q] = tap_conv<R, false, e>(w, k->t[0][e]);
+                    D[1][q] = tap_conv<R, false, e>(w + 1, k->t[0][e]);
+                }
+            });
+        });
+    }
+
+    // E = M D, or V B^T (f B D) with the rows of B (f = 1 but for KN)
+    template <typename M>
+    static __device__ __forceinline__ void point(const M& m, KP k, const T (&D)[S], T (&E)[S])
+    {
+        if constexpr (MF) {
+#pragma unroll
+            for (int p = 0; p < S; ++p) {
+                T acc = T(0);
+#pragma unroll
+                for (int q = 0; q < S; ++q) {
+                    const int lo = p < q ? p : q, hi = p < q ? q : p;
+                    acc += m[lo * S - lo * (lo - 1) / 2 + hi - lo] * D[q];
+                }
+                E[p] = acc;
+            }
+        } else {
+            T v = m[ROWS * S];
+            T Ar[ROWS];
+#pragma unroll
+            for (int r = 0; r < ROWS; ++r) {
+                T acc = T(0);
+#pragma unroll
+                for (int q = 0; q < S; ++q) acc += m[r * S + q] * D[q];
+                Ar[r] = acc;
+            }
+            if constexpr (MODE == TAP_KN) {
+                T s2 = T(0);
+#pragma unroll
+                for (int r = 0; r < ROWS; ++r) s2 += Ar[r] * Ar[r];
+                v *= T(1) + k->kappa * s2;
+            }
+#pragma unroll
+            for (int r = 0; r < ROWS; ++r) Ar[r] *= v;
+#pragma unroll
+            for (int p = 0; p < S; ++p) {
+                T acc = T(0);
+#pragma unroll
+                for (int r = 0; r < ROWS; ++r) acc += m[r * S + p] * Ar[r];
+                E[p] = acc;
+            }
+        }
+    }
+
+    static __device__ __forceinline__ uint32_t rec_at(uint32_t w, int i)
+    {
+        const uint32_t c = (w >> (2 * i)) & 3;
+        return c == 2 ? (w >> 4) + ((i && (w & 3) == 2) ? 1u : 0u) : c;
+    }
+
+    static __device__ __forceinline__ double run(KP kp, T* smem, const Tio* in, Tio* out, const Tio* dwith, int x0,
+                                                 int y0, int zlo, int zhi)
+    {
+        T* const sZ = smem;
+        T* const sY = sZ + G::NSZ;
+        T* const sE = sY + G::NSY;
+        T* const sF = sE + G::NSE;
+        const int tid = threadIdx.x;
+        const int nx = kp->n[0], ny = kp->n[1], nz = kp->n[2], nxy = nx * ny, gx = kp->gx;
+        const uint8_t* const mask_in = kp->mask_in;
+        const uint8_t* const mask_out = kp->mask_out;
+        double dacc = 0.0;
+
+        // input columns of this thread
+        uint32_t col[NC];
+        if constexpr (G::P1) {
+#pragma unroll
+            for (int k = 0; k < NC; ++k) {
+                const int c = min(tid + k * NT, XL * YL - 1);
+                col[k] = (uint32_t)(tap_wrap(y0 - HY - RY + c / XL, ny) * nx + tap_wrap(x0 - HX - R + c % XL, nx));
+            }
+        }
+        // E-level items: two nodes along x.  K modes: word offset in a plane;
+        // UH, LOAD: offsets of the two nodes
+        uint32_t it3[NP3], jt3[NP3];
+        if constexpr (A) {
+#pragma unroll
+            for (int k = 0; k < NP3; ++k) {
+                const int it = min(tid + k * RO::NA, N3 - 1);
+                const int gi = it % (XE / 2), gy = tap_wrap(y0 - HY + it / (XE / 2), ny);
+                if constexpr (KMODE) {
+                    it3[k] = (uint32_t)(gy * gx + x0 / 2 + gi);
+                } else {
+                    it3[k] = (uint32_t)(gy * nx + tap_wrap(x0 - HX + 2 * gi, nx));
+                    jt3[k] = (uint32_t)(gy * nx + tap_wrap(x0 - HX + 2 * gi + 1, nx));
+                }
+            }
+        }
+        T zin[NC][2 * RZ + 1];   // the last planes of each column
+#pragma unroll
+        for (int k = 0; k < NC; ++k)
+#pragma unroll
+            for (int j = 0; j <= 2 * RZ; ++j) zin[k][j] = T(0);
+        const int i5 = RO::SPLIT ? tid - RO::NA : tid;
+        const bool do5 = Bq && i5 >= 0 && i5 < N5;
+        const int x5 = i5 % TX, y5 = i5 / TX * NB5;
+        T zout[NB5][2 * RZ + 1];
+        uint8_t mk5[NB5];
+        bool ok5[NB5];
+        uint32_t o5 = 0;
+        if constexpr (Bq) {
+#pragma unroll
+            for (int k = 0; k < NB5; ++k) {
+#pragma unroll
+                for (int j = 0; j <= 2 * RZ; ++j) zout[k][j] = T(0);
+                ok5[k] = do5 && x0 + x5 < nx && y0 + y5 + k < ny;
+                mk5[k] = 0;
+            }
+            o5 = (uint32_t)((y0 + y5) * nx + x0 + x5);
+        }
+        const int nE = zhi - zlo + 2 * HZ;               // E-level planes
+        int pin = tap_wrap(zlo - HZ - RZ, nz);           // next plane to load
+        int pe = tap_wrap(zlo - HZ, nz);                 // next plane of the E level
+        // values are loaded a step ahead and masked when they are used
+        Tio nxt[NC];
+        uint8_t nmk[NC];
+        if constexpr (G::P1) {
+            const Tio* pi = in + (long)pin * nxy;
+            const uint8_t* pm = mask_in + (long)pin * nxy;
+#pragma unroll
+            for (int k = 0; k < NC; ++k) {
+                nxt[k] = pi[col[k]];
+                nmk[k] = pm[col[k]];
+            }
+        }
+        uint32_t word[NP3];
+        if constexpr (A && KMODE) {
+            const uint32_t* pw = kp->words + (long)pe * ny * gx;
+#pragma unroll
+            for (int k = 0; k < NP3; ++k) word[k] = pw[it3[k]];
+        }
+        const int s0 = G::P1 ? 0 : 2 * RZ + 1, s1 = nE + 2 * RZ + (G::P2 ? 2 : 1);
+        for (int s = s0; s < s1; ++s) {
+            // ---------------------------------------------------------- half A
+            if constexpr (G::P1) {
+                if (s < nE + 2 * RZ) {
+                    const KP k_ = tap_fresh(kp);
+                    T cur[NC];
+#pragma unroll
+                    for (int k = 0; k < NC; ++k) cur[k] = nmk[k] ? T(nxt[k]) : T(0);
+                    if (s + 1 < nE + 2 * RZ) {
+                        pin = (pin + 1 == nz) ? 0 : pin + 1;
+                        const Tio* pi = in + (long)pin * nxy;
+                        const uint8_t* pm = mask_in + (long)pin * nxy;
+#pragma unroll
+                        for (int k = 0; k < NC; ++k) {
+                            nxt[k] = pi[col[k]];
+                            nmk[k] = pm[col[k]];
+                        }
+                    }
+#pragma unroll
+                    for (int k = 0; k < NC; ++k) {
+#pragma unroll
+                        for (int j = 0; j < 2 * RZ; ++j) zin[k][j] = zin[k][j + 1];
+                        zin[k][2 * RZ] = cur[k];
+                    }
+                    if (s >= 2 * RZ) {
+#pragma unroll
+                        for (int k = 0; k < NC; ++k)
+                            if ((k + 1) * NT <= XL * YL || tid + k * NT < XL * YL)
+                                tap_for<NZ>([&](auto ec) {
+                                    constexpr int e = decltype(ec)::value;
+                                    sZ[e * YL * XL + tid + k * NT] = tap_conv<RZ, false, e>(zin[k], k_->t[2][e]);
+                                });
+                    }
+                }
+            }
+            if constexpr (A) {
+                if (s >= 2 * RZ + 1 && s < nE + 2 * RZ + 1) {
+                    const KP k_ = tap_fresh(kp);
+#pragma unroll
+                    for (int k = 0; k < NP3; ++k) {
+                        const int it = tid + k * RO::NA;
+                        if (it < N3) {
+                            const int gi = it % (XE / 2), yy = it / (XE / 2);
+                            T D[2][S];
+                            if constexpr (G::P1) x_conv(sY, yy, gi, k_, D);
+                            if constexpr (MODE == TAP_UH) {
+                                // u = sum_p b0_p D_p (times V for V o N; Eq 94)
+                                const T* b0 = k_->b0 + (long)pe * nxy;
+                                const T* vol = k_->vol ? k_->vol + (long)pe * nxy : nullptr;
+                                Tio* o = out + (long)pe * nxy;
+#pragma unroll
+                                for (int i = 0; i < 2; ++i) {
+                                    if (x0 + 2 * gi + i < nx && y0 + yy < ny) {
+                                        const uint32_t g = i ? jt3[k] : it3[k];
+                                        T acc = T(0);
+#pragma unroll
+                                        for (int p = 0; p < S; ++p) acc += (b0 + p * k_->nn)[g] * D[i][p];
+                                        o[g] = Tio(vol ? acc * vol[g] : acc);
+                                    }
+                                }
+                            } else {
+                                T E[2][S];
+                                if constexpr (MODE == TAP_LOAD) {
+                                    // E_p = (V) b0_p r  (Eq 92, Alg 4)
+                                    const T* b0 = k_->b0 + (long)pe * nxy;
+                                    const T* vol = k_->vol ? k_->vol + (long)pe * nxy : nullptr;
+                                    const Tio* pi = in + (long)pe * nxy;
+#pragma unroll
+                                    for (int i = 0; i < 2; ++i) {
+                                        const uint32_t g = i ? jt3[k] : it3[k];
+                                        const T x = vol ? T(pi[g]) * vol[g] : T(pi[g]);
+#pragma unroll
+                                        for (int p = 0; p < S; ++p) E[i][p] = (b0 + p * k_->nn)[g] * x;
+                                    }
+                                } else if (__all((word[k] & 15) == 5)) {
+                                    // interior nodes throughout the wave: the shared record
+#pragma unroll
+                                    for (int i = 0; i < 2; ++i) point(k_->mint, k_, D[i], E[i]);
+                                } else {
+#pragma unroll
+                                    for (int i = 0; i < 2; ++i)
+                                        point(k_->rec + (size_t)rec_at(word[k], i) * RP, k_, D[i], E[i]);
+                                }
+#pragma unroll
+                                for (int p = 0; p < S; ++p)
+                                    *reinterpret_cast<TapPair<T>*>(sE + (p * YE + yy) * XE + 2 * gi) =
+                                        TapPair<T>{E[0][p], E[1][p]};
+                            }
+                        }
+                    }
+                    if constexpr (!KMODE) pe = (pe + 1 == nz) ? 0 : pe + 1;
+                }
+            }
+            if constexpr (Bq) {
+                if (s >= 2 * RZ + 2 && do5) {
+                    const KP k_ = tap_fresh(kp);
+                    T g[NZ][NB5];
+#pragma unroll
+                    for (int e = 0; e < NZ; ++e)
+#pragma unroll
+                        for (int j = 0; j < NB5; ++j) g[e][j] = T(0);
+                    tap_for<NY>([&](auto fc) {
+                        constexpr int f = decltype(fc)::value, e = B::tab.yey[f];
+                        T w[NB5 + 2 * RY];
+#pragma unroll
+                        for (int j = 0; j < NB5 + 2 * RY; ++j) w[j] = sF[(f * YE + y5 + j) * TX + x5];
+#pragma unroll
+                        for (int j = 0; j < NB5; ++j)
+                            g[B::tab.yez[f]][j] += tap_conv<RY, true, e>(w + j, k_->t[1][e]);
+                    });
+#pragma unroll
+                    for (int k = 0; k < NB5; ++k)
+#pragma unroll
+                        for (int j = 0; j <= 2 * RZ; ++j) {
+                            const int o = RZ - j, ao = o < 0 ? -o : o;
+                            T acc = j < 2 * RZ ? zout[k][j < 2 * RZ ? j + 1 : j] : T(0);
+#pragma unroll
+                            for (int e = 0; e < NZ; ++e) {
+                                if (RZ == 0) acc += g[e][k];
+                                else if (!(e > 0 && o == 0))
+                                    acc = (o < 0 && (e & 1)) ? acc - k_->t[2][e][ao] * g[e][k]
+                                                             : acc + k_->t[2][e][ao] * g[e][k];
+                            }
+                            zout[k][j] = acc;
+                        }
+                    if (s >= 4 * RZ + 2) {
+                        const long zo = (long)(zlo + s - (4 * RZ + 2)) * nxy;
+#pragma unroll
+                        for (int k = 0; k < NB5; ++k) {
+                            if (ok5[k]) {
+                                const Tio v = mk5[k] ? Tio(zout[k][0]) : Tio(0);
+                                (out + zo)[o5 + (uint32_t)(k * nx)] = v;
+                                if (dwith) dacc += (double)v * (double)(dwith + zo)[o5 + (uint32_t)(k * nx)];
+                            }
+                        }
+                    }
+                }
+            }
+            tap_barrier();
+            // ---------------------------------------------------------- half B
+            if constexpr (A && KMODE) {
+                // the classes of the next plane, asked for ahead of their use
+                if (s >= 2 * RZ + 1 && s + 1 < nE + 2 * RZ + 1) {
+                    pe = (pe + 1 == nz) ? 0 : pe + 1;
+                    const uint32_t* pw = tap_fresh(kp)->words + (long)pe * ny * gx;
+#pragma unroll
+                    for (int k = 0; k < NP3; ++k) word[k] = pw[it3[k]];
+                }
+            }
+            if constexpr (Bq) {
+                // the mask of the next result plane
+                if (s + 1 >= 4 * RZ + 2 && s + 1 < s1) {
+                    const uint8_t* pm = mask_out + (long)(zlo + s + 1 - (4 * RZ + 2)) * nxy;
+#pragma unroll
+                    for (int k = 0; k < NB5; ++k)
+                        if (ok5[k]) mk5[k] = pm[o5 + (uint32_t)(k * nx)];
+                }
+            }
+            if constexpr (G::P1) {
+                if (s >= 2 * RZ && s < nE + 2 * RZ && (!RO::SPLIT || !G::P2 || tid < RO::N2)) {
+                    const KP k_ = tap_fresh(kp);
+                    for (int it = tid; it < XL * (YE / NB2); it += G::P2 ? RO::N2 : NT) {
+                        const int x = it % XL, yb = it / XL * NB2;
+                        T w[NZ][NB2 + 2 * RY];
+#pragma unroll
+                        for (int e = 0; e < NZ; ++e)
+#pragma unroll
+                            for (int j = 0; j < NB2 + 2 * RY; ++j) w[e][j] = sZ[(e * YL + yb + j) * XL + x];
+                        tap_for<NY>([&](auto fc) {
+                            constexpr int f = decltype(fc)::value, e = B::tab.yey[f];
+#pragma unroll
+                            for (int j = 0; j < NB2; ++j)
+                                sY[(f * YE + yb + j) * XL + x] =
+                                    tap_conv<RY, false, e>(w[B::tab.yez[f]] + j, k_->t[1][e]);
+                        });
+                    }
+                }
+            }
+            if constexpr (G::P2) {
+                if (s >= 2 * RZ + 1 && s < nE + 2 * RZ + 1 && (!RO::SPLIT || tid >= RO::N2)) {
+                    const KP k_ = tap_fresh(kp);
+                    for (int it = RO::SPLIT ? tid - RO::N2 : tid; it < TX / XB4 * YE; it += RO::N4) {
+                        const int xb = it % (TX / XB4) * XB4, yy = it / (TX / XB4);
+                        T f_[NY][XB4];
+#pragma unroll
+                        for (int f = 0; f < NY; ++f)
+#pragma unroll
+                            for (int j = 0; j < XB4; ++j) f_[f][j] = T(0);
+                        tap_for<S>([&](auto qc) {
+                            constexpr int q = decltype(qc)::value, e = B::tab.xex[q];
+                            T w[XB4 + 2 * R];
+                            const TapPair<T>* src =
+                                reinterpret_cast<const TapPair<T>*>(sE + (q * YE + yy) * XE + xb);
+#pragma unroll
+                            for (int j = 0; j < XB4 / 2 + R; ++j) {
+                                const TapPair<T> v = src[j];
+                                w[2 * j] = v.x;
+                                w[2 * j + 1] = v.y;
+                            }
+#pragma unroll
+                            for (int j = 0; j < XB4; ++j)
+                                f_[B::tab.xyf[q]][j] += tap_conv<R, true, e>(w + j, k_->t[0][e]);
+                        });
+#pragma unroll
+                        for (int f = 0; f < NY; ++f)
+#pragma unroll
+                            for (int j = 0; j < XB4 / 2; ++j)
+                                reinterpret_cast<TapPair<T>*>(sF + (f * YE + yy) * TX + xb)[j] =
+                                    TapPair<T>{f_[f][2 * j], f_[f][2 * j + 1]};
+                    }
+                }
+            }
+            tap_barrier();
+        }
+        return dacc;
+    }
+};
+
+template <typename T, typename Tio, class B, int R, int MODE, int ROWS, int TX, int TY, int NT>
+__global__ __launch_bounds__(NT, tap_min_waves(sizeof(T), tap_lds_of<B, R, MODE, TX, TY>, NT, tap_cap(sizeof(T), B::S, R))) void k_tap(const TapArgs<T>)
+{
+    using G = TapGeom<B, R, MODE, TX, TY>;
+    using RO = TapRoles<B::DIM, NT>;
+    __shared__ __align__(16) T smem[G::LDS > 0 ? G::LDS : 1];
+    const TapArgPtr<T> kp = (TapArgPtr<T>)__builtin_amdgcn_kernarg_segment_ptr();
+
+    const int tid = threadIdx.x;
+    const int nx = kp->n[0], ny = kp->n[1], nxy = nx * ny, ntx = kp->ntx, nty = kp->nty;
+    const long rj = (long)blockIdx.y * kp->rb;
+    const Tio* const in = reinterpret_cast<const Tio*>((const char*)kp->in + rj);
+    Tio* const out = reinterpret_cast<Tio*>((char*)kp->out + rj);
+    double* const dpart = kp->dot_part;
+    const Tio* const dwith = dpart ? reinterpret_cast<const Tio*>((const char*)kp->dot_with + rj) : nullptr;
+    int b = (int)tap_xcd(blockIdx.x, gridDim.x);
+    const int tx = b % ntx;
+    b /= ntx;
+    const int ty = b % nty;
+    const int x0 = tx * TX, y0 = ty * TY;
+    const int za = (b / nty) * kp->cz, ze = min(za + kp->cz, kp->n[2]);
+    // planes of the chunk outside the domain's extent in this tile column are zero
+    const int2 zr = kp->zr[ty * ntx + tx];
+    const int zlo = min(max(za, zr.x), ze), zhi = max(zlo, min(ze, zr.y + 1));
+    if (za < zlo || zhi < ze) {
+        for (int i = tid; i < TX * TY; i += NT) {
+            const int x = x0 + i % TX, y = y0 + i / TX;
+            if (x < nx && y < ny) {
+                Tio* o = out + (long)y * nx + x;
+                for (int z = za; z < zlo; ++z) o[(long)z * nxy] = Tio(0);
+                for (int z = zhi; z < ze; ++z) o[(long)z * nxy] = Tio(0);
+            }
+        }
+    }
+    double dacc = 0.0;
+    if (zlo < zhi) {
+        // the roles hold different state: each gets its own copy of the march
+        // (both meet at the same number of barriers)
+        if constexpr (!RO::SPLIT) {
+            dacc = TapMarch<T, Tio, B, R, MODE, ROWS, TX, TY, NT, 3>::run(kp, smem, in, out, dwith, x0, y0, zlo, zhi);
+        } else {
+            if (__builtin_amdgcn_readfirstlane(tid) < RO::NA)
+                dacc = TapMarch<T, Tio, B, R, MODE, ROWS, TX, TY, NT, 1>::run(kp, smem, in, out, dwith, x0, y0, zlo, zhi);
+            else
+                dacc = TapMarch<T, Tio, B, R, MODE, ROWS, TX, TY, NT, 2>::run(kp, smem, in, out, dwith, x0, y0, zlo, zhi);
+        }
+    }
+    if constexpr (G::P2) {
+        if (dpart) {
+            __shared__ double sh[NT / 64];
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) dacc += __shfl_xor(dacc, o, 64);
+            if ((tid & 63) == 0) sh[tid >> 6] = dacc;
+            __syncthreads();
+            if (tid == 0) {
+                double r = 0.0;
+                for (int i = 0; i < NT / 64; ++i) r += sh[i];
+                dpart[(long)blockIdx.y * kp->dot_stride + blockIdx.x] = r;
+            }
+        }
+    }
+}
+
+// Tile of a variant: the columns of one workgroup and its threads.
+template <int DIM>
+struct TapTile {
+    static constexpr int TX = DIM == 1 ? 256 : 32, TY = DIM == 1 ? 1 : 16, NT = DIM == 1 ? 256 : 512;
+};
+
+// instantiated in tap_f32.hip and tap_f64.hip
+template <typename T, typename Tio, class B, int R, int MODE, int ROWS>
+void tap_go(const TapArgs<T>& a, dim3 grid, hipStream_t st)
+{
+    using TT = TapTile<B::DIM>;
+    hipLaunchKernelGGL((k_tap<T, Tio, B, R, MODE, ROWS, TT::TX, TT::TY, TT::NT>), grid, dim3(TT::NT), 0, st, a);
+}
+
+}  // namespace fcrkpm

@@ -1,0 +1,137 @@
+"""The direct tap kernels (short supports: both halves of an operator summed
+directly in one launch) against the FP64 oracle and the FFT passes.
+
+Boxes sit at the edges of the kernel's tiles (32 x 16 columns marched along z,
+256 nodes in 1D): one node more and less than a tile, boxes smaller than one,
+axes with odd factors, and domains that fill an axis (periodic), that leave
+whole tiles outside, or that touch neither end.  Tolerances: in FP64 the
+library's bars (1e-11 of the largest value against the oracle); in FP32 at most
+about a hundred roundings of 6e-8 follow one another in a product, each
+relative to terms no larger than ten times the result's scale: 6e-5 bounds
+them, and the library's FP32 bar of 2e-5 is kept."""
+import math
+
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda"
+
+
+def fc():
+    from paper_2403_19854_amd import fcrkpm
+    return fcrkpm
+
+
+def domain(dims, at, kind, seed=1):
+    """chi, Dirichlet mask, volumes [nz][ny][nx] on a box of nodes."""
+    m = int(math.floor(at))
+    shape = tuple(reversed(dims))
+    ix = np.meshgrid(*[np.arange(n) for n in reversed(dims)], indexing="ij")[::-1]
+    rng = np.random.default_rng(seed)
+    if kind == "box":
+        chi = np.ones(shape, bool)
+        for k, n in enumerate(dims):
+            chi &= ix[k] <= n - m - 1
+    elif kind == "periodic":
+        chi = np.ones(shape, bool)
+    elif kind == "inside":      # touches no end of the box
+        chi = np.ones(shape, bool)
+        for k, n in enumerate(dims):
+            chi &= (ix[k] >= 2) & (ix[k] < n - m - 1)
+    else:                       # ball
+        r2 = sum((ix[k] - dims[k] / 2.0) ** 2 / (0.4 * dims[k]) ** 2 for k in range(len(dims)))
+        chi = r2 <= 1.0
+    dirichlet = np.zeros(shape, bool)
+    for ax in range(len(dims)):
+        for sh in (1, -1):
+            dirichlet |= chi & ~np.roll(chi, sh, ax)
+    h = tuple(1.0 / n for n in dims)
+    vol = np.where(chi, rng.uniform(0.5, 1.5, shape) * np.prod(h), 0.0)
+    return h, chi.astype(np.uint8), dirichlet.astype(np.uint8), vol
+
+
+def make(dims, at, degree, kind):
+    f = fc()
+    h, chi, dirichlet, vol = domain(dims, at, kind)
+    g = f.Problem(dims, h, (at,) * len(dims), degree, chi, dirichlet, vol, device=DEV)
+    assert g.get_option(f.OPT_TAPS) == 1
+    o = oracle.Oracle(dims, h, (at,) * len(dims), degree, chi, vol)
+    return g, o, chi, (chi > dirichlet).astype(np.uint8)
+
+
+def check(got, ref, tol, what):
+    scale = np.abs(ref).max()
+    err = np.abs(got - ref).max() / scale
+    print(f"  {what}: {err:.2e}", flush=True)
+    assert np.isfinite(got).all() and err <= tol
+
+
+LINEAR_3D = [
+    ((32, 16, 20), 2.5, "box"), ((30, 15, 9), 2.0, "box"), ((35, 18, 10), 1.5, "inside"),
+    ((36, 30, 28), 2.5, "ball"), ((64, 49, 12), 3.0, "box"), ((16, 12, 40), 3.5, "box"),
+    ((7, 9, 8), 2.5, "periodic"), ((5, 4, 6), 1.5, "box"), ((32, 32, 32), 2.5, "periodic"),
+]
+
+
+@pytest.mark.parametrize("dims,at,kind", LINEAR_3D)
+def test_stiffness_linear_3d(dims, at, kind):
+    print(f"\n[taps K linear] {dims} support {at} {kind}", flush=True)
+    f = fc()
+    g, o, chi, free = make(dims, at, 1, kind)
+    x = np.random.default_rng(2).standard_normal(chi.shape)   # not masked: the library masks it
+    if kind == "periodic":
+        # the oracle's neighbourhoods do not wrap around: the FP64 FFT passes are
+        # the reference (they match the closed form of a periodic domain)
+        g.set_option(f.OPT_TAPS, 0)
+        apply = lambda v: g.apply("K_FULL", torch.from_numpy(v).to(DEV)).cpu().numpy()
+        mass = g.apply("M", torch.from_numpy(x).to(DEV)).cpu().numpy()
+    else:
+        apply = o.apply_k
+        mass = np.where(chi > 0, o.apply_m(np.where(chi > 0, x, 0.0)), 0.0)
+    ref = apply(np.where(chi > 0, x, 0.0))
+    refk = np.where(free > 0, apply(np.where(free > 0, x, 0.0)), 0.0)
+    g.set_option(f.OPT_TAPS, 1)
+    for dtype, tol in ((torch.float64, 1e-11), (torch.float32, 2e-5)):
+        xt = torch.from_numpy(x).to(DEV, dtype)
+        full = g.apply("K_FULL", xt).cpu().numpy().astype(np.float64)
+        k = g.apply("K", xt).cpu().numpy()
+        check(full, np.where(chi > 0, ref, 0.0), tol, f"K_FULL {dtype}")
+        check(k.astype(np.float64), refk, tol, f"K {dtype}")
+        assert np.all(k[free == 0] == 0.0)
+        # right-hand sides of one launch equal single ones bit for bit
+        three = g.apply("K", torch.stack([xt, 2 * xt, xt])).cpu().numpy()
+        np.testing.assert_array_equal(three[0], k)
+        np.testing.assert_array_equal(three[2], k)
+        g.set_option(f.OPT_TAPS, 0)
+        assert g.get_option(f.OPT_TAPS) == 0
+        fft = g.apply("K", xt).cpu().numpy().astype(np.float64)
+        g.set_option(f.OPT_TAPS, 1)
+        check(k.astype(np.float64), fft, 1e-12 if dtype == torch.float64 else tol, f"K vs FFT {dtype}")
+    check(g.apply("M", torch.from_numpy(x).to(DEV)).cpu().numpy(), mass, 1e-11, "M")
+
+
+def test_fft_options_pin_the_fft_passes():
+    """Options that ask for FFT passes switch the direct sums off; their default
+    gives the choice back.  A support beyond 3 nodes never takes them."""
+    f = fc()
+    h, chi, dirichlet, vol = domain((32, 32, 32), 2.5, "box")
+    g = f.Problem((32,) * 3, h, (2.5,) * 3, 1, chi, dirichlet, vol, device=DEV)
+    for opt, off, on in ((f.OPT_REGPATH, 0, 1), (f.OPT_LINECONST, 0, 1),
+                         (f.OPT_SEP_LINES32, 4, g.get_option(f.OPT_SEP_LINES32)), (f.OPT_TAPS, 0, 1)):
+        if off == on:
+            continue
+        g.set_option(opt, off)
+        assert g.get_option(f.OPT_TAPS) == 0
+        g.set_option(opt, on)
+        assert g.get_option(f.OPT_TAPS) == 1
+    with pytest.raises(f.FcrkpmError):
+        g.set_option(f.OPT_TAPS, 2)
+    h, chi, dirichlet, vol = domain((32, 32, 32), 4.5, "box")
+    g = f.Problem((32,) * 3, h, (4.5,) * 3, 1, chi, dirichlet, vol, device=DEV)
+    assert g.get_option(f.OPT_TAPS) == 0
