@@ -609,6 +609,19 @@ void tap_k(Ctx& c, const Tio* in, Tio* out, const uint8_t* mask, int nrhs, hipSt
     launch_tap<T, Tio>(c, 0, in, out, mask, mask, nullptr, nrhs, dot_part, dot_with, dot_stride, st);
 }
 
+// Whether a K-type product runs on the direct kernels.  They do at most half
+// the work of the FFT passes for radii 1 and 2; at R = 3 the linear basis on a
+// 128^3 box is faster on the FP32 register path (60.6 us against 70.8; 64^3:
+// 35.5 against 28.0, and FP64 356 against 82.6).
+template <typename T, typename Tio>
+bool tap_serves_k(const Ctx& c)
+{
+    if (!tap_active(c)) return false;
+    if (std::is_same_v<T, float> && std::is_same_v<Tio, float> && c.degree == 1 && c.tap_r == 3 && c.n[0] == 128)
+        return !use_reg_path(c, 1);
+    return true;
+}
+
 // slots per right-hand side of the p.q partials of a last pass or a direct
 // product with more workgroups than kRedBlocks
 long wide_slots(const Ctx& c) { return std::max(reg_dot_slots(c), tap_dot_slots(c)); }
@@ -719,7 +732,7 @@ void apply_one(Ctx& c, int op, const Tio* in, Tio* out, int nrhs, hipStream_t st
             const uint8_t* mk = (op == FCRKPM_OP_K) ? c.freem : c.chi;
             const int pwk = (op == OP_KN) ? SEP_PW_KN : SEP_PW_K;
             // (without its nonlinear term the gradient force is K d)
-            if (tap_active(c) && (op != OP_KN || c.pw_kappa == 0.0)) {
+            if (tap_serves_k<T, Tio>(c) && (op != OP_KN || c.pw_kappa == 0.0)) {
                 tap_k<T, Tio>(c, in, out, mk, nrhs, st);
                 break;
             }
@@ -885,7 +898,7 @@ template <typename T, typename TP>
 bool fused_cg(Ctx& c, int nrhs)
 {
     if constexpr (std::is_same_v<T, float> && std::is_same_v<TP, float>)
-        return !tap_active(c) && use_reg_path(c, nrhs);
+        return !tap_serves_k<T, T>(c) && use_reg_path(c, nrhs);
     else
         return false;
 }
@@ -901,7 +914,7 @@ void cg_iteration(Ctx& c, T* x, T* r, T* p, T* q, int nrhs, int parity, hipStrea
     double* pq_part = c.partial;
     double* rr_part = c.partial + (size_t)kRedBlocks * c.cap_rhs;
     int npq = red_blocks(c.nn);
-    if (tap_active(c)) {
+    if (tap_serves_k<TP, T>(c)) {
         // the direct product leaves the p.q partials of its workgroups (in the
         // wide slots, summed to one, when they outnumber kRedBlocks)
         const long nb = tap_blocks(c, nrhs, sizeof(TP));

@@ -3,5 +3,4 @@
 
 namespace fcrkpm {
 FC_TAP_F32(FC_TAP_BUILD)
-FC_TAP_MIX(FC_TAP_BUILD)
 }  // namespace fcrkpm

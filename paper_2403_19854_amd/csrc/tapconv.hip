@@ -43,8 +43,8 @@ void tap_free(TapSet* s)
     delete s;
 }
 
-int tile_x(const Ctx& c) { return c.dim == 1 ? TapTile<1>::TX : TapTile<3>::TX; }
-int tile_y(const Ctx& c) { return c.dim == 1 ? TapTile<1>::TY : TapTile<3>::TY; }
+int tile_x(const Ctx& c) { return tap_tile_x(c.dim, c.degree, c.tap_r); }
+int tile_y(const Ctx& c) { return tap_tile_y(c.dim); }
 int tap_gx(const Ctx& c)
 {
     const int tx = tile_x(c);
@@ -199,16 +199,8 @@ int tap_planes(const Ctx& c, int nrhs, int elem)
 
 }  // namespace
 
-// The direct kernels serve taps of radius 1 to 3 for the linear bases, and for
-// the higher ones the radii that their moment matrices need.
-static bool tap_radius_ok(int dim, int degree, int r)
-{
-    if (r < 1 || r > kTapR) return false;
-    if (dim < 3 || degree > 1) return false;
-    if (degree == 1) return true;
-    if (degree == 2) return r >= 2;
-    return dim < 3 && r == 3;
-}
+// Bases and radii with a kernel (tap_list.hpp).
+static bool tap_served(const Ctx& c) { return c.tap_r >= c.degree && c.tap_r >= 1 && c.tap_r <= kTapR; }
 
 bool tap_active(const Ctx& c) { return c.use_taps && !c.fft_pins && c.tap; }
 
@@ -252,7 +244,7 @@ void tap_setup(Ctx& c, const double (*taps)[kTapE][kTapR + 1], hipStream_t st)
 // words and records of the coefficient rows in use (c.ba_64, c.krows, c.cls)
 void tap_build(Ctx& c, hipStream_t st)
 {
-    if (!tap_radius_ok(c.dim, c.degree, c.tap_r)) return;
+    if (!tap_served(c)) return;
     TapSet* s = new TapSet();
     c.tap = s;
     const bool mf = c.degree == 1;

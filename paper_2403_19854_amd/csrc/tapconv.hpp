@@ -684,18 +684,20 @@ __global__ __launch_bounds__(NT, tap_min_waves(sizeof(T), tap_lds_of<B, R, MODE,
     }
 }
 
-// Tile of a variant: the columns of one workgroup and its threads.
-template <int DIM>
-struct TapTile {
-    static constexpr int TX = DIM == 1 ? 256 : 32, TY = DIM == 1 ? 1 : 16, NT = DIM == 1 ? 256 : 512;
-};
+// Tile of a variant: the columns of one workgroup and its threads.  32 x 16
+// columns over 8 waves: 64 x 16 and 32 x 32 over 16 waves overlap less but
+// measured slower (256^3 FP32: 189 and 188 us against 175), 32 x 8 over 4 waves
+// too (197).  The quadratic basis in 3D at R = 3 takes half the columns, so
+// that its FP64 fields fit the LDS.
+constexpr int tap_tile_x(int dim, int degree, int r) { return dim == 1 ? 256 : dim == 3 && degree == 2 && r == 3 ? 16 : 32; }
+constexpr int tap_tile_y(int dim) { return dim == 1 ? 1 : 16; }
 
 // instantiated in tap_f32.hip and tap_f64.hip
 template <typename T, typename Tio, class B, int R, int MODE, int ROWS>
 void tap_go(const TapArgs<T>& a, dim3 grid, hipStream_t st)
 {
-    using TT = TapTile<B::DIM>;
-    hipLaunchKernelGGL((k_tap<T, Tio, B, R, MODE, ROWS, TT::TX, TT::TY, TT::NT>), grid, dim3(TT::NT), 0, st, a);
+    constexpr int TX = tap_tile_x(B::DIM, B::DEG, R), TY = tap_tile_y(B::DIM), NT = B::DIM == 1 ? 256 : 512;
+    hipLaunchKernelGGL((k_tap<T, Tio, B, R, MODE, ROWS, TX, TY, NT>), grid, dim3(NT), 0, st, a);
 }
 
 }  // namespace fcrkpm

@@ -72,18 +72,26 @@ def check(got, ref, tol, what):
     assert np.isfinite(got).all() and err <= tol
 
 
-LINEAR_3D = [
+STIFFNESS = [
     ((32, 16, 20), 2.5, "box"), ((30, 15, 9), 2.0, "box"), ((35, 18, 10), 1.5, "inside"),
     ((36, 30, 28), 2.5, "ball"), ((64, 49, 12), 3.0, "box"), ((16, 12, 40), 3.5, "box"),
     ((7, 9, 8), 2.5, "periodic"), ((5, 4, 6), 1.5, "box"), ((32, 32, 32), 2.5, "periodic"),
 ]
+# 1D and 2D, and the quadratic and cubic bases (radius 2 and 3)
+OTHER_BASES = [
+    ((256,), 2.5, "box", 1), ((250,), 1.5, "inside", 1), ((512,), 3.5, "box", 1), ((9,), 2.0, "periodic", 1),
+    ((270,), 2.5, "box", 2), ((128,), 3.5, "box", 2), ((225,), 4.0, "box", 3),
+    ((35, 16), 2.5, "box", 1), ((30, 49), 1.5, "ball", 1), ((64, 15), 3.5, "box", 1),
+    ((36, 35), 3.0, "box", 2), ((70, 48), 3.5, "ball", 2), ((40, 36), 4.0, "box", 3),
+    ((12, 10, 9), 2.5, "box", 2), ((36, 30, 28), 3.0, "ball", 2), ((35, 16, 18), 3.5, "box", 2),
+]
 
 
-@pytest.mark.parametrize("dims,at,kind", LINEAR_3D)
-def test_stiffness_linear_3d(dims, at, kind):
-    print(f"\n[taps K linear] {dims} support {at} {kind}", flush=True)
+@pytest.mark.parametrize("dims,at,kind,degree", [c + (1,) for c in STIFFNESS] + OTHER_BASES)
+def test_stiffness_and_mass(dims, at, kind, degree):
+    print(f"\n[taps K] {dims} support {at} {kind} degree {degree}", flush=True)
     f = fc()
-    g, o, chi, free = make(dims, at, 1, kind)
+    g, o, chi, free = make(dims, at, degree, kind)
     x = np.random.default_rng(2).standard_normal(chi.shape)   # not masked: the library masks it
     if kind == "periodic":
         # the oracle's neighbourhoods do not wrap around: the FP64 FFT passes are
