@@ -1526,8 +1526,12 @@ void run_solvers_on(const std::vector<Solver*>& all, bool graphs, hipStream_t st
             }
             if (need) {
                 HIPCHK(hipEventSynchronize(ev[slot ^ 1]));
+                bool f64 = true;
+                for (Solver* s : act) f64 = f64 && s->ph == PH_F64;
                 for (Solver* s : act) s->service(slot ^ 1, st);
-                nposted = 0;
+                // FP64 CG goes on unchanged, so its last block is still to be
+                // polled: each right-hand side stops where it would alone
+                nposted = f64 ? 1 : 0;
             }
         }
     } catch (...) {
