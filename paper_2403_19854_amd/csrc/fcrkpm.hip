@@ -87,13 +87,13 @@ void* scratch_address()
 // sizes).
 enum Kind {
     KD_P1_X, KD_P1_Y, KD_P1_Z, KD_MID_K, KD_MID_UH, KD_MID_LOAD, KD_P2_X, KD_P2_Y, KD_P2_Z,
-    KD_SETUP_PASS, KD_TAP_K, KD_STAGES
+    KD_SETUP_PASS, KD_TAP_K, KD_TAP_UH, KD_TAP_LOAD, KD_STAGES
 };
 constexpr int KD_NKINDS = 2 * KD_STAGES;  // FP64 kinds, then FP32 kinds
 const char* const kStageNames[KD_STAGES] = {
     "sep_part1_x", "sep_part1_y", "sep_part1_z", "sep_mid_k", "sep_mid_uh", "sep_mid_load",
     "sep_part2_x", "sep_part2_y", "sep_part2_z", "sep_setup_pass",
-    "tap_k"};
+    "tap_k", "tap_uh", "tap_load"};
 std::string kind_name(int k)
 {
     return std::string(kStageNames[k % KD_STAGES]) + (k >= KD_STAGES ? "_f32" : "_f64");
@@ -606,7 +606,7 @@ void tap_k(Ctx& c, const Tio* in, Tio* out, const uint8_t* mask, int nrhs, hipSt
 {
     const double bytes = (double)c.nn * (2 * sizeof(Tio) + 2 + (dot_part ? sizeof(Tio) : 0));
     ProfScope ps(c, kind_of<T>(KD_TAP_K), bytes * nrhs, st);
-    launch_tap<T, Tio>(c, 0, in, out, mask, mask, nullptr, nrhs, dot_part, dot_with, dot_stride, st);
+    launch_tap<T, Tio>(c, SEP_PW_K, in, out, mask, mask, nullptr, nullptr, nrhs, dot_part, dot_with, dot_stride, st);
 }
 
 // Whether a K-type product runs on the direct kernels.  They do at most half
@@ -711,11 +711,60 @@ OpSet* shift_set(Ctx& c, double cm, double ck, hipStream_t st)
 // c.pw_kappa between the two halves (Alg B.1 with N(g) = (1 + kappa |g|^2) g)
 constexpr int OP_KN = 100;
 
+// The operators that the direct kernels serve: false leaves the call to the
+// FFT passes.  (Without its nonlinear term the gradient force is K d.)
+template <typename T, typename Tio>
+bool tap_apply(Ctx& c, int op, const Tio* in, Tio* out, int nrhs, hipStream_t st)
+{
+    if (op == FCRKPM_OP_K || op == FCRKPM_OP_K_FULL || (op == OP_KN && c.pw_kappa == 0.0)) {
+        if (!tap_serves_k<T, Tio>(c)) return false;
+        tap_k<T, Tio>(c, in, out, op == FCRKPM_OP_K ? c.freem : c.chi, nrhs, st);
+        return true;
+    }
+    if (!tap_active(c)) return false;
+    if constexpr (std::is_same_v<T, Tio>) {
+        const double nn = (double)c.nn * nrhs, rt = sizeof(T);
+        switch (op) {
+            case OP_KN:
+                if constexpr (std::is_same_v<T, double>) {
+                    // only nodes that are not interior read their rows
+                    ProfScope ps(c, kind_of<T>(KD_TAP_K),
+                                 nn * (2 * rt + 2) + (double)c.ncls2 * (c.dim * c.s + 1) * rt * nrhs, st);
+                    launch_tap<T, Tio>(c, SEP_PW_KN, in, out, c.chi, c.chi, c.ba_64, c.vol64, nrhs, nullptr,
+                                       nullptr, 0, st);
+                    return true;
+                }
+                return false;
+            case FCRKPM_OP_UH:
+            case FCRKPM_OP_VN: {
+                ProfScope ps(c, kind_of<T>(KD_TAP_UH), nn * (2 * rt + 1 + (c.s + (op == FCRKPM_OP_VN)) * rt), st);
+                launch_tap<T, Tio>(c, SEP_PW_UH, in, out, c.chi, nullptr, b0_of<T>(c),
+                                   op == FCRKPM_OP_VN ? vol_of<T>(c) : nullptr, nrhs, nullptr, nullptr, 0, st);
+                return true;
+            }
+            case FCRKPM_OP_FQ:
+                if (!c.area64) return false;  // refused below
+                [[fallthrough]];
+            case FCRKPM_OP_FR:
+            case FCRKPM_OP_NT: {
+                const T* w = op == FCRKPM_OP_FR ? vol_of<T>(c) : op == FCRKPM_OP_FQ ? area_of<T>(c) : nullptr;
+                ProfScope ps(c, kind_of<T>(KD_TAP_LOAD), nn * (2 * rt + 1 + (c.s + (w != nullptr)) * rt), st);
+                launch_tap<T, Tio>(c, SEP_PW_LOAD, in, out, nullptr, c.chi, b0_of<T>(c), w, nrhs, nullptr,
+                                   nullptr, 0, st);
+                return true;
+            }
+            default: return false;
+        }
+    }
+    return false;
+}
+
 // One operator on nrhs consecutive fields, arithmetic precision T, field type
 // Tio (Alg 2, 3, 4, C.1, B.1); every pass covers all fields in one launch.
 template <typename T, typename Tio = T>
 void apply_one(Ctx& c, int op, const Tio* in, Tio* out, int nrhs, hipStream_t st)
 {
+    if (tap_apply<T, Tio>(c, op, in, out, nrhs, st)) return;
     ensure_work(c, nrhs);
     const SepPlan& sp = c.basis_plan;
     const int k = sp.k, last = c.axes[k - 1];
@@ -731,11 +780,6 @@ void apply_one(Ctx& c, int op, const Tio* in, Tio* out, int nrhs, hipStream_t st
         case OP_KN: {
             const uint8_t* mk = (op == FCRKPM_OP_K) ? c.freem : c.chi;
             const int pwk = (op == OP_KN) ? SEP_PW_KN : SEP_PW_K;
-            // (without its nonlinear term the gradient force is K d)
-            if (tap_serves_k<T, Tio>(c) && (op != OP_KN || c.pw_kappa == 0.0)) {
-                tap_k<T, Tio>(c, in, out, mk, nrhs, st);
-                break;
-            }
             if constexpr (std::is_same_v<T, float> && std::is_same_v<Tio, float>) {
                 if (op != OP_KN && use_reg_path(c, nrhs)) {
                     reg_k(c, in, out, mk, nrhs, st);
@@ -915,9 +959,9 @@ void cg_iteration(Ctx& c, T* x, T* r, T* p, T* q, int nrhs, int parity, hipStrea
     double* rr_part = c.partial + (size_t)kRedBlocks * c.cap_rhs;
     int npq = red_blocks(c.nn);
     if (tap_serves_k<TP, T>(c)) {
-        // the direct product leaves the p.q partials of its workgroups (in the
-        // wide slots, summed to one, when they outnumber kRedBlocks)
-        const long nb = tap_blocks(c, nrhs, sizeof(TP));
+        // the direct product leaves the p.q partials (in the wide slots, summed
+        // to one, when they outnumber kRedBlocks)
+        const long nb = tap_dots(c, sizeof(TP));
         const bool wide = nb > kRedBlocks;
         tap_k<TP, T>(c, p, q, c.freem, nrhs, st, wide ? c.partial_wide : pq_part, p,
                      wide ? wide_slots(c) : kRedBlocks);
@@ -2168,6 +2212,19 @@ void prepare_solve(Ctx& c, int nrhs, const double* r, const double* g, const dou
     else HIPCHK(hipMemsetAsync(x, 0, sizeof(double) * nn * nrhs, st));
 }
 
+// u^h = N d at the end of a solve.  A caller may take u^h in place of d: the
+// direct kernel reads neighbours while it writes, so it then reads a copy.
+void apply_uh(Ctx& c, const double* d, double* uh, int nrhs, hipStream_t st)
+{
+    const size_t n = (size_t)c.nn * nrhs;
+    if (d < uh + n && uh < d + n) {
+        double* t = vec64(c, V_T);
+        HIPCHK(hipMemcpyAsync(t, d, sizeof(double) * n, hipMemcpyDeviceToDevice, st));
+        d = t;
+    }
+    apply_one<double>(c, FCRKPM_OP_UH, d, uh, nrhs, st);
+}
+
 // d = chi_Omega x + chi_Gamma_g g, and u^h = N d when asked (Alg 3)
 void finish_solve(Ctx& c, int nrhs, const double* g, double* d_out, double* uh_out,
                   hipStream_t st)
@@ -2181,7 +2238,7 @@ void finish_solve(Ctx& c, int nrhs, const double* g, double* d_out, double* uh_o
     } else {
         HIPCHK(hipMemcpyAsync(d_out, x, sizeof(double) * nn * nrhs, hipMemcpyDeviceToDevice, st));
     }
-    if (uh_out) apply_one<double>(c, FCRKPM_OP_UH, d_out, uh_out, nrhs, st);
+    if (uh_out) apply_uh(c, d_out, uh_out, nrhs, st);
 }
 
 void check_solve_args(int mode, int nrhs, double tol, int maxit)
@@ -2602,6 +2659,11 @@ namespace {
 // with the coefficient rows b^a in place of b^0 (Eq 15-16, Alg 3 with b^a)
 void apply_grad(Ctx& c, const double* x, double* out, hipStream_t st)
 {
+    if (tap_active(c)) {
+        launch_tap<double, double>(c, kTapGrad, x, out, c.chi, nullptr, c.ba_64, nullptr, 1, nullptr, nullptr, 0,
+                                   st);
+        return;
+    }
     if (use_reg_path64(c) && reg_kn_ok(c, st)) {
         launch_reg_kn(c, x, out, 0.0, RK_GRAD, st);
         return;
@@ -2790,7 +2852,7 @@ extern "C" fcrkpm_status fcrkpm_solve_nonlinear_cg(fcrkpm_ctx* ctx, int32_t kind
         }
         conv = conv || sqrt(rn) <= tol * fnorm;
         HIPCHK(hipMemcpyAsync(d_inout, d, sizeof(double) * nn, hipMemcpyDeviceToDevice, st));
-        if (uh_out) apply_one<double>(c, FCRKPM_OP_UH, d, uh_out, 1, st);
+        if (uh_out) apply_uh(c, d, uh_out, 1, st);
         HIPCHK(hipStreamSynchronize(st));
         HIPCHK(hipGetLastError());
         if (info) {
@@ -2905,7 +2967,7 @@ extern "C" fcrkpm_status fcrkpm_solve_nonlinear(fcrkpm_ctx* ctx, int32_t mode, d
         }
         acc.rel_res = rel;
         acc.true_rel_res = rel;
-        if (uh_out) apply_one<double>(c, FCRKPM_OP_UH, d_inout, uh_out, 1, st);
+        if (uh_out) apply_uh(c, d_inout, uh_out, 1, st);
         HIPCHK(hipStreamSynchronize(st));
         free_set(c.jac_set);
         HIPCHK(hipGetLastError());

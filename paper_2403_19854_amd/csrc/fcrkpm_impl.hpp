@@ -305,19 +305,20 @@ void launch_reg_k(const Ctx& c, const float* in, float* out, const uint8_t* mask
 // kernels of short support.  tap_setup (once) keeps the taps t[axis][e][o] and
 // the domain's extent per tile; tap_build makes the words and records of the
 // coefficient rows in use; tap_active tells whether the current product can
-// run on them; tap_blocks is the number of workgroups (and so of dot partials)
-// per right-hand side, at most tap_dot_slots.
+// run on them; tap_dots is the number of dot partials per right-hand side (the
+// same for a batch as for one), at most tap_dot_slots.
+constexpr int kTapGrad = 4;  // launch_tap's mode of the implicit gradient; the others are SEP_PW_*
 void tap_setup(Ctx& c, const double (*taps)[5][4], hipStream_t st);
 void tap_build(Ctx& c, hipStream_t st);
 bool tap_active(const Ctx& c);
-long tap_blocks(const Ctx& c, int nrhs, int elem_bytes);
+long tap_dots(const Ctx& c, int elem_bytes);
 long tap_dot_slots(const Ctx& c);
 void tap_release(Ctx& c);
 void tap_release_set(void*& s);
 template <typename T, typename Tio>
 void launch_tap(const Ctx& c, int mode, const Tio* in, Tio* out, const uint8_t* mask_in,
-                const uint8_t* mask_out, const T* vol, int nrhs, double* dot_part, const void* dot_with,
-                long dot_stride, hipStream_t st);
+                const uint8_t* mask_out, const T* rows, const T* vol, int nrhs, double* dot_part,
+                const void* dot_with, long dot_stride, hipStream_t st);
 
 // throws the library's FCRKPM_ERR_UNSUPPORTED status with this message
 [[noreturn]] void raise_unsupported(const char* msg);

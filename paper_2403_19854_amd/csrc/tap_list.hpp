@@ -7,27 +7,33 @@
 #pragma once
 #include "tapconv.hpp"
 
-#define FC_TAP_LIN(X, T, U, DIM) \
-    X(T, U, DIM, 1, 1, TAP_K, DIM) X(T, U, DIM, 1, 2, TAP_K, DIM) X(T, U, DIM, 1, 3, TAP_K, DIM)
-#define FC_TAP_R2(X, T, U, DIM, DEG, ROWS) X(T, U, DIM, DEG, 2, TAP_K, ROWS)
-#define FC_TAP_R3(X, T, U, DIM, DEG, ROWS) X(T, U, DIM, DEG, 3, TAP_K, ROWS)
-// 1D and 2D
-#define FC_TAP_LOW(X, T, U)                                                                                     \
-    FC_TAP_LIN(X, T, U, 1) FC_TAP_LIN(X, T, U, 2)                                                               \
-    FC_TAP_R2(X, T, U, 1, 2, 1) FC_TAP_R3(X, T, U, 1, 2, 1) FC_TAP_R2(X, T, U, 1, 2, 2)                         \
-    FC_TAP_R3(X, T, U, 1, 2, 2) FC_TAP_R2(X, T, U, 2, 2, 1) FC_TAP_R3(X, T, U, 2, 2, 1)                         \
-    FC_TAP_R2(X, T, U, 2, 2, 2) FC_TAP_R3(X, T, U, 2, 2, 2) FC_TAP_R2(X, T, U, 2, 2, 3)                         \
-    FC_TAP_R3(X, T, U, 2, 2, 3) FC_TAP_R3(X, T, U, 1, 3, 1) FC_TAP_R3(X, T, U, 1, 3, 2)                         \
-    FC_TAP_R3(X, T, U, 2, 3, 1) FC_TAP_R3(X, T, U, 2, 3, 2) FC_TAP_R3(X, T, U, 2, 3, 3)
-// 3D
-#define FC_TAP_3D(X, T, U)                                                                                      \
-    FC_TAP_LIN(X, T, U, 3)                                                                                      \
-    FC_TAP_R2(X, T, U, 3, 2, 1) FC_TAP_R2(X, T, U, 3, 2, 3) FC_TAP_R2(X, T, U, 3, 2, 4)                         \
-    FC_TAP_R3(X, T, U, 3, 2, 1) FC_TAP_R3(X, T, U, 3, 2, 3) FC_TAP_R3(X, T, U, 3, 2, 4)
+// X(T, U, dimension, degree, radius, mode, rows) for every basis and radius
+#define FC_TAP_LIN(X, T, U, DIM, MODE, ROWS) \
+    X(T, U, DIM, 1, 1, MODE, ROWS) X(T, U, DIM, 1, 2, MODE, ROWS) X(T, U, DIM, 1, 3, MODE, ROWS)
+#define FC_TAP_QUAD(X, T, U, DIM, MODE, ROWS) X(T, U, DIM, 2, 2, MODE, ROWS) X(T, U, DIM, 2, 3, MODE, ROWS)
+#define FC_TAP_CUB(X, T, U, DIM, MODE, ROWS) X(T, U, DIM, 3, 3, MODE, ROWS)
+#define FC_TAP_ALL(X, T, U, MODE, R1, R2, R3)                                                                  \
+    FC_TAP_LIN(X, T, U, 1, MODE, R1) FC_TAP_LIN(X, T, U, 2, MODE, R2) FC_TAP_LIN(X, T, U, 3, MODE, R3)          \
+    FC_TAP_QUAD(X, T, U, 1, MODE, R1) FC_TAP_QUAD(X, T, U, 2, MODE, R2) FC_TAP_QUAD(X, T, U, 3, MODE, R3)       \
+    FC_TAP_CUB(X, T, U, 1, MODE, R1) FC_TAP_CUB(X, T, U, 2, MODE, R2)
+// K's rows, then the mass's and the shifted operator's of the higher bases
+#define FC_TAP_KS(X, T, U)                                                                                     \
+    FC_TAP_ALL(X, T, U, TAP_K, 1, 2, 3)                                                                        \
+    FC_TAP_QUAD(X, T, U, 2, TAP_K, 1) FC_TAP_QUAD(X, T, U, 3, TAP_K, 1) FC_TAP_CUB(X, T, U, 2, TAP_K, 1)       \
+    FC_TAP_QUAD(X, T, U, 1, TAP_K, 2) FC_TAP_QUAD(X, T, U, 2, TAP_K, 3) FC_TAP_QUAD(X, T, U, 3, TAP_K, 4)      \
+    FC_TAP_CUB(X, T, U, 1, TAP_K, 2) FC_TAP_CUB(X, T, U, 2, TAP_K, 3)
+#define FC_TAP_NODE(X, T, U) FC_TAP_ALL(X, T, U, TAP_UH, 1, 1, 1) FC_TAP_ALL(X, T, U, TAP_LOAD, 1, 1, 1)
+// the gradient force and the implicit gradient run in FP64 (in 1D the gradient
+// has the one row of u^h)
+#define FC_TAP_GRADS(X, T, U)                                                                                  \
+    FC_TAP_ALL(X, T, U, TAP_KN, 1, 2, 3)                                                                       \
+    FC_TAP_LIN(X, T, U, 2, TAP_UH, 2) FC_TAP_QUAD(X, T, U, 2, TAP_UH, 2) FC_TAP_CUB(X, T, U, 2, TAP_UH, 2)     \
+    FC_TAP_LIN(X, T, U, 3, TAP_UH, 3) FC_TAP_QUAD(X, T, U, 3, TAP_UH, 3)
 
-#define FC_TAP_F32(X) FC_TAP_LOW(X, float, float) FC_TAP_3D(X, float, float)
-#define FC_TAP_F64(X) FC_TAP_LOW(X, double, double) FC_TAP_3D(X, double, double)
-#define FC_TAP_MIX(X) FC_TAP_LOW(X, float, double) FC_TAP_3D(X, float, double)
+#define FC_TAP_F32(X) FC_TAP_KS(X, float, float) FC_TAP_NODE(X, float, float)
+#define FC_TAP_F64(X) FC_TAP_KS(X, double, double)
+#define FC_TAP_F64N(X) FC_TAP_NODE(X, double, double) FC_TAP_GRADS(X, double, double)
+#define FC_TAP_MIX(X) FC_TAP_KS(X, float, double)
 
 #define FC_TAP_EXTERN(T, U, DIM, DEG, R, MODE, ROWS) \
     extern template void tap_go<T, U, TapBasis<DIM, DEG>, R, MODE, ROWS>(const TapArgs<T>&, dim3, hipStream_t);
@@ -37,5 +43,6 @@
 namespace fcrkpm {
 FC_TAP_F32(FC_TAP_EXTERN)
 FC_TAP_F64(FC_TAP_EXTERN)
+FC_TAP_F64N(FC_TAP_EXTERN)
 FC_TAP_MIX(FC_TAP_EXTERN)
 }  // namespace fcrkpm

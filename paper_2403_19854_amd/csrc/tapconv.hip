@@ -166,22 +166,23 @@ int tap_lds(const Ctx& c)
 // step with r workgroups on a CU takes about 0.9 + 0.6 r (us at R = 2 in FP32;
 // measured 1.6, 2.0 and 2.7 for r = 1, 2, 3), and a last round that fills a
 // few CUs takes as long as a full one.
-int tap_planes_for(const Ctx& c, int nrhs, int elem)
+// unit: the chunk has to be a multiple of so many planes.
+int tap_planes(const Ctx& c, int nrhs, int elem, int unit)
 {
+    const int nz = c.n[2];
     if (c.dim < 3) return 1;
     const long tiles = (long)c.tap_nt[0] * c.tap_nt[1] * nrhs;
-    const int occ = tap_residents(elem, tap_lds(c), tap_cap(elem, c.s, c.tap_r)), nz = c.n[2];
+    const int occ = tap_residents(elem, tap_lds(c), tap_cap(elem, c.s, c.tap_r));
     const double slots = (double)c.tap_cus * occ;
-    int best = nz;
+    int best = unit;
     double cost = 1e300;
-    for (int k = 1; k <= nz; ++k) {
-        const int cz = (nz + k - 1) / k;
-        if ((nz + cz - 1) / cz != k) continue;
-        const double wg = (double)tiles * k, full = floor(wg / slots), rem = wg - full * slots;
-        const double t = (cz + 4 * c.tap_r + 2) *
+    for (int k = (nz + unit - 1) / unit; k >= 1; --k) {
+        const int cz = ((nz + k - 1) / k + unit - 1) / unit * unit;
+        const double wg = (double)tiles * ((nz + cz - 1) / cz), full = floor(wg / slots), rem = wg - full * slots;
+        const double t = (std::min(cz, nz) + 4 * c.tap_r + 2) *
                          (full * (0.9 + 0.6 * occ) +
-                          (rem > 0.0 ? 0.9 + 0.6 * std::max(1.0, rem / c.tap_cus) : 0.0));
-        if (t < cost) {
+                          (rem > 0.0 ? 0.9 + 0.6 * ceil(rem / c.tap_cus) : 0.0));
+        if (t <= cost) {
             cost = t;
             best = cz;
         }
@@ -189,13 +190,9 @@ int tap_planes_for(const Ctx& c, int nrhs, int elem)
     return best;
 }
 
-// more right-hand sides never cut finer than one (the dot partials of one fit
-// the slots of any)
-int tap_planes(const Ctx& c, int nrhs, int elem)
-{
-    const int cz = tap_planes_for(c, nrhs, elem);
-    return nrhs > 1 ? std::max(cz, tap_planes_for(c, 1, elem)) : cz;
-}
+// planes per dot partial: the chunk of one right-hand side, so that the dots of
+// a batch add up the same partials as single ones
+int tap_unit(const Ctx& c, int elem) { return tap_planes(c, 1, elem, 1); }
 
 }  // namespace
 
@@ -204,13 +201,13 @@ static bool tap_served(const Ctx& c) { return c.tap_r >= c.degree && c.tap_r >= 
 
 bool tap_active(const Ctx& c) { return c.use_taps && !c.fft_pins && c.tap; }
 
-long tap_blocks(const Ctx& c, int nrhs, int elem)
+long tap_dots(const Ctx& c, int elem)
 {
-    const int cz = tap_planes(c, nrhs, elem);
-    return (long)c.tap_nt[0] * c.tap_nt[1] * ((c.n[2] + cz - 1) / cz);
+    const int cu = tap_unit(c, elem);
+    return (long)c.tap_nt[0] * c.tap_nt[1] * ((c.n[2] + cu - 1) / cu);
 }
 
-long tap_dot_slots(const Ctx& c) { return c.tap ? std::max(tap_blocks(c, 1, 4), tap_blocks(c, 1, 8)) : 0; }
+long tap_dot_slots(const Ctx& c) { return c.tap ? std::max(tap_dots(c, 4), tap_dots(c, 8)) : 0; }
 
 void tap_release_set(void*& s)
 {
@@ -307,7 +304,7 @@ void tap_build(Ctx& c, hipStream_t st)
 
 template <typename T, typename Tio>
 void launch_tap(const Ctx& c, int mode, const Tio* in, Tio* out, const uint8_t* mask_in,
-                const uint8_t* mask_out, const T* vol, int nrhs, double* dot_part, const void* dot_with,
+                const uint8_t* mask_out, const T* rows_in, const T* vol, int nrhs, double* dot_part, const void* dot_with,
                 long dot_stride, hipStream_t st)
 {
     const TapSet& s = *(const TapSet*)c.tap;
@@ -323,36 +320,40 @@ void launch_tap(const Ctx& c, int mode, const Tio* in, Tio* out, const uint8_t* 
     }
     a.ntx = c.tap_nt[0];
     a.nty = c.tap_nt[1];
-    a.cz = tap_planes(c, nrhs, sizeof(T));
+    a.cu = tap_unit(c, sizeof(T));
+    a.cz = nrhs > 1 ? tap_planes(c, nrhs, sizeof(T), a.cu) : a.cu;
     a.zr = c.tap_zr;
     a.words = s.words;
     a.gx = tap_gx(c);
     if constexpr (sizeof(T) == 8) {
         a.rec = s.rec64;
         memcpy(a.mint, s.m64, sizeof(a.mint));
-        a.b0 = c.b0_64;
+        if (mode == TAP_KN) memcpy(a.mint, c.cint64, sizeof(double) * (c.dim * c.s + 1));
     } else {
         a.rec = s.rec32;
         memcpy(a.mint, s.m32, sizeof(a.mint));
-        a.b0 = c.b0_32;
     }
+    a.rows = rows_in;
     a.vol = vol;
     a.kappa = (T)c.pw_kappa;
     a.dot_part = dot_part;
     a.dot_with = dot_with;
     a.dot_stride = dot_stride;
     a.nn = c.nn;
-    a.rb = c.nn * (long)sizeof(Tio);
-    const dim3 grid((unsigned)tap_blocks(c, nrhs, sizeof(T)), (unsigned)nrhs);
-    const int rows = (mode == TAP_K && c.degree > 1) ? c.krows : c.dim;
+    a.rb = c.nn * (long)sizeof(Tio) * (mode == TAP_GRAD ? c.dim : 1);
+    const dim3 grid((unsigned)((long)a.ntx * a.nty * ((c.n[2] + a.cz - 1) / a.cz)), (unsigned)nrhs);
+    // the linear bases keep M, whatever the rows it was made of
+    const int rows = mode == TAP_K ? (c.degree > 1 ? c.krows : c.dim) : mode == TAP_KN || mode == TAP_GRAD ? c.dim : 1;
+    const int kmode = mode == TAP_GRAD ? TAP_UH : mode;
     bool done = false;
 #define FC_TAP_CASE(T_, TIO_, DIM, DEG, R, MODE, ROWS)                                              \
-    if (!done && c.dim == DIM && c.degree == DEG && c.tap_r == R && mode == MODE && rows == ROWS) { \
+    if (!done && c.dim == DIM && c.degree == DEG && c.tap_r == R && kmode == MODE && rows == ROWS) { \
         tap_go<T_, TIO_, TapBasis<DIM, DEG>, R, MODE, ROWS>(a, grid, st);                       \
         done = true;                                                                                \
     }
     if constexpr (sizeof(T) == 8) {
         FC_TAP_F64(FC_TAP_CASE)
+        FC_TAP_F64N(FC_TAP_CASE)
     } else if constexpr (sizeof(Tio) == 4) {
         FC_TAP_F32(FC_TAP_CASE)
     } else {
@@ -363,12 +364,12 @@ void launch_tap(const Ctx& c, int mode, const Tio* in, Tio* out, const uint8_t* 
 }
 
 template void launch_tap<float, float>(const Ctx&, int, const float*, float*, const uint8_t*, const uint8_t*,
-                                       const float*, int, double*, const void*, long, hipStream_t);
+                                       const float*, const float*, int, double*, const void*, long, hipStream_t);
 template void launch_tap<double, double>(const Ctx&, int, const double*, double*, const uint8_t*,
-                                         const uint8_t*, const double*, int, double*, const void*, long,
+                                         const uint8_t*, const double*, const double*, int, double*, const void*, long,
                                          hipStream_t);
 template void launch_tap<float, double>(const Ctx&, int, const double*, double*, const uint8_t*,
-                                        const uint8_t*, const float*, int, double*, const void*, long,
+                                        const uint8_t*, const float*, const float*, int, double*, const void*, long,
                                         hipStream_t);
 
 }  // namespace fcrkpm

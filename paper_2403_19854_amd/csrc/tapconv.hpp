@@ -38,7 +38,9 @@ constexpr int kTapR = 3;          // largest tap radius
 constexpr int kTapE = 5;          // exponents 0..4 (moments of the quadratic basis)
 constexpr int kTapMint = 41;      // interior constants: rows (dim + 1) * s of the quadratic basis, and V
 
-enum { TAP_K = 0, TAP_UH = 1, TAP_LOAD = 2, TAP_KN = 3 };
+// K products; u^h; the loads f^r, f^q and N^T y; the gradient force.  TAP_GRAD
+// is u^h with the rows b^a (one field, its dim components nn apart).
+enum { TAP_K = SEP_PW_K, TAP_UH = SEP_PW_UH, TAP_LOAD = SEP_PW_LOAD, TAP_KN = SEP_PW_KN, TAP_GRAD = kTapGrad };
 
 // Monomials of degree <= DEG in DIM variables (the library's basis order), as
 // the tree the passes walk: fields after z (exponent ez), after y (ey, ez),
@@ -94,16 +96,17 @@ struct TapArgs {
     T t[3][kTapE][kTapR + 1];  // t[axis][e][o], o = 0..R
     int n[3];
     int ntx, nty;              // tiles along x and y
-    int cz;                    // planes per chunk
+    int cz;                    // planes per chunk (one workgroup), a multiple of cu
+    int cu;                    // planes per dot partial
     const int2* zr;            // per tile column: first and last plane with a domain node
     const uint32_t* words;     // [nz][ny][gx]: classes and first record of two nodes
     int gx;                    // words per row (the row starts R nodes before x = 0)
     const T* rec;              // records of the class-2 nodes
     T mint[kTapMint];          // record of the interior nodes
-    const T* b0;               // [s][nn] (UH, LOAD)
-    const T* vol;              // [nn] or NULL (UH, LOAD)
+    const T* rows;             // UH, LOAD: b^0 [s][nn] (UH also b^a, [dim][s][nn]); KN: b^a
+    const T* vol;              // UH, LOAD: weight [nn] or NULL; KN: V [nn]
     T kappa;                   // KN
-    double* dot_part;          // per-workgroup partials of out . dot_with, or NULL
+    double* dot_part;          // partials of out . dot_with per tile and cu planes, or NULL
     const void* dot_with;
     long dot_stride;           // partial slots between right-hand sides
     long nn;
@@ -200,19 +203,23 @@ constexpr int tap_residents(int elem, int lds, int cap)
     const int n = 160 * 1024 / (elem * lds + 64);
     return n < 1 ? 1 : n > cap ? cap : n;
 }
-constexpr int tap_cap(int elem, int s, int r) { return elem == 4 && s <= 4 && r <= 2 ? 3 : 2; }
+constexpr int tap_cap(int elem, int s, int r)
+{
+    return elem == 4 && s <= 4 && r <= 2 ? 3 : elem == 8 && s == 10 && r == 3 ? 1 : 2;
+}
 constexpr int tap_min_waves(int elem, int lds, int nt, int cap) { return tap_residents(elem, lds, cap) * (nt / 64) / 4; }
 
-// The arguments live in the kernel-argument segment.  Every phase reads the
-// taps it needs from there again (scalar loads that hit the constant cache):
-// held in scalar registers all at once they would not fit.
+// The arguments live in the kernel-argument segment.  The taps and the interior
+// record of a small basis stay in scalar registers; those of a large one would
+// not fit, so every phase reads what it needs again (scalar loads that hit the
+// constant cache; 1.5% slower where both work).
 template <typename T>
 using TapArgPtr = const __attribute__((address_space(4))) TapArgs<T>*;
 
-template <typename P>
+template <bool HOLD, typename P>
 __device__ __forceinline__ P tap_fresh(P p)
 {
-    asm volatile("" : "+s"(p));
+    if constexpr (!HOLD) asm volatile("" : "+s"(p));
     return p;
 }
 
@@ -243,7 +250,7 @@ struct TapMarch {
     static constexpr int NB5 = TY % 4 == 0 ? 4 : 1;                         // rows per item, y reflection
     static constexpr int N3 = XE / 2 * YE, NP3 = (N3 + RO::NA - 1) / RO::NA;
     static constexpr int N5 = TX * (TY / NB5);
-    static_assert((!G::P2 || N5 <= RO::NB) && XE % 2 == 0 && TX % XB4 == 0);
+    static_assert((!G::P2 || (N5 <= RO::NB && N5 % 64 == 0)) && XE % 2 == 0 && TX % XB4 == 0);
     static constexpr bool MF = tap_mform<B, MODE>();
     static constexpr int RP = tap_rec_pitch(MF, S, ROWS, sizeof(T));
     static constexpr bool A = (ROLE & 1) != 0, Bq = (ROLE & 2) != 0 && G::P2;
@@ -321,8 +328,9 @@ struct TapMarch {
         return c == 2 ? (w >> 4) + ((i && (w & 3) == 2) ? 1u : 0u) : c;
     }
 
-    static __device__ __forceinline__ double run(KP kp, T* smem, const Tio* in, Tio* out, const Tio* dwith, int x0,
-                                                 int y0, int zlo, int zhi)
+    static __device__ __forceinline__ void run(KP kp, T* smem, double* dsum, const Tio* in, Tio* out,
+                                               const Tio* dwith, double* dpart, int tile, int ntiles, int x0, int y0,
+                                               int zlo, int zhi)
     {
         T* const sZ = smem;
         T* const sY = sZ + G::NSZ;
@@ -333,6 +341,9 @@ struct TapMarch {
         const uint8_t* const mask_in = kp->mask_in;
         const uint8_t* const mask_out = kp->mask_out;
         double dacc = 0.0;
+        bool flush = false;                        // the wave sums of a partial wait in dsum
+        int left = kp->cu - zlo % kp->cu;          // planes up to the partial's end
+        if (dpart) dpart += (long)(zlo / kp->cu) * ntiles + tile;
 
         // input columns of this thread
         uint32_t col[NC];
@@ -343,17 +354,16 @@ struct TapMarch {
                 col[k] = (uint32_t)(tap_wrap(y0 - HY - RY + c / XL, ny) * nx + tap_wrap(x0 - HX - R + c % XL, nx));
             }
         }
-        // E-level items: two nodes along x.  K modes: word offset in a plane;
-        // UH, LOAD: offsets of the two nodes
-        uint32_t it3[NP3], jt3[NP3];
+        // E-level items: two nodes along x; word offset in a plane (K, KN) and
+        // offsets of the two nodes (the modes that read node arrays)
+        uint32_t wt3[NP3], it3[NP3], jt3[NP3];
         if constexpr (A) {
 #pragma unroll
             for (int k = 0; k < NP3; ++k) {
                 const int it = min(tid + k * RO::NA, N3 - 1);
                 const int gi = it % (XE / 2), gy = tap_wrap(y0 - HY + it / (XE / 2), ny);
-                if constexpr (KMODE) {
-                    it3[k] = (uint32_t)(gy * gx + x0 / 2 + gi);
-                } else {
+                if constexpr (KMODE) wt3[k] = (uint32_t)(gy * gx + x0 / 2 + gi);
+                if constexpr (MODE != TAP_K) {
                     it3[k] = (uint32_t)(gy * nx + tap_wrap(x0 - HX + 2 * gi, nx));
                     jt3[k] = (uint32_t)(gy * nx + tap_wrap(x0 - HX + 2 * gi + 1, nx));
                 }
@@ -400,14 +410,14 @@ struct TapMarch {
         if constexpr (A && KMODE) {
             const uint32_t* pw = kp->words + (long)pe * ny * gx;
 #pragma unroll
-            for (int k = 0; k < NP3; ++k) word[k] = pw[it3[k]];
+            for (int k = 0; k < NP3; ++k) word[k] = pw[wt3[k]];
         }
         const int s0 = G::P1 ? 0 : 2 * RZ + 1, s1 = nE + 2 * RZ + (G::P2 ? 2 : 1);
         for (int s = s0; s < s1; ++s) {
             // ---------------------------------------------------------- half A
             if constexpr (G::P1) {
                 if (s < nE + 2 * RZ) {
-                    const KP k_ = tap_fresh(kp);
+                    const KP k_ = tap_fresh<(S <= 4)>(kp);
                     T cur[NC];
 #pragma unroll
                     for (int k = 0; k < NC; ++k) cur[k] = nmk[k] ? T(nxt[k]) : T(0);
@@ -440,7 +450,7 @@ struct TapMarch {
             }
             if constexpr (A) {
                 if (s >= 2 * RZ + 1 && s < nE + 2 * RZ + 1) {
-                    const KP k_ = tap_fresh(kp);
+                    const KP k_ = tap_fresh<(S <= 4)>(kp);
 #pragma unroll
                     for (int k = 0; k < NP3; ++k) {
                         const int it = tid + k * RO::NA;
@@ -449,25 +459,29 @@ struct TapMarch {
                             T D[2][S];
                             if constexpr (G::P1) x_conv(sY, yy, gi, k_, D);
                             if constexpr (MODE == TAP_UH) {
-                                // u = sum_p b0_p D_p (times V for V o N; Eq 94)
-                                const T* b0 = k_->b0 + (long)pe * nxy;
+                                // u = sum_p b0_p D_p (times V for V o N; Eq 94), or with
+                                // the rows b^a the implicit gradient, a field per row
                                 const T* vol = k_->vol ? k_->vol + (long)pe * nxy : nullptr;
-                                Tio* o = out + (long)pe * nxy;
 #pragma unroll
-                                for (int i = 0; i < 2; ++i) {
-                                    if (x0 + 2 * gi + i < nx && y0 + yy < ny) {
-                                        const uint32_t g = i ? jt3[k] : it3[k];
-                                        T acc = T(0);
+                                for (int r = 0; r < ROWS; ++r) {
+                                    const T* b = k_->rows + (long)r * S * k_->nn + (long)pe * nxy;
+                                    Tio* o = out + r * k_->nn + (long)pe * nxy;
 #pragma unroll
-                                        for (int p = 0; p < S; ++p) acc += (b0 + p * k_->nn)[g] * D[i][p];
-                                        o[g] = Tio(vol ? acc * vol[g] : acc);
+                                    for (int i = 0; i < 2; ++i) {
+                                        if (x0 + 2 * gi + i < nx && y0 + yy < ny) {
+                                            const uint32_t g = i ? jt3[k] : it3[k];
+                                            T acc = T(0);
+#pragma unroll
+                                            for (int p = 0; p < S; ++p) acc += (b + p * k_->nn)[g] * D[i][p];
+                                            o[g] = Tio(vol ? acc * vol[g] : acc);
+                                        }
                                     }
                                 }
                             } else {
                                 T E[2][S];
                                 if constexpr (MODE == TAP_LOAD) {
                                     // E_p = (V) b0_p r  (Eq 92, Alg 4)
-                                    const T* b0 = k_->b0 + (long)pe * nxy;
+                                    const T* b = k_->rows + (long)pe * nxy;
                                     const T* vol = k_->vol ? k_->vol + (long)pe * nxy : nullptr;
                                     const Tio* pi = in + (long)pe * nxy;
 #pragma unroll
@@ -475,12 +489,24 @@ struct TapMarch {
                                         const uint32_t g = i ? jt3[k] : it3[k];
                                         const T x = vol ? T(pi[g]) * vol[g] : T(pi[g]);
 #pragma unroll
-                                        for (int p = 0; p < S; ++p) E[i][p] = (b0 + p * k_->nn)[g] * x;
+                                        for (int p = 0; p < S; ++p) E[i][p] = (b + p * k_->nn)[g] * x;
                                     }
                                 } else if (__all((word[k] & 15) == 5)) {
                                     // interior nodes throughout the wave: the shared record
 #pragma unroll
                                     for (int i = 0; i < 2; ++i) point(k_->mint, k_, D[i], E[i]);
+                                } else if constexpr (MODE == TAP_KN) {
+                                    // rows and V from the node arrays (zero outside the domain)
+                                    const T* b = k_->rows + (long)pe * nxy;
+#pragma unroll
+                                    for (int i = 0; i < 2; ++i) {
+                                        const uint32_t g = i ? jt3[k] : it3[k];
+                                        T m[ROWS * S + 1];
+#pragma unroll
+                                        for (int j = 0; j < ROWS * S; ++j) m[j] = (b + j * k_->nn)[g];
+                                        m[ROWS * S] = (k_->vol + (long)pe * nxy)[g];
+                                        point(m, k_, D[i], E[i]);
+                                    }
                                 } else {
 #pragma unroll
                                     for (int i = 0; i < 2; ++i)
@@ -498,7 +524,7 @@ struct TapMarch {
             }
             if constexpr (Bq) {
                 if (s >= 2 * RZ + 2 && do5) {
-                    const KP k_ = tap_fresh(kp);
+                    const KP k_ = tap_fresh<(S <= 4)>(kp);
                     T g[NZ][NB5];
 #pragma unroll
                     for (int e = 0; e < NZ; ++e)
@@ -529,13 +555,25 @@ struct TapMarch {
                             zout[k][j] = acc;
                         }
                     if (s >= 4 * RZ + 2) {
-                        const long zo = (long)(zlo + s - (4 * RZ + 2)) * nxy;
+                        const int z = zlo + s - (4 * RZ + 2);
+                        const long zo = (long)z * nxy;
 #pragma unroll
                         for (int k = 0; k < NB5; ++k) {
                             if (ok5[k]) {
                                 const Tio v = mk5[k] ? Tio(zout[k][0]) : Tio(0);
                                 (out + zo)[o5 + (uint32_t)(k * nx)] = v;
                                 if (dwith) dacc += (double)v * (double)(dwith + zo)[o5 + (uint32_t)(k * nx)];
+                            }
+                        }
+                        if (dwith) {
+                            if (--left == 0 || z + 1 == zhi) {
+                                // the partial of these planes is complete
+#pragma unroll
+                                for (int o = 32; o > 0; o >>= 1) dacc += __shfl_xor(dacc, o, 64);
+                                if ((tid & 63) == 0) dsum[i5 >> 6] = dacc;
+                                dacc = 0.0;
+                                left = kp->cu;
+                                flush = true;
                             }
                         }
                     }
@@ -547,12 +585,22 @@ struct TapMarch {
                 // the classes of the next plane, asked for ahead of their use
                 if (s >= 2 * RZ + 1 && s + 1 < nE + 2 * RZ + 1) {
                     pe = (pe + 1 == nz) ? 0 : pe + 1;
-                    const uint32_t* pw = tap_fresh(kp)->words + (long)pe * ny * gx;
+                    const uint32_t* pw = tap_fresh<(S <= 4)>(kp)->words + (long)pe * ny * gx;
 #pragma unroll
-                    for (int k = 0; k < NP3; ++k) word[k] = pw[it3[k]];
+                    for (int k = 0; k < NP3; ++k) word[k] = pw[wt3[k]];
                 }
             }
             if constexpr (Bq) {
+                if (flush) {
+                    if (i5 == 0) {
+                        double r = 0.0;
+#pragma unroll
+                        for (int w = 0; w < N5 / 64; ++w) r += dsum[w];
+                        *dpart = r;
+                    }
+                    dpart += ntiles;
+                    flush = false;
+                }
                 // the mask of the next result plane
                 if (s + 1 >= 4 * RZ + 2 && s + 1 < s1) {
                     const uint8_t* pm = mask_out + (long)(zlo + s + 1 - (4 * RZ + 2)) * nxy;
@@ -563,7 +611,7 @@ struct TapMarch {
             }
             if constexpr (G::P1) {
                 if (s >= 2 * RZ && s < nE + 2 * RZ && (!RO::SPLIT || !G::P2 || tid < RO::N2)) {
-                    const KP k_ = tap_fresh(kp);
+                    const KP k_ = tap_fresh<(S <= 4)>(kp);
                     for (int it = tid; it < XL * (YE / NB2); it += G::P2 ? RO::N2 : NT) {
                         const int x = it % XL, yb = it / XL * NB2;
                         T w[NZ][NB2 + 2 * RY];
@@ -583,7 +631,7 @@ struct TapMarch {
             }
             if constexpr (G::P2) {
                 if (s >= 2 * RZ + 1 && s < nE + 2 * RZ + 1 && (!RO::SPLIT || tid >= RO::N2)) {
-                    const KP k_ = tap_fresh(kp);
+                    const KP k_ = tap_fresh<(S <= 4)>(kp);
                     for (int it = RO::SPLIT ? tid - RO::N2 : tid; it < TX / XB4 * YE; it += RO::N4) {
                         const int xb = it % (TX / XB4) * XB4, yy = it / (TX / XB4);
                         T f_[NY][XB4];
@@ -617,7 +665,6 @@ struct TapMarch {
             }
             tap_barrier();
         }
-        return dacc;
     }
 };
 
@@ -634,7 +681,7 @@ __global__ __launch_bounds__(NT, tap_min_waves(sizeof(T), tap_lds_of<B, R, MODE,
     const long rj = (long)blockIdx.y * kp->rb;
     const Tio* const in = reinterpret_cast<const Tio*>((const char*)kp->in + rj);
     Tio* const out = reinterpret_cast<Tio*>((char*)kp->out + rj);
-    double* const dpart = kp->dot_part;
+    double* const dpart = kp->dot_part ? kp->dot_part + (long)blockIdx.y * kp->dot_stride : nullptr;
     const Tio* const dwith = dpart ? reinterpret_cast<const Tio*>((const char*)kp->dot_with + rj) : nullptr;
     int b = (int)tap_xcd(blockIdx.x, gridDim.x);
     const int tx = b % ntx;
@@ -655,32 +702,26 @@ __global__ __launch_bounds__(NT, tap_min_waves(sizeof(T), tap_lds_of<B, R, MODE,
             }
         }
     }
-    double dacc = 0.0;
+    const int ntiles = ntx * nty, tile = ty * ntx + tx;
+    if constexpr (G::P2) {
+        if (dpart && tid == 0)
+            for (int u = za / kp->cu; u * kp->cu < ze; ++u)
+                if (zlo >= zhi || (u + 1) * kp->cu <= zlo || u * kp->cu >= zhi) dpart[(long)u * ntiles + tile] = 0.0;
+    }
     if (zlo < zhi) {
         // the roles hold different state: each gets its own copy of the march
         // (both meet at the same number of barriers)
+        __shared__ double dsum[NT / 64];
+#define FC_TAP_RUN(ROLE)                                                                                          \
+    TapMarch<T, Tio, B, R, MODE, ROWS, TX, TY, NT, ROLE>::run(kp, smem, dsum, in, out, dwith, dpart, tile, ntiles, \
+                                                              x0, y0, zlo, zhi)
         if constexpr (!RO::SPLIT) {
-            dacc = TapMarch<T, Tio, B, R, MODE, ROWS, TX, TY, NT, 3>::run(kp, smem, in, out, dwith, x0, y0, zlo, zhi);
+            FC_TAP_RUN(3);
         } else {
-            if (__builtin_amdgcn_readfirstlane(tid) < RO::NA)
-                dacc = TapMarch<T, Tio, B, R, MODE, ROWS, TX, TY, NT, 1>::run(kp, smem, in, out, dwith, x0, y0, zlo, zhi);
-            else
-                dacc = TapMarch<T, Tio, B, R, MODE, ROWS, TX, TY, NT, 2>::run(kp, smem, in, out, dwith, x0, y0, zlo, zhi);
+            if (__builtin_amdgcn_readfirstlane(tid) < RO::NA) FC_TAP_RUN(1);
+            else FC_TAP_RUN(2);
         }
-    }
-    if constexpr (G::P2) {
-        if (dpart) {
-            __shared__ double sh[NT / 64];
-#pragma unroll
-            for (int o = 32; o > 0; o >>= 1) dacc += __shfl_xor(dacc, o, 64);
-            if ((tid & 63) == 0) sh[tid >> 6] = dacc;
-            __syncthreads();
-            if (tid == 0) {
-                double r = 0.0;
-                for (int i = 0; i < NT / 64; ++i) r += sh[i];
-                dpart[(long)blockIdx.y * kp->dot_stride + blockIdx.x] = r;
-            }
-        }
+#undef FC_TAP_RUN
     }
 }
 

@@ -143,3 +143,53 @@ def test_fft_options_pin_the_fft_passes():
     h, chi, dirichlet, vol = domain((32, 32, 32), 4.5, "box")
     g = f.Problem((32,) * 3, h, (4.5,) * 3, 1, chi, dirichlet, vol, device=DEV)
     assert g.get_option(f.OPT_TAPS) == 0
+
+
+NODE_OPS = [
+    ((36, 30, 28), 2.5, "ball", 1), ((35, 18, 10), 1.5, "inside", 1), ((32, 16, 20), 3.5, "box", 1),
+    ((35, 16, 18), 3.0, "box", 2), ((20, 18, 16), 3.5, "box", 2), ((35, 49), 2.0, "ball", 1),
+    ((64, 15), 3.5, "box", 2), ((40, 36), 4.0, "box", 3), ((270,), 2.5, "box", 1), ((128,), 3.5, "box", 2),
+    ((225,), 4.0, "box", 3),
+]
+
+
+@pytest.mark.parametrize("dims,at,kind,degree", NODE_OPS)
+def test_node_operators(dims, at, kind, degree):
+    """u^h, V o N, the loads and the gradient force (Alg 3, 4, A.1, B.1)."""
+    print(f"\n[taps N, N^T, B] {dims} support {at} {kind} degree {degree}", flush=True)
+    f = fc()
+    g, o, chi, free = make(dims, at, degree, kind)
+    rng = np.random.default_rng(4)
+    x = rng.standard_normal(chi.shape)
+    xm = np.where(chi > 0, x, 0.0)
+    area = np.where(chi > 0, rng.uniform(0.0, 1.0, chi.shape), 0.0)
+    g.set_boundary(area)
+    refs = {"UH": o.apply_uh(xm), "VN": o.apply_vn(xm), "FR": o.apply_fr(xm), "NT": o.apply_nt(xm),
+            "FQ": o.apply_fq(xm, area)}
+    for dtype, tol in ((torch.float64, 1e-11), (torch.float32, 2e-5)):
+        xt = torch.from_numpy(x).to(DEV, dtype)
+        for op, ref in refs.items():
+            got = g.apply(op, xt).cpu().numpy()
+            check(got.astype(np.float64), np.where(chi > 0, ref, 0.0), tol, f"{op} {dtype}")
+            assert np.all(got[chi == 0] == 0.0)
+            np.testing.assert_array_equal(g.apply(op, torch.stack([2 * xt, xt])).cpu().numpy()[1], got)
+    kappa = 0.8 * min(1.0 / n for n in dims) ** 2
+    ref = o.apply_fn_grad(xm, kappa)
+    xt = torch.from_numpy(x).to(DEV)
+    check(g.gradient_force(xt, kappa).cpu().numpy(), np.where(chi > 0, ref, 0.0), 1e-11, "gradient force")
+
+
+def test_uh_over_d():
+    """A caller of the C interface may take u^h in place of d."""
+    import ctypes as C
+    f = fc()
+    h, chi, dirichlet, vol = domain((36, 30, 28), 2.5, "box")
+    g = f.Problem((36, 30, 28), h, (2.5,) * 3, 1, chi, dirichlet, vol, device=DEV)
+    r = torch.from_numpy(np.where(chi > 0, 1.0, 0.0)).to(DEV)
+    _, uh, _ = g.solve(r, tol=1e-10)
+    d = torch.zeros_like(r)
+    st = f.load_library().fcrkpm_solve(g._h, f.MODE_F64, 1, C.c_void_p(r.data_ptr()), None,
+                                       C.c_void_p(d.data_ptr()), C.c_void_p(d.data_ptr()), 1e-10, 20000,
+                                       None, C.c_void_p(torch.cuda.current_stream().cuda_stream))
+    assert st == f.OK
+    assert torch.equal(d, uh)
