@@ -182,9 +182,9 @@ struct Ctx {
     int tuned[3] = {0, 16, 16};         // setup's register variant and lines per workgroup (FP32, FP64)
     int tap_r = 0;                      // tap radius: the largest ceil(a~) - 1 of the axes
     double tap_t[3][5][4] = {};         // taps t_e(o) of each axis, o = 0..3
-    int tap_nt[2] = {0, 0};             // tiles along x and y
+    int tap_nt[2][2] = {};              // tiles along x and y, of the large and the small tile
     int tap_cus = 256;                  // compute units of the device
-    int2* tap_zr = nullptr;             // first and last domain plane of each tile column
+    int2* tap_zr[2] = {};               // first and last domain plane of each tile column
     void* tap = nullptr;                // class words and records of the K-type product in use
 };
 

@@ -36,9 +36,9 @@
 #define FC_TAP_MIX(X) FC_TAP_KS(X, float, double)
 
 #define FC_TAP_EXTERN(T, U, DIM, DEG, R, MODE, ROWS) \
-    extern template void tap_go<T, U, TapBasis<DIM, DEG>, R, MODE, ROWS>(const TapArgs<T>&, dim3, hipStream_t);
+    extern template void tap_go<T, U, TapBasis<DIM, DEG>, R, MODE, ROWS>(const TapArgs<T>&, dim3, bool, hipStream_t);
 #define FC_TAP_BUILD(T, U, DIM, DEG, R, MODE, ROWS) \
-    template void tap_go<T, U, TapBasis<DIM, DEG>, R, MODE, ROWS>(const TapArgs<T>&, dim3, hipStream_t);
+    template void tap_go<T, U, TapBasis<DIM, DEG>, R, MODE, ROWS>(const TapArgs<T>&, dim3, bool, hipStream_t);
 
 namespace fcrkpm {
 FC_TAP_F32(FC_TAP_EXTERN)

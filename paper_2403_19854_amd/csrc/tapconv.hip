@@ -43,8 +43,8 @@ void tap_free(TapSet* s)
     delete s;
 }
 
-int tile_x(const Ctx& c) { return tap_tile_x(c.dim, c.degree, c.tap_r); }
-int tile_y(const Ctx& c) { return tap_tile_y(c.dim); }
+int tile_x(const Ctx& c, bool small = false) { return tap_tile_x(c.dim, c.degree, c.tap_r, small); }
+int tile_y(const Ctx& c, bool small = false) { return tap_tile_y(c.dim, small); }
 int tap_gx(const Ctx& c)
 {
     const int tx = tile_x(c);
@@ -151,9 +151,9 @@ __global__ __launch_bounds__(256) void k_tap_words(const uint8_t* __restrict__ c
 }
 
 // values one workgroup keeps in LDS (TapGeom of a K product)
-int tap_lds(const Ctx& c)
+int tap_lds(const Ctx& c, bool small)
 {
-    const int r = c.tap_r, d = c.degree, dim = c.dim, tx = tile_x(c), ty = tile_y(c);
+    const int r = c.tap_r, d = c.degree, dim = c.dim, tx = tile_x(c, small), ty = tile_y(c, small);
     const int ry = dim > 1 ? r : 0;
     const int nz = dim > 2 ? d + 1 : 1;
     const int ny = dim > 2 ? (d + 1) * (d + 2) / 2 : dim > 1 ? d + 1 : 1;
@@ -161,38 +161,64 @@ int tap_lds(const Ctx& c)
     return nz * yl * xl + ny * ye * xl + c.s * ye * xe + ny * ye * tx;
 }
 
-// Planes per chunk.  A chunk of cz planes takes cz + 4R + 2 steps, so few long
-// chunks do the least work, but the workgroups have to fill the chip evenly: a
-// step with r workgroups on a CU takes about 0.9 + 0.6 r (us at R = 2 in FP32;
-// measured 1.6, 2.0 and 2.7 for r = 1, 2, 3), and a last round that fills a
-// few CUs takes as long as a full one.
+// Tile and planes per chunk.  A chunk of cz planes takes cz + 2R + 2 steps, so
+// few long chunks do the least work, but the workgroups have to fill the chip
+// evenly: a step with r workgroups on a CU takes about s0 + s1 r, and a last
+// round that fills a few CUs takes as long as a full one.  Measured at R = 2 in
+// FP32, us a step: large tile 1.45-1.8, 1.9-2.05, 2.4-2.5 for r = 1, 2, 3; small
+// tile 1.15-1.25, 1.2-1.5, 1.3-1.6, 1.5-1.7 for r = 1 to 4 (a quarter of the
+// columns, so it pays only where the large tile leaves CUs idle: 32^3 10.1 us
+// against 11.9, 48^3 FP64 15.9 against 17.5; 128^3 39.7 against 32.1).  In FP64:
+// 1.9-2.4, 2.8-3.1; 1.35-1.8, 1.55-2.0, 1.85-2.2, 2.2-2.4.
+struct TapCut {
+    bool small;
+    int cz;
+    double cost;
+};
+
 // unit: the chunk has to be a multiple of so many planes.
-int tap_planes(const Ctx& c, int nrhs, int elem, int unit)
+TapCut tap_cut_tile(const Ctx& c, bool small, int nrhs, int elem, int unit)
 {
     const int nz = c.n[2];
-    if (c.dim < 3) return 1;
-    const long tiles = (long)c.tap_nt[0] * c.tap_nt[1] * nrhs;
-    const int occ = tap_residents(elem, tap_lds(c), tap_cap(elem, c.s, c.tap_r));
-    const double slots = (double)c.tap_cus * occ;
-    int best = unit;
-    double cost = 1e300;
+    if (c.dim < 3) return {false, 1, 0.0};
+    const long tiles = (long)c.tap_nt[small][0] * c.tap_nt[small][1] * nrhs;
+    const bool f64 = elem == 8;
+    const int occ = tap_residents(elem, tap_lds(c, small), tap_threads(c.dim, small), c.s, c.tap_r);
+    const double slots = (double)c.tap_cus * occ, s0 = f64 ? (small ? 1.25 : 1.4) : (small ? 1.0 : 1.1),
+                 s1 = f64 ? (small ? 0.3 : 0.85) : (small ? 0.16 : 0.47);
+    TapCut best{small, unit, 1e300};
     for (int k = (nz + unit - 1) / unit; k >= 1; --k) {
         const int cz = ((nz + k - 1) / k + unit - 1) / unit * unit;
         const double wg = (double)tiles * ((nz + cz - 1) / cz), full = floor(wg / slots), rem = wg - full * slots;
-        const double t = (std::min(cz, nz) + 4 * c.tap_r + 2) *
-                         (full * (0.9 + 0.6 * occ) +
-                          (rem > 0.0 ? 0.9 + 0.6 * ceil(rem / c.tap_cus) : 0.0));
-        if (t <= cost) {
-            cost = t;
-            best = cz;
-        }
+        const double t = (std::min(cz, nz) + 2 * c.tap_r + 2) *
+                         (full * (s0 + s1 * occ) + (rem > 0.0 ? s0 + s1 * ceil(rem / c.tap_cus) : 0.0));
+        if (t <= best.cost) best = {small, cz, t};
     }
     return best;
 }
 
-// planes per dot partial: the chunk of one right-hand side, so that the dots of
-// a batch add up the same partials as single ones
-int tap_unit(const Ctx& c, int elem) { return tap_planes(c, 1, elem, 1); }
+TapCut tap_cut_one(const Ctx& c, int elem)
+{
+    const TapCut a = tap_cut_tile(c, false, 1, elem, 1);
+    if (c.dim < 3) return a;
+    const TapCut b = tap_cut_tile(c, true, 1, elem, 1);
+    return b.cost < a.cost ? b : a;
+}
+
+// The cut of a K product over nrhs right-hand sides.  With dots it is a
+// multiple of one right-hand side's, so that a batch adds up the same partials
+// as single products.
+TapCut tap_cut(const Ctx& c, int mode, int nrhs, int elem, bool dots)
+{
+    if (mode != TAP_K) return tap_cut_tile(c, false, nrhs, elem, 1);
+    const TapCut one = tap_cut_one(c, elem);
+    if (nrhs == 1) return one;
+    if (dots) return tap_cut_tile(c, one.small, nrhs, elem, one.cz);
+    const TapCut a = tap_cut_tile(c, false, nrhs, elem, 1);
+    if (c.dim < 3) return a;
+    const TapCut b = tap_cut_tile(c, true, nrhs, elem, 1);
+    return b.cost < a.cost ? b : a;
+}
 
 }  // namespace
 
@@ -203,8 +229,8 @@ bool tap_active(const Ctx& c) { return c.use_taps && !c.fft_pins && c.tap; }
 
 long tap_dots(const Ctx& c, int elem)
 {
-    const int cu = tap_unit(c, elem);
-    return (long)c.tap_nt[0] * c.tap_nt[1] * ((c.n[2] + cu - 1) / cu);
+    const TapCut u = tap_cut_one(c, elem);
+    return (long)c.tap_nt[u.small][0] * c.tap_nt[u.small][1] * ((c.n[2] + u.cz - 1) / u.cz);
 }
 
 long tap_dot_slots(const Ctx& c) { return c.tap ? std::max(tap_dots(c, 4), tap_dots(c, 8)) : 0; }
@@ -218,8 +244,10 @@ void tap_release_set(void*& s)
 void tap_release(Ctx& c)
 {
     tap_release_set(c.tap);
-    if (c.tap_zr) (void)hipFree(c.tap_zr);
-    c.tap_zr = nullptr;
+    for (auto& z : c.tap_zr) {
+        if (z) (void)hipFree(z);
+        z = nullptr;
+    }
 }
 
 // taps and the domain's extent per tile column (once per context)
@@ -229,12 +257,14 @@ void tap_setup(Ctx& c, const double (*taps)[kTapE][kTapR + 1], hipStream_t st)
     int dev = 0;
     tap_check(hipGetDevice(&dev));
     tap_check(hipDeviceGetAttribute(&c.tap_cus, hipDeviceAttributeMultiprocessorCount, dev));
-    const int tx = tile_x(c), ty = tile_y(c);
-    c.tap_nt[0] = (c.n[0] + tx - 1) / tx;
-    c.tap_nt[1] = (c.n[1] + ty - 1) / ty;
-    c.tap_zr = tap_alloc<int2>((size_t)c.tap_nt[0] * c.tap_nt[1]);
-    hipLaunchKernelGGL(k_tap_extent, dim3(c.tap_nt[0] * c.tap_nt[1]), dim3(256), 0, st, c.chi, c.n[0], c.n[1],
-                       c.n[2], c.tap_nt[0], tx, ty, c.tap_zr);
+    for (int small = 0; small < (c.dim == 3 ? 2 : 1); ++small) {
+        const int tx = tile_x(c, small), ty = tile_y(c, small);
+        const int nx = c.tap_nt[small][0] = (c.n[0] + tx - 1) / tx;
+        const int ny = c.tap_nt[small][1] = (c.n[1] + ty - 1) / ty;
+        c.tap_zr[small] = tap_alloc<int2>((size_t)nx * ny);
+        hipLaunchKernelGGL(k_tap_extent, dim3(nx * ny), dim3(256), 0, st, c.chi, c.n[0], c.n[1], c.n[2], nx, tx,
+                           ty, c.tap_zr[small]);
+    }
     tap_check(hipGetLastError());
 }
 
@@ -318,11 +348,12 @@ void launch_tap(const Ctx& c, int mode, const Tio* in, Tio* out, const uint8_t* 
         for (int e = 0; e < kTapE; ++e)
             for (int o = 0; o <= kTapR; ++o) a.t[k][e][o] = (T)c.tap_t[k][e][o];
     }
-    a.ntx = c.tap_nt[0];
-    a.nty = c.tap_nt[1];
-    a.cu = tap_unit(c, sizeof(T));
-    a.cz = nrhs > 1 ? tap_planes(c, nrhs, sizeof(T), a.cu) : a.cu;
-    a.zr = c.tap_zr;
+    const TapCut cut = tap_cut(c, mode, nrhs, sizeof(T), dot_part != nullptr);
+    a.ntx = c.tap_nt[cut.small][0];
+    a.nty = c.tap_nt[cut.small][1];
+    a.cu = dot_part ? tap_cut_one(c, sizeof(T)).cz : cut.cz;
+    a.cz = cut.cz;
+    a.zr = c.tap_zr[cut.small];
     a.words = s.words;
     a.gx = tap_gx(c);
     if constexpr (sizeof(T) == 8) {
@@ -348,7 +379,7 @@ void launch_tap(const Ctx& c, int mode, const Tio* in, Tio* out, const uint8_t* 
     bool done = false;
 #define FC_TAP_CASE(T_, TIO_, DIM, DEG, R, MODE, ROWS)                                              \
     if (!done && c.dim == DIM && c.degree == DEG && c.tap_r == R && kmode == MODE && rows == ROWS) { \
-        tap_go<T_, TIO_, TapBasis<DIM, DEG>, R, MODE, ROWS>(a, grid, st);                       \
+        tap_go<T_, TIO_, TapBasis<DIM, DEG>, R, MODE, ROWS>(a, grid, cut.small, st);                       \
         done = true;                                                                                \
     }
     if constexpr (sizeof(T) == 8) {

@@ -196,18 +196,22 @@ struct TapGeom {
 
 template <class B, int R, int MODE, int TX, int TY>
 constexpr int tap_lds_of = TapGeom<B, R, MODE, TX, TY>::LDS;
-// Workgroups that the LDS of a CU (160 KB) holds, at most `cap`; the registers are
-// held to what that needs (waves per SIMD).
-constexpr int tap_residents(int elem, int lds, int cap)
+// Workgroups that a CU is meant to hold: as many as the LDS (160 KB) takes, but
+// no more than leave every thread the registers it needs (about 80 of 4 bytes
+// for the small bases in FP32 at R <= 2, 128 in FP64 and for larger ones, 256
+// for ten monomials in FP64 or at R = 3).
+constexpr int tap_residents(int elem, int lds, int nt, int s, int r)
 {
-    const int n = 160 * 1024 / (elem * lds + 64);
-    return n < 1 ? 1 : n > cap ? cap : n;
+    const int waves = elem == 4 && s <= 4 && r <= 2 ? 24 : elem == 8 && (s == 10 || r == 3) ? 8 : s == 10 && r == 3 ? 8 : 16;
+    const int byregs = waves / (nt / 64), bylds = 160 * 1024 / (elem * lds + 64);
+    const int n = byregs < bylds ? byregs : bylds;
+    return n < 1 ? 1 : n;
 }
-constexpr int tap_cap(int elem, int s, int r)
+constexpr int tap_min_waves(int elem, int lds, int nt, int s, int r)
 {
-    return elem == 4 && s <= 4 && r <= 2 ? 3 : elem == 8 && s == 10 && r == 3 ? 1 : 2;
+    const int w = tap_residents(elem, lds, nt, s, r) * (nt / 64) / 4;
+    return w < 1 ? 1 : w;
 }
-constexpr int tap_min_waves(int elem, int lds, int nt, int cap) { return tap_residents(elem, lds, cap) * (nt / 64) / 4; }
 
 // The arguments live in the kernel-argument segment.  The taps and the interior
 // record of a small basis stay in scalar registers; those of a large one would
@@ -247,7 +251,7 @@ struct TapMarch {
     static constexpr int NC = G::P1 ? (XL * YL + NT - 1) / NT : 1;          // input columns per thread
     static constexpr int NB2 = YE % 4 == 0 ? 4 : YE % 2 == 0 ? 2 : 1;       // rows per item, y convolution
     static constexpr int XB4 = 4;                                           // nodes per item, x reflection
-    static constexpr int NB5 = TY % 4 == 0 ? 4 : 1;                         // rows per item, y reflection
+    static constexpr int NB5 = TY % 4 ? 1 : TX * TY >= 256 ? 4 : 2;         // rows per item, y reflection
     static constexpr int N3 = XE / 2 * YE, NP3 = (N3 + RO::NA - 1) / RO::NA;
     static constexpr int N5 = TX * (TY / NB5);
     static_assert((!G::P2 || (N5 <= RO::NB && N5 % 64 == 0)) && XE % 2 == 0 && TX % XB4 == 0);
@@ -369,11 +373,6 @@ struct TapMarch {
                 }
             }
         }
-        T zin[NC][2 * RZ + 1];   // the last planes of each column
-#pragma unroll
-        for (int k = 0; k < NC; ++k)
-#pragma unroll
-            for (int j = 0; j <= 2 * RZ; ++j) zin[k][j] = T(0);
         const int i5 = RO::SPLIT ? tid - RO::NA : tid;
         const bool do5 = Bq && i5 >= 0 && i5 < N5;
         const int x5 = i5 % TX, y5 = i5 / TX * NB5;
@@ -394,16 +393,24 @@ struct TapMarch {
         const int nE = zhi - zlo + 2 * HZ;               // E-level planes
         int pin = tap_wrap(zlo - HZ - RZ, nz);           // next plane to load
         int pe = tap_wrap(zlo - HZ, nz);                 // next plane of the E level
-        // values are loaded a step ahead and masked when they are used
+        // the last planes of each column: the first 2 RZ are loaded here, all at
+        // once; from then on values are loaded a step ahead and masked when they
+        // are used
+        T zin[NC][2 * RZ + 1];
         Tio nxt[NC];
         uint8_t nmk[NC];
         if constexpr (G::P1) {
-            const Tio* pi = in + (long)pin * nxy;
-            const uint8_t* pm = mask_in + (long)pin * nxy;
 #pragma unroll
-            for (int k = 0; k < NC; ++k) {
-                nxt[k] = pi[col[k]];
-                nmk[k] = pm[col[k]];
+            for (int j = 0; j <= 2 * RZ; ++j) {
+                const Tio* pi = in + (long)pin * nxy;
+                const uint8_t* pm = mask_in + (long)pin * nxy;
+#pragma unroll
+                for (int k = 0; k < NC; ++k) {
+                    nxt[k] = pi[col[k]];
+                    nmk[k] = pm[col[k]];
+                    if (j < 2 * RZ) zin[k][j + 1] = nmk[k] ? T(nxt[k]) : T(0);
+                }
+                if (j < 2 * RZ) pin = (pin + 1 == nz) ? 0 : pin + 1;
             }
         }
         uint32_t word[NP3];
@@ -412,7 +419,7 @@ struct TapMarch {
 #pragma unroll
             for (int k = 0; k < NP3; ++k) word[k] = pw[wt3[k]];
         }
-        const int s0 = G::P1 ? 0 : 2 * RZ + 1, s1 = nE + 2 * RZ + (G::P2 ? 2 : 1);
+        const int s0 = G::P1 ? 2 * RZ : 2 * RZ + 1, s1 = nE + 2 * RZ + (G::P2 ? 2 : 1);
         for (int s = s0; s < s1; ++s) {
             // ---------------------------------------------------------- half A
             if constexpr (G::P1) {
@@ -437,15 +444,13 @@ struct TapMarch {
                         for (int j = 0; j < 2 * RZ; ++j) zin[k][j] = zin[k][j + 1];
                         zin[k][2 * RZ] = cur[k];
                     }
-                    if (s >= 2 * RZ) {
 #pragma unroll
-                        for (int k = 0; k < NC; ++k)
-                            if ((k + 1) * NT <= XL * YL || tid + k * NT < XL * YL)
-                                tap_for<NZ>([&](auto ec) {
-                                    constexpr int e = decltype(ec)::value;
-                                    sZ[e * YL * XL + tid + k * NT] = tap_conv<RZ, false, e>(zin[k], k_->t[2][e]);
-                                });
-                    }
+                    for (int k = 0; k < NC; ++k)
+                        if ((k + 1) * NT <= XL * YL || tid + k * NT < XL * YL)
+                            tap_for<NZ>([&](auto ec) {
+                                constexpr int e = decltype(ec)::value;
+                                sZ[e * YL * XL + tid + k * NT] = tap_conv<RZ, false, e>(zin[k], k_->t[2][e]);
+                            });
                 }
             }
             if constexpr (A) {
@@ -610,7 +615,7 @@ struct TapMarch {
                 }
             }
             if constexpr (G::P1) {
-                if (s >= 2 * RZ && s < nE + 2 * RZ && (!RO::SPLIT || !G::P2 || tid < RO::N2)) {
+                if (s < nE + 2 * RZ && (!RO::SPLIT || !G::P2 || tid < RO::N2)) {
                     const KP k_ = tap_fresh<(S <= 4)>(kp);
                     for (int it = tid; it < XL * (YE / NB2); it += G::P2 ? RO::N2 : NT) {
                         const int x = it % XL, yb = it / XL * NB2;
@@ -669,7 +674,7 @@ struct TapMarch {
 };
 
 template <typename T, typename Tio, class B, int R, int MODE, int ROWS, int TX, int TY, int NT>
-__global__ __launch_bounds__(NT, tap_min_waves(sizeof(T), tap_lds_of<B, R, MODE, TX, TY>, NT, tap_cap(sizeof(T), B::S, R))) void k_tap(const TapArgs<T>)
+__global__ __launch_bounds__(NT, tap_min_waves(sizeof(T), tap_lds_of<B, R, MODE, TX, TY>, NT, B::S, R)) void k_tap(const TapArgs<T>)
 {
     using G = TapGeom<B, R, MODE, TX, TY>;
     using RO = TapRoles<B::DIM, NT>;
@@ -730,14 +735,27 @@ __global__ __launch_bounds__(NT, tap_min_waves(sizeof(T), tap_lds_of<B, R, MODE,
 // measured slower (256^3 FP32: 189 and 188 us against 175), 32 x 8 over 4 waves
 // too (197).  The quadratic basis in 3D at R = 3 takes half the columns, so
 // that its FP64 fields fit the LDS.
-constexpr int tap_tile_x(int dim, int degree, int r) { return dim == 1 ? 256 : dim == 3 && degree == 2 && r == 3 ? 16 : 32; }
-constexpr int tap_tile_y(int dim) { return dim == 1 ? 1 : 16; }
+// SMALL: 16 x 8 columns over 4 waves, for 3D boxes that leave the chip idle.
+constexpr int tap_tile_x(int dim, int degree, int r, bool small)
+{
+    return dim == 1 ? 256 : small || (dim == 3 && degree == 2 && r == 3) ? 16 : 32;
+}
+constexpr int tap_tile_y(int dim, bool small) { return dim == 1 ? 1 : small ? 8 : 16; }
+constexpr int tap_threads(int dim, bool small) { return dim == 1 || small ? 256 : 512; }
 
 // instantiated in tap_f32.hip and tap_f64.hip
 template <typename T, typename Tio, class B, int R, int MODE, int ROWS>
-void tap_go(const TapArgs<T>& a, dim3 grid, hipStream_t st)
+void tap_go(const TapArgs<T>& a, dim3 grid, bool small, hipStream_t st)
 {
-    constexpr int TX = tap_tile_x(B::DIM, B::DEG, R), TY = tap_tile_y(B::DIM), NT = B::DIM == 1 ? 256 : 512;
+    if constexpr (B::DIM == 3 && MODE == TAP_K) {
+        if (small) {
+            constexpr int TX = tap_tile_x(3, B::DEG, R, true), TY = tap_tile_y(3, true), NT = tap_threads(3, true);
+            hipLaunchKernelGGL((k_tap<T, Tio, B, R, MODE, ROWS, TX, TY, NT>), grid, dim3(NT), 0, st, a);
+            return;
+        }
+    }
+    constexpr int TX = tap_tile_x(B::DIM, B::DEG, R, false), TY = tap_tile_y(B::DIM, false);
+    constexpr int NT = tap_threads(B::DIM, false);
     hipLaunchKernelGGL((k_tap<T, Tio, B, R, MODE, ROWS, TX, TY, NT>), grid, dim3(NT), 0, st, a);
 }
 
