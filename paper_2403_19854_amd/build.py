@@ -10,7 +10,8 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libfcrkpm.so")
 SOURCES = ["kernels.hip", "sepconv.hip", "regpass.hip", "fcrkpm.hip",
-           "tapconv.hip", "tap_f32.hip", "tap_f64.hip", "tap_f64n.hip", "tap_mix.hip"]
+           "tapconv.hip", "tap_f32.hip", "tap_f64.hip", "tap_f64n.hip", "tap_mix.hip",
+           "tap_cg32.hip", "tap_cg64.hip"]
 
 HIPCC_FLAGS = [
     "-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950",

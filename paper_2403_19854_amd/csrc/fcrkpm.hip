@@ -598,15 +598,15 @@ void reg_k(Ctx& c, const float* in, float* out, const uint8_t* mask, int nrhs, h
     launch_reg_k(c, in, out, mask, nrhs, dot_part, dot_with, st, rp, pu);
 }
 
-// The K-type product on the direct tap kernels, with the partials of
-// out . dot_with where dot_part is given.
+// The K-type product on the direct tap kernels; with cg the one of a CG
+// iteration, which reads r in place of the mask and also writes p.
 template <typename T, typename Tio>
 void tap_k(Ctx& c, const Tio* in, Tio* out, const uint8_t* mask, int nrhs, hipStream_t st,
-           double* dot_part = nullptr, const Tio* dot_with = nullptr, long dot_stride = 0)
+           const TapCg* cg = nullptr)
 {
-    const double bytes = (double)c.nn * (2 * sizeof(Tio) + 2 + (dot_part ? sizeof(Tio) : 0));
+    const double bytes = (double)c.nn * (2 * sizeof(Tio) + (cg ? 2 * sizeof(Tio) + 1 : 2));
     ProfScope ps(c, kind_of<T>(KD_TAP_K), bytes * nrhs, st);
-    launch_tap<T, Tio>(c, SEP_PW_K, in, out, mask, mask, nullptr, nullptr, nrhs, dot_part, dot_with, dot_stride, st);
+    launch_tap<T, Tio>(c, cg ? kTapCg : SEP_PW_K, in, out, mask, mask, nullptr, nullptr, nrhs, st, cg);
 }
 
 // Whether a K-type product runs on the direct kernels.  They do at most half
@@ -730,8 +730,7 @@ bool tap_apply(Ctx& c, int op, const Tio* in, Tio* out, int nrhs, hipStream_t st
                     // only nodes that are not interior read their rows
                     ProfScope ps(c, kind_of<T>(KD_TAP_K),
                                  nn * (2 * rt + 2) + (double)c.ncls2 * (c.dim * c.s + 1) * rt * nrhs, st);
-                    launch_tap<T, Tio>(c, SEP_PW_KN, in, out, c.chi, c.chi, c.ba_64, c.vol64, nrhs, nullptr,
-                                       nullptr, 0, st);
+                    launch_tap<T, Tio>(c, SEP_PW_KN, in, out, c.chi, c.chi, c.ba_64, c.vol64, nrhs, st);
                     return true;
                 }
                 return false;
@@ -739,7 +738,7 @@ bool tap_apply(Ctx& c, int op, const Tio* in, Tio* out, int nrhs, hipStream_t st
             case FCRKPM_OP_VN: {
                 ProfScope ps(c, kind_of<T>(KD_TAP_UH), nn * (2 * rt + 1 + (c.s + (op == FCRKPM_OP_VN)) * rt), st);
                 launch_tap<T, Tio>(c, SEP_PW_UH, in, out, c.chi, nullptr, b0_of<T>(c),
-                                   op == FCRKPM_OP_VN ? vol_of<T>(c) : nullptr, nrhs, nullptr, nullptr, 0, st);
+                                   op == FCRKPM_OP_VN ? vol_of<T>(c) : nullptr, nrhs, st);
                 return true;
             }
             case FCRKPM_OP_FQ:
@@ -749,8 +748,7 @@ bool tap_apply(Ctx& c, int op, const Tio* in, Tio* out, int nrhs, hipStream_t st
             case FCRKPM_OP_NT: {
                 const T* w = op == FCRKPM_OP_FR ? vol_of<T>(c) : op == FCRKPM_OP_FQ ? area_of<T>(c) : nullptr;
                 ProfScope ps(c, kind_of<T>(KD_TAP_LOAD), nn * (2 * rt + 1 + (c.s + (w != nullptr)) * rt), st);
-                launch_tap<T, Tio>(c, SEP_PW_LOAD, in, out, nullptr, c.chi, b0_of<T>(c), w, nrhs, nullptr,
-                                   nullptr, 0, st);
+                launch_tap<T, Tio>(c, SEP_PW_LOAD, in, out, nullptr, c.chi, b0_of<T>(c), w, nrhs, st);
                 return true;
             }
             default: return false;
@@ -935,38 +933,46 @@ void dots(Ctx& c, const T* a, const T* b, int nrhs, int idx, hipStream_t st)
     launch_reduce_to(c.partial, c.nn, nrhs, c.scal + idx, st);
 }
 
-// the register-resident product can fold the CG direction update into its
-// first pass (FP32 vectors and products only), and the p.q partials into its
-// last pass where its workgroups fit the partial slots
+// a product that can fold the CG direction update in: the direct kernels where
+// vectors and products have one type, and the register path (FP32), whose first
+// pass applies it and whose last leaves the p.q partials
 template <typename T, typename TP>
 bool fused_cg(Ctx& c, int nrhs)
 {
-    if constexpr (std::is_same_v<T, float> && std::is_same_v<TP, float>)
-        return !tap_serves_k<T, T>(c) && use_reg_path(c, nrhs);
-    else
-        return false;
+    if constexpr (!std::is_same_v<T, TP>) return false;
+    else if (tap_serves_k<T, T>(c)) return true;
+    else return std::is_same_v<T, float> && use_reg_path(c, nrhs);
 }
 
 // one CG iteration for all active right-hand sides: vectors of type T, K
-// products in precision TP.  With `fused`, the product's first pass applies
-// the direction update left pending by the previous iteration (pend) and this
-// iteration leaves its own update pending unless `last`.
+// products in precision TP.  With `fused`, the product applies the direction
+// update left pending by the previous iteration (pend) and this iteration
+// leaves its own update pending unless `last`.  The direct kernels then write
+// the new direction to `p_new` (the old one lies in `p`) and the last update
+// of a block goes to `p_end`.
 template <typename T, typename TP = T>
 void cg_iteration(Ctx& c, T* x, T* r, T* p, T* q, int nrhs, int parity, hipStream_t st,
-                  bool fused = false, bool pend = false, bool last = true)
+                  bool fused = false, bool pend = false, bool last = true, T* p_new = nullptr,
+                  T* p_end = nullptr)
 {
     double* pq_part = c.partial;
     double* rr_part = c.partial + (size_t)kRedBlocks * c.cap_rhs;
     int npq = red_blocks(c.nn);
-    if (tap_serves_k<TP, T>(c)) {
+    bool direct = false;
+    if constexpr (std::is_same_v<T, TP>) direct = tap_serves_k<T, T>(c);
+    if (direct) {
         // the direct product leaves the p.q partials (in the wide slots, summed
         // to one, when they outnumber kRedBlocks)
-        const long nb = tap_dots(c, sizeof(TP));
-        const bool wide = nb > kRedBlocks;
-        tap_k<TP, T>(c, p, q, c.freem, nrhs, st, wide ? c.partial_wide : pq_part, p,
-                     wide ? wide_slots(c) : kRedBlocks);
-        npq = wide ? 1 : (int)nb;
-        if (wide) launch_reduce_wide(c.partial_wide, (int)nb, wide_slots(c), nrhs, pq_part, st);
+        if constexpr (std::is_same_v<T, TP>) {
+            const long nb = tap_dots(c, sizeof(T));
+            const bool wide = nb > kRedBlocks;
+            const TapCg cg{r, p_new, wide ? c.partial_wide : pq_part, wide ? wide_slots(c) : kRedBlocks, pend,
+                           rr_part, red_blocks(c.nn), c.scal, parity ^ 1, c.act};
+            tap_k<T, T>(c, p, q, c.freem, nrhs, st, &cg);
+            p = p_new;
+            npq = wide ? 1 : (int)nb;
+            if (wide) launch_reduce_wide(c.partial_wide, (int)nb, wide_slots(c), nrhs, pq_part, st);
+        }
     } else if constexpr (std::is_same_v<T, float> && std::is_same_v<TP, float>) {
         if (fused) {
             // the last pass of the product also leaves the p.q partials (in
@@ -1000,7 +1006,8 @@ void cg_iteration(Ctx& c, T* x, T* r, T* p, T* q, int nrhs, int parity, hipStrea
         launch_dot_partial<T>(p, q, c.nn, nrhs, pq_part, c.act, st);
     }
     launch_cg_xr<T>(x, r, p, q, c.nn, nrhs, pq_part, npq, c.scal, parity, rr_part, c.act, st);
-    if (!fused || last) launch_cg_p<T>(p, r, c.nn, nrhs, rr_part, c.scal, parity, c.act, st);
+    if (!fused || last)
+        launch_cg_p<T>(p_end ? p_end : p, p, r, c.nn, nrhs, rr_part, c.scal, parity, c.act, st);
 }
 
 constexpr int kCheck = 8;  // CG iterations per convergence poll (even: parity returns)
@@ -1149,6 +1156,8 @@ struct Solver {
             launch_to32(vec64(c, V_R), vec32(c, 1), nn * nrhs, st);
             HIPCHK(hipMemcpyAsync(vec32(c, 2), vec32(c, 1), sizeof(float) * nn * nrhs,
                                   hipMemcpyDeviceToDevice, st));
+            // the second array of directions: zero where the products do not write it
+            HIPCHK(hipMemsetAsync(vec32(c, 4), 0, sizeof(float) * nn * nrhs, st));
             dots<float>(c, vec32(c, 1), vec32(c, 1), nrhs, S_RR0, st);
         } else {
             HIPCHK(hipMemsetAsync(vec64(c, V_T), 0, sizeof(double) * nn * nrhs, st));
@@ -1172,6 +1181,7 @@ struct Solver {
         ph = PH_F64;
         HIPCHK(hipMemcpyAsync(vec64(c, V_P), vec64(c, V_R), sizeof(double) * nn * nrhs,
                               hipMemcpyDeviceToDevice, st));
+        HIPCHK(hipMemsetAsync(vec64(c, V_T), 0, sizeof(double) * nn * nrhs, st));  // second array of directions
         launch_set_scalar(c.scal, S_BREAK, 0.0, nrhs, st);
         dots<double>(c, vec64(c, V_R), vec64(c, V_R), nrhs, S_RR0, st);
         const double* h = read_scalars(c, nrhs, st);
@@ -1200,17 +1210,24 @@ struct Solver {
     void enqueue(int nb, hipStream_t st)
     {
         int par = parity;
-        const bool fused = ph == PH_REFINED && mode == FCRKPM_MODE_F32_REFINED &&
-                           fused_cg<float, float>(c, nrhs);
+        // within a block the direction update of iteration i runs in the product
+        // of iteration i+1; the block ends with it applied.  The direct product
+        // takes the direction from one array to another: it alternates between
+        // two and the block ends in the first.
+        if (ph == PH_F64) {
+            const bool fused = fused_cg<double, double>(c, nrhs);
+            double* v[2] = {vec64(c, V_P), vec64(c, fused ? V_T : V_P)};
+            for (int i = 0; i < nb; ++i, par ^= 1)
+                cg_iteration<double>(c, vec64(c, V_X), vec64(c, V_R), v[i & 1], vec64(c, V_Q), nrhs, par, st, fused,
+                                     fused && i > 0, i == nb - 1, v[~i & 1], v[0]);
+            return;
+        }
+        const bool fused = mode == FCRKPM_MODE_F32_REFINED && fused_cg<float, float>(c, nrhs);
+        float* v[2] = {vec32(c, 2), vec32(c, fused && tap_serves_k<float, float>(c) ? 4 : 2)};
         for (int i = 0; i < nb; ++i, par ^= 1) {
-            if (ph == PH_F64)
-                cg_iteration<double>(c, vec64(c, V_X), vec64(c, V_R), vec64(c, V_P), vec64(c, V_Q),
-                                     nrhs, par, st);
-            else if (mode == FCRKPM_MODE_F32_REFINED)
-                // within a block the direction update of iteration i runs in the
-                // first pass of iteration i+1; the block ends with it applied
-                cg_iteration<float, float>(c, vec32(c, 0), vec32(c, 1), vec32(c, 2), vec32(c, 3),
-                                           nrhs, par, st, fused, i > 0, i == nb - 1);
+            if (mode == FCRKPM_MODE_F32_REFINED)
+                cg_iteration<float, float>(c, vec32(c, 0), vec32(c, 1), v[i & 1], vec32(c, 3), nrhs, par, st, fused,
+                                           i > 0, i == nb - 1, v[~i & 1], v[0]);
             else
                 cg_iteration<double, float>(c, vec64(c, V_T), vec64(c, V_R), vec64(c, V_P),
                                             vec64(c, V_Q), nrhs, par, st);
@@ -2660,8 +2677,7 @@ namespace {
 void apply_grad(Ctx& c, const double* x, double* out, hipStream_t st)
 {
     if (tap_active(c)) {
-        launch_tap<double, double>(c, kTapGrad, x, out, c.chi, nullptr, c.ba_64, nullptr, 1, nullptr, nullptr, 0,
-                                   st);
+        launch_tap<double, double>(c, kTapGrad, x, out, c.chi, nullptr, c.ba_64, nullptr, 1, st);
         return;
     }
     if (use_reg_path64(c) && reg_kn_ok(c, st)) {

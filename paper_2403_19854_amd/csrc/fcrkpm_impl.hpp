@@ -307,7 +307,21 @@ void launch_reg_k(const Ctx& c, const float* in, float* out, const uint8_t* mask
 // coefficient rows in use; tap_active tells whether the current product can
 // run on them; tap_dots is the number of dot partials per right-hand side (the
 // same for a batch as for one), at most tap_dot_slots.
-constexpr int kTapGrad = 4;  // launch_tap's mode of the implicit gradient; the others are SEP_PW_*
+// launch_tap's modes beyond SEP_PW_*: the implicit gradient, and K with the
+// direction update of CG and the partials of p . K p
+constexpr int kTapGrad = 4, kTapCg = 5;
+struct TapCg {
+    const void* r;
+    void* pnew;              // the new p (the old one is the input)
+    double* dot_part;
+    long dot_stride;
+    bool pend;               // an update is pending: beta from the nrr partials rr_part
+    const double* rr_part;
+    int nrr;
+    double* scal;
+    int parity;
+    const int* act;
+};
 void tap_setup(Ctx& c, const double (*taps)[5][4], hipStream_t st);
 void tap_build(Ctx& c, hipStream_t st);
 bool tap_active(const Ctx& c);
@@ -317,8 +331,8 @@ void tap_release(Ctx& c);
 void tap_release_set(void*& s);
 template <typename T, typename Tio>
 void launch_tap(const Ctx& c, int mode, const Tio* in, Tio* out, const uint8_t* mask_in,
-                const uint8_t* mask_out, const T* rows, const T* vol, int nrhs, double* dot_part,
-                const void* dot_with, long dot_stride, hipStream_t st);
+                const uint8_t* mask_out, const T* rows, const T* vol, int nrhs, hipStream_t st,
+                const TapCg* cg = nullptr);
 
 // throws the library's FCRKPM_ERR_UNSUPPORTED status with this message
 [[noreturn]] void raise_unsupported(const char* msg);
@@ -376,7 +390,7 @@ void launch_cg_xr(T* x, T* r, const T* p, const T* q, long n, int nrhs, const do
                   int npq, double* scal, int parity, double* rr_part, const int* act,
                   hipStream_t st);
 template <typename T>
-void launch_cg_p(T* p, const T* r, long n, int nrhs, const double* rr_part, double* scal,
+void launch_cg_p(T* p, const T* p_old, const T* r, long n, int nrhs, const double* rr_part, double* scal,
                  int parity, const int* act, hipStream_t st);
 void launch_set_scalar(double* scal, int idx, double v, int nrhs, hipStream_t st);
 void launch_set_flag(int* act, int j, int v, hipStream_t st);

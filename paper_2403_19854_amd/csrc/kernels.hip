@@ -541,7 +541,7 @@ void launch_cg_xr(T* x, T* r, const T* p, const T* q, long n, int nrhs, const do
 }
 
 template <typename T>
-__global__ __launch_bounds__(kRedThreads) void k_cg_p(T* __restrict__ p, const T* __restrict__ r,
+__global__ __launch_bounds__(kRedThreads) void k_cg_p(T* p, const T* p_old, const T* __restrict__ r,
                                                       long n, const double* __restrict__ rr_part,
                                                       double* scal, int parity,
                                                       const int* __restrict__ act)
@@ -550,6 +550,7 @@ __global__ __launch_bounds__(kRedThreads) void k_cg_p(T* __restrict__ p, const T
     const int j = blockIdx.y;
     if (!act[j]) return;
     p += j * n;
+    p_old += j * n;
     r += j * n;
     scal += j * kScal;
     const long stride = (long)gridDim.x * blockDim.x;
@@ -563,7 +564,7 @@ __global__ __launch_bounds__(kRedThreads) void k_cg_p(T* __restrict__ p, const T
             const long i = 4 * (first + u * stride);
             if (i < n) {
                 rs[u] = ld4(r + i);
-                ps[u] = ld4(p + i);
+                ps[u] = ld4(p_old + i);
             }
         }
     }
@@ -583,22 +584,22 @@ __global__ __launch_bounds__(kRedThreads) void k_cg_p(T* __restrict__ p, const T
         }
         for (long i = 4 * (first + kPre * stride); i < n; i += 4 * stride) {
             const Vec4<T> rv = ld4(r + i);
-            Vec4<T> pv = ld4(p + i);
+            Vec4<T> pv = ld4(p_old + i);
 #pragma unroll
             for (int u = 0; u < 4; ++u) pv.v[u] = rv.v[u] + beta * pv.v[u];
             st4(p + i, pv);
         }
     } else {
-        for (long i = first; i < n; i += stride) p[i] = r[i] + beta * p[i];
+        for (long i = first; i < n; i += stride) p[i] = r[i] + beta * p_old[i];
     }
     if (blockIdx.x == 0 && threadIdx.x == 0) scal[1 - parity] = rr_new;
 }
 
 template <typename T>
-void launch_cg_p(T* p, const T* r, long n, int nrhs, const double* rr_part, double* scal,
+void launch_cg_p(T* p, const T* p_old, const T* r, long n, int nrhs, const double* rr_part, double* scal,
                  int parity, const int* act, hipStream_t st)
 {
-    hipLaunchKernelGGL((k_cg_p<T>), dim3(red_blocks(n), nrhs), dim3(kRedThreads), 0, st, p, r, n,
+    hipLaunchKernelGGL((k_cg_p<T>), dim3(red_blocks(n), nrhs), dim3(kRedThreads), 0, st, p, p_old, r, n,
                        rr_part, scal, parity, act);
 }
 
@@ -612,9 +613,9 @@ template void launch_cg_xr<double>(double*, double*, const double*, const double
 template void launch_cg_xr<float>(float*, float*, const float*, const float*, long, int,
                                   const double*, int, double*, int, double*, const int*,
                                   hipStream_t);
-template void launch_cg_p<double>(double*, const double*, long, int, const double*, double*, int,
+template void launch_cg_p<double>(double*, const double*, const double*, long, int, const double*, double*, int,
                                   const int*, hipStream_t);
-template void launch_cg_p<float>(float*, const float*, long, int, const double*, double*, int,
+template void launch_cg_p<float>(float*, const float*, const float*, long, int, const double*, double*, int,
                                  const int*, hipStream_t);
 
 // scal[j*kScal + idx] = v for every right-hand side

@@ -17,11 +17,11 @@
     FC_TAP_QUAD(X, T, U, 1, MODE, R1) FC_TAP_QUAD(X, T, U, 2, MODE, R2) FC_TAP_QUAD(X, T, U, 3, MODE, R3)       \
     FC_TAP_CUB(X, T, U, 1, MODE, R1) FC_TAP_CUB(X, T, U, 2, MODE, R2)
 // K's rows, then the mass's and the shifted operator's of the higher bases
-#define FC_TAP_KS(X, T, U)                                                                                     \
-    FC_TAP_ALL(X, T, U, TAP_K, 1, 2, 3)                                                                        \
-    FC_TAP_QUAD(X, T, U, 2, TAP_K, 1) FC_TAP_QUAD(X, T, U, 3, TAP_K, 1) FC_TAP_CUB(X, T, U, 2, TAP_K, 1)       \
-    FC_TAP_QUAD(X, T, U, 1, TAP_K, 2) FC_TAP_QUAD(X, T, U, 2, TAP_K, 3) FC_TAP_QUAD(X, T, U, 3, TAP_K, 4)      \
-    FC_TAP_CUB(X, T, U, 1, TAP_K, 2) FC_TAP_CUB(X, T, U, 2, TAP_K, 3)
+#define FC_TAP_KS(X, T, U, MODE)                                                                               \
+    FC_TAP_ALL(X, T, U, MODE, 1, 2, 3)                                                                         \
+    FC_TAP_QUAD(X, T, U, 2, MODE, 1) FC_TAP_QUAD(X, T, U, 3, MODE, 1) FC_TAP_CUB(X, T, U, 2, MODE, 1)          \
+    FC_TAP_QUAD(X, T, U, 1, MODE, 2) FC_TAP_QUAD(X, T, U, 2, MODE, 3) FC_TAP_QUAD(X, T, U, 3, MODE, 4)         \
+    FC_TAP_CUB(X, T, U, 1, MODE, 2) FC_TAP_CUB(X, T, U, 2, MODE, 3)
 #define FC_TAP_NODE(X, T, U) FC_TAP_ALL(X, T, U, TAP_UH, 1, 1, 1) FC_TAP_ALL(X, T, U, TAP_LOAD, 1, 1, 1)
 // the gradient force and the implicit gradient run in FP64 (in 1D the gradient
 // has the one row of u^h)
@@ -30,10 +30,13 @@
     FC_TAP_LIN(X, T, U, 2, TAP_UH, 2) FC_TAP_QUAD(X, T, U, 2, TAP_UH, 2) FC_TAP_CUB(X, T, U, 2, TAP_UH, 2)     \
     FC_TAP_LIN(X, T, U, 3, TAP_UH, 3) FC_TAP_QUAD(X, T, U, 3, TAP_UH, 3)
 
-#define FC_TAP_F32(X) FC_TAP_KS(X, float, float) FC_TAP_NODE(X, float, float)
-#define FC_TAP_F64(X) FC_TAP_KS(X, double, double)
+// one list per translation unit
+#define FC_TAP_F32(X) FC_TAP_KS(X, float, float, TAP_K) FC_TAP_NODE(X, float, float)
+#define FC_TAP_F64(X) FC_TAP_KS(X, double, double, TAP_K)
 #define FC_TAP_F64N(X) FC_TAP_NODE(X, double, double) FC_TAP_GRADS(X, double, double)
-#define FC_TAP_MIX(X) FC_TAP_KS(X, float, double)
+#define FC_TAP_MIX(X) FC_TAP_KS(X, float, double, TAP_K)
+#define FC_TAP_CG32(X) FC_TAP_KS(X, float, float, TAP_CG)
+#define FC_TAP_CG64(X) FC_TAP_KS(X, double, double, TAP_CG)
 
 #define FC_TAP_EXTERN(T, U, DIM, DEG, R, MODE, ROWS) \
     extern template void tap_go<T, U, TapBasis<DIM, DEG>, R, MODE, ROWS>(const TapArgs<T>&, dim3, bool, hipStream_t);
@@ -45,4 +48,6 @@ FC_TAP_F32(FC_TAP_EXTERN)
 FC_TAP_F64(FC_TAP_EXTERN)
 FC_TAP_F64N(FC_TAP_EXTERN)
 FC_TAP_MIX(FC_TAP_EXTERN)
+FC_TAP_CG32(FC_TAP_EXTERN)
+FC_TAP_CG64(FC_TAP_EXTERN)
 }  // namespace fcrkpm

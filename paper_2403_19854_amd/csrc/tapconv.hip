@@ -197,27 +197,24 @@ TapCut tap_cut_tile(const Ctx& c, bool small, int nrhs, int elem, int unit)
     return best;
 }
 
-TapCut tap_cut_one(const Ctx& c, int elem)
+// the cheaper tile
+TapCut tap_cut_best(const Ctx& c, int nrhs, int elem)
 {
-    const TapCut a = tap_cut_tile(c, false, 1, elem, 1);
-    if (c.dim < 3) return a;
-    const TapCut b = tap_cut_tile(c, true, 1, elem, 1);
-    return b.cost < a.cost ? b : a;
-}
-
-// The cut of a K product over nrhs right-hand sides.  With dots it is a
-// multiple of one right-hand side's, so that a batch adds up the same partials
-// as single products.
-TapCut tap_cut(const Ctx& c, int mode, int nrhs, int elem, bool dots)
-{
-    if (mode != TAP_K) return tap_cut_tile(c, false, nrhs, elem, 1);
-    const TapCut one = tap_cut_one(c, elem);
-    if (nrhs == 1) return one;
-    if (dots) return tap_cut_tile(c, one.small, nrhs, elem, one.cz);
     const TapCut a = tap_cut_tile(c, false, nrhs, elem, 1);
     if (c.dim < 3) return a;
     const TapCut b = tap_cut_tile(c, true, nrhs, elem, 1);
     return b.cost < a.cost ? b : a;
+}
+
+// The cut of a launch over nrhs right-hand sides.  In CG it is a multiple of
+// one right-hand side's, so that a batch adds up the same dot partials as
+// single products.
+TapCut tap_cut(const Ctx& c, int mode, int nrhs, int elem)
+{
+    if (mode == TAP_K) return tap_cut_best(c, nrhs, elem);
+    if (mode != TAP_CG) return tap_cut_tile(c, false, nrhs, elem, 1);
+    const TapCut one = tap_cut_best(c, 1, elem);
+    return nrhs == 1 ? one : tap_cut_tile(c, one.small, nrhs, elem, one.cz);
 }
 
 }  // namespace
@@ -229,7 +226,7 @@ bool tap_active(const Ctx& c) { return c.use_taps && !c.fft_pins && c.tap; }
 
 long tap_dots(const Ctx& c, int elem)
 {
-    const TapCut u = tap_cut_one(c, elem);
+    const TapCut u = tap_cut_best(c, 1, elem);
     return (long)c.tap_nt[u.small][0] * c.tap_nt[u.small][1] * ((c.n[2] + u.cz - 1) / u.cz);
 }
 
@@ -276,10 +273,6 @@ void tap_build(Ctx& c, hipStream_t st)
     c.tap = s;
     const bool mf = c.degree == 1;
     const int nv = tap_rec_values(mf, c.s, c.krows);
-    if (nv > kTapMint) {
-        tap_release_set(c.tap);
-        return;
-    }
     const int rp32 = tap_rec_pitch(mf, c.s, c.krows, 4), rp64 = tap_rec_pitch(mf, c.s, c.krows, 8);
     if (c.cls && c.nconst.bmax >= 0.0) {
         const NodeConst& nc = c.nconst;
@@ -319,8 +312,9 @@ void tap_build(Ctx& c, hipStream_t st)
     s->rec64 = tap_alloc<double>((size_t)n * rp64);
     std::vector<float> h32((size_t)2 * rp32, 0.0f);
     std::vector<double> h64((size_t)2 * rp64, 0.0);
-    std::copy(s->m32, s->m32 + nv, h32.begin() + rp32);
-    std::copy(s->m64, s->m64 + nv, h64.begin() + rp64);
+    const int ni = std::min(nv, kTapMint);  // wider records have no interior class
+    std::copy(s->m32, s->m32 + ni, h32.begin() + rp32);
+    std::copy(s->m64, s->m64 + ni, h64.begin() + rp64);
     tap_check(hipMemcpyAsync(s->rec32, h32.data(), h32.size() * sizeof(float), hipMemcpyHostToDevice, st));
     tap_check(hipMemcpyAsync(s->rec64, h64.data(), h64.size() * sizeof(double), hipMemcpyHostToDevice, st));
     const unsigned long long first = 2;
@@ -334,8 +328,7 @@ void tap_build(Ctx& c, hipStream_t st)
 
 template <typename T, typename Tio>
 void launch_tap(const Ctx& c, int mode, const Tio* in, Tio* out, const uint8_t* mask_in,
-                const uint8_t* mask_out, const T* rows_in, const T* vol, int nrhs, double* dot_part, const void* dot_with,
-                long dot_stride, hipStream_t st)
+                const uint8_t* mask_out, const T* rows_in, const T* vol, int nrhs, hipStream_t st, const TapCg* cg)
 {
     const TapSet& s = *(const TapSet*)c.tap;
     TapArgs<T> a = {};
@@ -348,10 +341,10 @@ void launch_tap(const Ctx& c, int mode, const Tio* in, Tio* out, const uint8_t* 
         for (int e = 0; e < kTapE; ++e)
             for (int o = 0; o <= kTapR; ++o) a.t[k][e][o] = (T)c.tap_t[k][e][o];
     }
-    const TapCut cut = tap_cut(c, mode, nrhs, sizeof(T), dot_part != nullptr);
+    const TapCut cut = tap_cut(c, mode, nrhs, sizeof(T));
     a.ntx = c.tap_nt[cut.small][0];
     a.nty = c.tap_nt[cut.small][1];
-    a.cu = dot_part ? tap_cut_one(c, sizeof(T)).cz : cut.cz;
+    a.cu = cg ? tap_cut_best(c, 1, sizeof(T)).cz : cut.cz;
     a.cz = cut.cz;
     a.zr = c.tap_zr[cut.small];
     a.words = s.words;
@@ -365,16 +358,25 @@ void launch_tap(const Ctx& c, int mode, const Tio* in, Tio* out, const uint8_t* 
         memcpy(a.mint, s.m32, sizeof(a.mint));
     }
     a.rows = rows_in;
+    if (cg) {
+        a.r = cg->r;
+        a.pnew = cg->pnew;
+        a.dot_part = cg->dot_part;
+        a.dot_stride = cg->dot_stride;
+        a.pend = cg->pend;
+        a.rr_part = cg->rr_part;
+        a.nrr = cg->nrr;
+        a.parity = cg->parity;
+        a.scal = cg->scal;
+        a.act = cg->act;
+    }
     a.vol = vol;
     a.kappa = (T)c.pw_kappa;
-    a.dot_part = dot_part;
-    a.dot_with = dot_with;
-    a.dot_stride = dot_stride;
     a.nn = c.nn;
     a.rb = c.nn * (long)sizeof(Tio) * (mode == TAP_GRAD ? c.dim : 1);
     const dim3 grid((unsigned)((long)a.ntx * a.nty * ((c.n[2] + a.cz - 1) / a.cz)), (unsigned)nrhs);
     // the linear bases keep M, whatever the rows it was made of
-    const int rows = mode == TAP_K ? (c.degree > 1 ? c.krows : c.dim) : mode == TAP_KN || mode == TAP_GRAD ? c.dim : 1;
+    const int rows = mode == TAP_K || mode == TAP_CG ? (c.degree > 1 ? c.krows : c.dim) : mode == TAP_KN || mode == TAP_GRAD ? c.dim : 1;
     const int kmode = mode == TAP_GRAD ? TAP_UH : mode;
     bool done = false;
 #define FC_TAP_CASE(T_, TIO_, DIM, DEG, R, MODE, ROWS)                                              \
@@ -385,8 +387,10 @@ void launch_tap(const Ctx& c, int mode, const Tio* in, Tio* out, const uint8_t* 
     if constexpr (sizeof(T) == 8) {
         FC_TAP_F64(FC_TAP_CASE)
         FC_TAP_F64N(FC_TAP_CASE)
+        FC_TAP_CG64(FC_TAP_CASE)
     } else if constexpr (sizeof(Tio) == 4) {
         FC_TAP_F32(FC_TAP_CASE)
+        FC_TAP_CG32(FC_TAP_CASE)
     } else {
         FC_TAP_MIX(FC_TAP_CASE)
     }
@@ -395,12 +399,12 @@ void launch_tap(const Ctx& c, int mode, const Tio* in, Tio* out, const uint8_t* 
 }
 
 template void launch_tap<float, float>(const Ctx&, int, const float*, float*, const uint8_t*, const uint8_t*,
-                                       const float*, const float*, int, double*, const void*, long, hipStream_t);
+                                       const float*, const float*, int, hipStream_t, const TapCg*);
 template void launch_tap<double, double>(const Ctx&, int, const double*, double*, const uint8_t*,
-                                         const uint8_t*, const double*, const double*, int, double*, const void*, long,
-                                         hipStream_t);
+                                         const uint8_t*, const double*, const double*, int, hipStream_t,
+                                         const TapCg*);
 template void launch_tap<float, double>(const Ctx&, int, const double*, double*, const uint8_t*,
-                                        const uint8_t*, const float*, const float*, int, double*, const void*, long,
-                                        hipStream_t);
+                                        const uint8_t*, const float*, const float*, int, hipStream_t,
+                                        const TapCg*);
 
 }  // namespace fcrkpm

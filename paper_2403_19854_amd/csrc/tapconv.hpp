@@ -36,11 +36,11 @@ namespace fcrkpm {
 
 constexpr int kTapR = 3;          // largest tap radius
 constexpr int kTapE = 5;          // exponents 0..4 (moments of the quadratic basis)
-constexpr int kTapMint = 41;      // interior constants: rows (dim + 1) * s of the quadratic basis, and V
+constexpr int kTapMint = kMaxNodeConst + 1;  // interior record: rows and V (wider row sets have no interior class)
 
 // K products; u^h; the loads f^r, f^q and N^T y; the gradient force.  TAP_GRAD
 // is u^h with the rows b^a (one field, its dim components nn apart).
-enum { TAP_K = SEP_PW_K, TAP_UH = SEP_PW_UH, TAP_LOAD = SEP_PW_LOAD, TAP_KN = SEP_PW_KN, TAP_GRAD = kTapGrad };
+enum { TAP_K = SEP_PW_K, TAP_UH = SEP_PW_UH, TAP_LOAD = SEP_PW_LOAD, TAP_KN = SEP_PW_KN, TAP_GRAD = kTapGrad, TAP_CG = kTapCg };
 
 // Monomials of degree <= DEG in DIM variables (the library's basis order), as
 // the tree the passes walk: fields after z (exponent ez), after y (ey, ez),
@@ -106,9 +106,17 @@ struct TapArgs {
     const T* rows;             // UH, LOAD: b^0 [s][nn] (UH also b^a, [dim][s][nn]); KN: b^a
     const T* vol;              // UH, LOAD: weight [nn] or NULL; KN: V [nn]
     T kappa;                   // KN
-    double* dot_part;          // partials of out . dot_with per tile and cu planes, or NULL
-    const void* dot_with;
-    long dot_stride;           // partial slots between right-hand sides
+    // TAP_CG: K p after the pending update p = r + beta p of CG (pend = 0: none),
+    // with the partials of p . K p; in holds the old p, pnew takes the new one
+    // (another array, as neighbours still read the old)
+    const void* r;
+    void* pnew;
+    double* dot_part;          // partials of p . K p per tile and cu planes
+    long dot_stride;           // their slots between right-hand sides
+    const double* rr_part;     // partials of the new r.r, nrr of them
+    int pend, nrr, parity;           // scal[parity] = old r.r; scal[1 - parity] takes the new
+    double* scal;
+    const int* act;            // right-hand sides still iterating
     long nn;
     long rb;                   // bytes between right-hand sides of in and out
 };
@@ -238,6 +246,16 @@ struct TapRoles {
     static constexpr int N2 = SPLIT ? NT / 2 : NT, N4 = SPLIT ? NT - N2 : NT;
 };
 
+// What TAP_CG adds to a march.
+template <typename T, typename Tio>
+struct TapUpdate {
+    const Tio* r = nullptr;
+    Tio* pnew = nullptr;
+    T alpha = T(0), beta = T(0);  // p = alpha r + beta p
+    double* dpart = nullptr;
+    double* dsum = nullptr;       // LDS, a slot per wave
+};
+
 // One workgroup's march; ROLE bit 0: D and E, bit 1: the reflections along y and z.
 template <typename T, typename Tio, class B, int R, int MODE, int ROWS, int TX, int TY, int NT, int ROLE>
 struct TapMarch {
@@ -247,7 +265,7 @@ struct TapMarch {
     static constexpr int S = B::S, NZ = B::NZ, NY = B::NY;
     static constexpr int RY = G::RY, RZ = G::RZ, HX = G::HX, HY = G::HY, HZ = G::HZ;
     static constexpr int XE = G::XE, YE = G::YE, XL = G::XL, YL = G::YL;
-    static constexpr bool KMODE = MODE == TAP_K || MODE == TAP_KN;
+    static constexpr bool CG = MODE == TAP_CG, KMODE = MODE == TAP_K || MODE == TAP_KN || CG;
     static constexpr int NC = G::P1 ? (XL * YL + NT - 1) / NT : 1;          // input columns per thread
     static constexpr int NB2 = YE % 4 == 0 ? 4 : YE % 2 == 0 ? 2 : 1;       // rows per item, y convolution
     static constexpr int XB4 = 4;                                           // nodes per item, x reflection
@@ -257,6 +275,7 @@ struct TapMarch {
     static_assert((!G::P2 || (N5 <= RO::NB && N5 % 64 == 0)) && XE % 2 == 0 && TX % XB4 == 0);
     static constexpr bool MF = tap_mform<B, MODE>();
     static constexpr int RP = tap_rec_pitch(MF, S, ROWS, sizeof(T));
+    static constexpr bool ICONST = ROWS * S <= kMaxNodeConst;  // wider row sets have no classes
     static constexpr bool A = (ROLE & 1) != 0, Bq = (ROLE & 2) != 0 && G::P2;
 
     // x convolutions of two nodes: D[i][q] from the y-level fields
@@ -332,9 +351,8 @@ struct TapMarch {
         return c == 2 ? (w >> 4) + ((i && (w & 3) == 2) ? 1u : 0u) : c;
     }
 
-    static __device__ __forceinline__ void run(KP kp, T* smem, double* dsum, const Tio* in, Tio* out,
-                                               const Tio* dwith, double* dpart, int tile, int ntiles, int x0, int y0,
-                                               int zlo, int zhi)
+    static __device__ __forceinline__ void run(KP kp, T* smem, const Tio* in, Tio* out, int tile, int ntiles,
+                                               int x0, int y0, int zlo, int zhi, const TapUpdate<T, Tio>& up)
     {
         T* const sZ = smem;
         T* const sY = sZ + G::NSZ;
@@ -345,17 +363,28 @@ struct TapMarch {
         const uint8_t* const mask_in = kp->mask_in;
         const uint8_t* const mask_out = kp->mask_out;
         double dacc = 0.0;
-        bool flush = false;                        // the wave sums of a partial wait in dsum
-        int left = kp->cu - zlo % kp->cu;          // planes up to the partial's end
-        if (dpart) dpart += (long)(zlo / kp->cu) * ntiles + tile;
+        bool flush = false;  // the wave sums of a partial wait in up.dsum
+        int left = 0;        // planes up to the partial's end
+        double* dpart = nullptr;
+        if constexpr (CG) {
+            left = kp->cu - zlo % kp->cu;
+            dpart = up.dpart + (long)(zlo / kp->cu) * ntiles + tile;
+        }
 
         // input columns of this thread
         uint32_t col[NC];
+        bool own[NC];
         if constexpr (G::P1) {
 #pragma unroll
             for (int k = 0; k < NC; ++k) {
                 const int c = min(tid + k * NT, XL * YL - 1);
                 col[k] = (uint32_t)(tap_wrap(y0 - HY - RY + c / XL, ny) * nx + tap_wrap(x0 - HX - R + c % XL, nx));
+                if constexpr (CG) {
+                    // columns of this tile: their new p is stored
+                    const int lx = c % XL - HX - R, ly = c / XL - HY - RY;
+                    own[k] = lx >= 0 && lx < TX && x0 + lx < nx && ly >= 0 && ly < TY && y0 + ly < ny &&
+                             tid + k * NT < XL * YL;
+                }
             }
         }
         // E-level items: two nodes along x; word offset in a plane (K, KN) and
@@ -367,7 +396,7 @@ struct TapMarch {
                 const int it = min(tid + k * RO::NA, N3 - 1);
                 const int gi = it % (XE / 2), gy = tap_wrap(y0 - HY + it / (XE / 2), ny);
                 if constexpr (KMODE) wt3[k] = (uint32_t)(gy * gx + x0 / 2 + gi);
-                if constexpr (MODE != TAP_K) {
+                if constexpr (MODE != TAP_K && !CG) {
                     it3[k] = (uint32_t)(gy * nx + tap_wrap(x0 - HX + 2 * gi, nx));
                     jt3[k] = (uint32_t)(gy * nx + tap_wrap(x0 - HX + 2 * gi + 1, nx));
                 }
@@ -397,19 +426,29 @@ struct TapMarch {
         // once; from then on values are loaded a step ahead and masked when they
         // are used
         T zin[NC][2 * RZ + 1];
+        // (CG vectors are zero off the free nodes: r comes in place of the mask)
         Tio nxt[NC];
-        uint8_t nmk[NC];
+        std::conditional_t<CG, Tio, uint8_t> nmk[NC];
+        const auto value = [&](int k) -> T {
+            if constexpr (CG) return up.alpha * T(nmk[k]) + up.beta * T(nxt[k]);
+            else return nmk[k] ? T(nxt[k]) : T(0);
+        };
+        const auto fetch = [&](int z) {
+            const Tio* pi = in + (long)z * nxy;
+#pragma unroll
+            for (int k = 0; k < NC; ++k) {
+                nxt[k] = pi[col[k]];
+                if constexpr (CG) nmk[k] = (up.r + (long)z * nxy)[col[k]];
+                else nmk[k] = (mask_in + (long)z * nxy)[col[k]];
+            }
+        };
         if constexpr (G::P1) {
 #pragma unroll
             for (int j = 0; j <= 2 * RZ; ++j) {
-                const Tio* pi = in + (long)pin * nxy;
-                const uint8_t* pm = mask_in + (long)pin * nxy;
+                fetch(pin);
 #pragma unroll
-                for (int k = 0; k < NC; ++k) {
-                    nxt[k] = pi[col[k]];
-                    nmk[k] = pm[col[k]];
-                    if (j < 2 * RZ) zin[k][j + 1] = nmk[k] ? T(nxt[k]) : T(0);
-                }
+                for (int k = 0; k < NC; ++k)
+                    if (j < 2 * RZ) zin[k][j + 1] = value(k);
                 if (j < 2 * RZ) pin = (pin + 1 == nz) ? 0 : pin + 1;
             }
         }
@@ -427,16 +466,19 @@ struct TapMarch {
                     const KP k_ = tap_fresh<(S <= 4)>(kp);
                     T cur[NC];
 #pragma unroll
-                    for (int k = 0; k < NC; ++k) cur[k] = nmk[k] ? T(nxt[k]) : T(0);
+                    for (int k = 0; k < NC; ++k) cur[k] = value(k);
+                    if constexpr (CG) {
+                        // the planes of the chunk itself
+                        if (s < zhi - zlo + 2 * RZ) {
+                            Tio* po = up.pnew + (long)pin * nxy;
+#pragma unroll
+                            for (int k = 0; k < NC; ++k)
+                                if (own[k]) po[col[k]] = Tio(cur[k]);
+                        }
+                    }
                     if (s + 1 < nE + 2 * RZ) {
                         pin = (pin + 1 == nz) ? 0 : pin + 1;
-                        const Tio* pi = in + (long)pin * nxy;
-                        const uint8_t* pm = mask_in + (long)pin * nxy;
-#pragma unroll
-                        for (int k = 0; k < NC; ++k) {
-                            nxt[k] = pi[col[k]];
-                            nmk[k] = pm[col[k]];
-                        }
+                        fetch(pin);
                     }
 #pragma unroll
                     for (int k = 0; k < NC; ++k) {
@@ -496,10 +538,11 @@ struct TapMarch {
 #pragma unroll
                                         for (int p = 0; p < S; ++p) E[i][p] = (b + p * k_->nn)[g] * x;
                                     }
-                                } else if (__all((word[k] & 15) == 5)) {
+                                } else if (ICONST && __all((word[k] & 15) == 5)) {
                                     // interior nodes throughout the wave: the shared record
 #pragma unroll
-                                    for (int i = 0; i < 2; ++i) point(k_->mint, k_, D[i], E[i]);
+                                    for (int i = 0; i < 2; ++i)
+                                        if constexpr (ICONST) point(k_->mint, k_, D[i], E[i]);
                                 } else if constexpr (MODE == TAP_KN) {
                                     // rows and V from the node arrays (zero outside the domain)
                                     const T* b = k_->rows + (long)pe * nxy;
@@ -567,15 +610,22 @@ struct TapMarch {
                             if (ok5[k]) {
                                 const Tio v = mk5[k] ? Tio(zout[k][0]) : Tio(0);
                                 (out + zo)[o5 + (uint32_t)(k * nx)] = v;
-                                if (dwith) dacc += (double)v * (double)(dwith + zo)[o5 + (uint32_t)(k * nx)];
+                                if constexpr (CG) {
+                                    // the new p here (asked for a step ahead it cost the third
+                                    // workgroup of a CU its registers: 256^3 FP32 359 us an
+                                    // iteration against 283)
+                                    const uint32_t g = o5 + (uint32_t)(k * nx);
+                                    const T pv = up.alpha * T((up.r + zo)[g]) + up.beta * T((in + zo)[g]);
+                                    dacc += (double)v * (double)pv;
+                                }
                             }
                         }
-                        if (dwith) {
+                        if constexpr (CG) {
                             if (--left == 0 || z + 1 == zhi) {
                                 // the partial of these planes is complete
 #pragma unroll
                                 for (int o = 32; o > 0; o >>= 1) dacc += __shfl_xor(dacc, o, 64);
-                                if ((tid & 63) == 0) dsum[i5 >> 6] = dacc;
+                                if ((tid & 63) == 0) up.dsum[i5 >> 6] = dacc;
                                 dacc = 0.0;
                                 left = kp->cu;
                                 flush = true;
@@ -596,11 +646,11 @@ struct TapMarch {
                 }
             }
             if constexpr (Bq) {
-                if (flush) {
+                if (CG && flush) {
                     if (i5 == 0) {
                         double r = 0.0;
 #pragma unroll
-                        for (int w = 0; w < N5 / 64; ++w) r += dsum[w];
+                        for (int w = 0; w < N5 / 64; ++w) r += up.dsum[w];
                         *dpart = r;
                     }
                     dpart += ntiles;
@@ -686,8 +736,33 @@ __global__ __launch_bounds__(NT, tap_min_waves(sizeof(T), tap_lds_of<B, R, MODE,
     const long rj = (long)blockIdx.y * kp->rb;
     const Tio* const in = reinterpret_cast<const Tio*>((const char*)kp->in + rj);
     Tio* const out = reinterpret_cast<Tio*>((char*)kp->out + rj);
-    double* const dpart = kp->dot_part ? kp->dot_part + (long)blockIdx.y * kp->dot_stride : nullptr;
-    const Tio* const dwith = dpart ? reinterpret_cast<const Tio*>((const char*)kp->dot_with + rj) : nullptr;
+    TapUpdate<T, Tio> up;
+    if constexpr (MODE == TAP_CG) {
+        if (!kp->act[blockIdx.y]) return;
+        __shared__ double sh[2][NT / 64];
+        up.dsum = sh[1];
+        up.r = reinterpret_cast<const Tio*>((const char*)kp->r + rj);
+        up.pnew = reinterpret_cast<Tio*>((char*)kp->pnew + rj);
+        up.dpart = kp->dot_part + (long)blockIdx.y * kp->dot_stride;
+        up.beta = T(1);
+        if (kp->pend) {
+            // beta from the partials of r.r, as the stand-alone update forms it
+            const double* part = kp->rr_part + (long)blockIdx.y * kRedBlocks;
+            double* scal = kp->scal + (long)blockIdx.y * kScal;
+            double v = 0.0;
+            for (int i = tid; i < kp->nrr; i += NT) v += part[i];
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+            if ((tid & 63) == 0) sh[0][tid >> 6] = v;
+            __syncthreads();
+            double rr = 0.0;
+            for (int i = 0; i < NT / 64; ++i) rr += sh[0][i];
+            const double old = scal[kp->parity];
+            up.alpha = T(1);
+            up.beta = old > 0.0 ? T(rr / old) : T(0);
+            if (blockIdx.x == 0 && tid == 0) scal[1 - kp->parity] = rr;
+        }
+    }
     int b = (int)tap_xcd(blockIdx.x, gridDim.x);
     const int tx = b % ntx;
     b /= ntx;
@@ -708,18 +783,17 @@ __global__ __launch_bounds__(NT, tap_min_waves(sizeof(T), tap_lds_of<B, R, MODE,
         }
     }
     const int ntiles = ntx * nty, tile = ty * ntx + tx;
-    if constexpr (G::P2) {
-        if (dpart && tid == 0)
+    if constexpr (MODE == TAP_CG) {
+        if (tid == 0)
             for (int u = za / kp->cu; u * kp->cu < ze; ++u)
-                if (zlo >= zhi || (u + 1) * kp->cu <= zlo || u * kp->cu >= zhi) dpart[(long)u * ntiles + tile] = 0.0;
+                if (zlo >= zhi || (u + 1) * kp->cu <= zlo || u * kp->cu >= zhi)
+                    up.dpart[(long)u * ntiles + tile] = 0.0;
     }
     if (zlo < zhi) {
         // the roles hold different state: each gets its own copy of the march
         // (both meet at the same number of barriers)
-        __shared__ double dsum[NT / 64];
 #define FC_TAP_RUN(ROLE)                                                                                          \
-    TapMarch<T, Tio, B, R, MODE, ROWS, TX, TY, NT, ROLE>::run(kp, smem, dsum, in, out, dwith, dpart, tile, ntiles, \
-                                                              x0, y0, zlo, zhi)
+    TapMarch<T, Tio, B, R, MODE, ROWS, TX, TY, NT, ROLE>::run(kp, smem, in, out, tile, ntiles, x0, y0, zlo, zhi, up)
         if constexpr (!RO::SPLIT) {
             FC_TAP_RUN(3);
         } else {
@@ -747,7 +821,7 @@ constexpr int tap_threads(int dim, bool small) { return dim == 1 || small ? 256 
 template <typename T, typename Tio, class B, int R, int MODE, int ROWS>
 void tap_go(const TapArgs<T>& a, dim3 grid, bool small, hipStream_t st)
 {
-    if constexpr (B::DIM == 3 && MODE == TAP_K) {
+    if constexpr (B::DIM == 3 && (MODE == TAP_K || MODE == TAP_CG)) {
         if (small) {
             constexpr int TX = tap_tile_x(3, B::DEG, R, true), TY = tap_tile_y(3, true), NT = tap_threads(3, true);
             hipLaunchKernelGGL((k_tap<T, Tio, B, R, MODE, ROWS, TX, TY, NT>), grid, dim3(NT), 0, st, a);
