@@ -11,7 +11,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libfcrkpm.so")
 SOURCES = ["kernels.hip", "sepconv.hip", "regpass.hip", "fcrkpm.hip",
            "tapconv.hip", "tap_f32.hip", "tap_f64.hip", "tap_f64n.hip", "tap_mix.hip",
-           "tap_cg32.hip", "tap_cg64.hip"]
+           "tap_cg32.hip", "tap_cg64.hip", "tap_mom.hip"]
 
 HIPCC_FLAGS = [
     "-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950",

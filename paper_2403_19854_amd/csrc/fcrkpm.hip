@@ -154,6 +154,25 @@ void dfree(T*& p)
     p = nullptr;
 }
 
+// Arrays that live and die together share one device allocation (an
+// allocation and its release cost about 70 us): want() each, then alloc().
+struct Block {
+    std::vector<std::pair<void**, size_t>> parts;
+    size_t total = 0;
+    template <typename T>
+    void want(T*& p, size_t count)
+    {
+        p = nullptr;
+        parts.emplace_back(reinterpret_cast<void**>(&p), total);
+        total += (count * sizeof(T) + 255) / 256 * 256;
+    }
+    void alloc(uint8_t*& base)
+    {
+        base = dalloc<uint8_t>(total);
+        for (auto& q : parts) *q.first = base + q.second;
+    }
+};
+
 void free_set(OpSet*& s)
 {
     if (!s) return;
@@ -178,18 +197,10 @@ void release(Ctx& c)
     free_set(c.mass_set);
     free_set(c.shift_set);
     free_set(c.jac_set);
-    dfree(c.chi);
+    dfree(c.base_block);
     dfree(c.cls);
-    dfree(c.freem);
-    dfree(c.dirm);
-    dfree(c.vol64);
-    dfree(c.vol32);
     dfree(c.area64);
     dfree(c.area32);
-    dfree(c.b0_64);
-    dfree(c.ba_64);
-    dfree(c.b0_32);
-    dfree(c.ba_32);
     for (int a = 0; a < 3; ++a) {
         dfree(c.tw64[a]);
         dfree(c.tw32[a]);
@@ -200,19 +211,13 @@ void release(Ctx& c)
     }
     dfree(c.work64);
     dfree(c.work32);
-    dfree(c.v64);
-    dfree(c.v32);
-    dfree(c.partial);
-    dfree(c.partial_wide);
-    dfree(c.scal);
-    dfree(c.act);
+    dfree(c.rhs_block);
     dfree(c.nbits[0]);
     dfree(c.nbits[1]);
     dfree(c.noff[0]);
     dfree(c.noff[1]);
     dfree(c.nrec[0]);
     dfree(c.nrec[1]);
-    dfree(c.dflag);
     if (c.aux) (void)hipStreamDestroy(c.aux);
     c.aux = nullptr;
     dfree(c.dprog);
@@ -626,7 +631,13 @@ bool tap_serves_k(const Ctx& c)
 // product with more workgroups than kRedBlocks
 long wide_slots(const Ctx& c) { return std::max(reg_dot_slots(c), tap_dot_slots(c)); }
 
+// Whether any K product of this context runs on FFT passes.
+bool fft_needed(const Ctx& c) { return !tap_serves_k<float, float>(c) || !tap_serves_k<double, double>(c); }
+
 void build_pointwise(Ctx& c, hipStream_t st);
+void fft_tables(Ctx& c, hipStream_t st);
+void fft_build(Ctx& c, hipStream_t st);
+void fft_ensure(Ctx& c, hipStream_t st);
 
 // Exchanges the pointwise data of the K-type product in use with `s`.
 void swap_set(Ctx& c, OpSet& s)
@@ -646,6 +657,7 @@ void swap_set(Ctx& c, OpSet& s)
     std::swap(c.nconst, s.nconst);
     std::swap(c.sym, s.sym);
     std::swap(c.tap, s.tap);
+    std::swap(c.fft_ready, s.fft_ready);
 }
 
 // The products of a scope use the set `s` (kernels take their arguments at
@@ -677,8 +689,10 @@ OpSet* make_set(Ctx& c, double ck, double cm, hipStream_t st, const double* wnod
         HIPCHK(hipGetLastError());
         SetScope use(c, s);
         build_pointwise(c, st);
-        // the line-constant middle pass, where this set's rows have the structure
-        sym_build(c, st);
+        if (fft_needed(c)) {
+            fft_tables(c, st);
+            fft_build(c, st);
+        }
         HIPCHK(hipStreamSynchronize(st));
     } catch (...) {
         free_set(s);
@@ -763,6 +777,7 @@ template <typename T, typename Tio = T>
 void apply_one(Ctx& c, int op, const Tio* in, Tio* out, int nrhs, hipStream_t st)
 {
     if (tap_apply<T, Tio>(c, op, in, out, nrhs, st)) return;
+    fft_ensure(c, st);
     ensure_work(c, nrhs);
     const SepPlan& sp = c.basis_plan;
     const int k = sp.k, last = c.axes[k - 1];
@@ -891,22 +906,19 @@ void ensure_rhs(Ctx& c, int nrhs)
     if (nrhs <= c.cap_rhs) return;
     if (c.capturing) fail(FCRKPM_ERR_ARG, "solver buffers cannot grow during graph capture");
     HIPCHK(hipDeviceSynchronize());
-    dfree(c.v64);
-    dfree(c.v32);
-    dfree(c.partial);
-    dfree(c.scal);
-    dfree(c.act);
+    dfree(c.rhs_block);
     if (c.hscal) (void)hipHostFree(c.hscal);
     c.hscal = nullptr;
     c.cap_rhs = 0;
     const size_t nn = (size_t)c.nn;
-    c.v64 = dalloc<double>(6 * nn * nrhs);
-    c.v32 = dalloc<float>(5 * nn * nrhs);
-    c.partial = dalloc<double>((size_t)2 * kRedBlocks * nrhs);
-    dfree(c.partial_wide);
-    if (wide_slots(c) > kRedBlocks) c.partial_wide = dalloc<double>((size_t)wide_slots(c) * nrhs);
-    c.scal = dalloc<double>((size_t)kScal * nrhs);
-    c.act = dalloc<int>(nrhs);
+    Block blk;
+    blk.want(c.v64, 6 * nn * nrhs);
+    blk.want(c.v32, 5 * nn * nrhs);
+    blk.want(c.partial, (size_t)2 * kRedBlocks * nrhs);
+    if (wide_slots(c) > kRedBlocks) blk.want(c.partial_wide, (size_t)wide_slots(c) * nrhs);
+    blk.want(c.scal, (size_t)kScal * nrhs);
+    blk.want(c.act, nrhs);
+    blk.alloc(c.rhs_block);
     HIPCHK(hipMemset(c.scal, 0, sizeof(double) * kScal * nrhs));
     HIPCHK(hipMemset(c.act, 0, sizeof(int) * nrhs));
     HIPCHK(hipHostMalloc((void**)&c.hscal, sizeof(double) * 3 * kScal * nrhs, hipHostMallocDefault));
@@ -1115,6 +1127,10 @@ struct Solver {
     void begin(hipStream_t st)
     {
         const long nn = c.nn;
+        if (fft_needed(c)) {
+            fft_ensure(c, st);
+            ensure_work(c, nrhs);
+        }
         dots<double>(c, vec64(c, V_B), vec64(c, V_B), nrhs, S_BB, st);
         const double* h = read_scalars(c, nrhs, st);
         for (int j = 0; j < nrhs; ++j) {
@@ -1664,21 +1680,20 @@ void build_pointwise(Ctx& c, hipStream_t st)
         NodeConst nc = {};
         nc.bmax = -1.0;  // no interior node: every domain node is class 2
         if (ref != 0x7fffffff) {
-            for (int q = 0; q < nb; ++q)
-                HIPCHK(hipMemcpy(&nc.b[q], c.ba_64 + (size_t)q * nn + ref, sizeof(double),
-                                 hipMemcpyDeviceToHost));
+            HIPCHK(hipMemcpy2D(nc.b, sizeof(double), c.ba_64 + ref, sizeof(double) * nn, sizeof(double), nb,
+                               hipMemcpyDeviceToHost));
             HIPCHK(hipMemcpy(&nc.v, c.vol64 + ref, sizeof(double), hipMemcpyDeviceToHost));
             nc.bmax = 0.0;
             for (int q = 0; q < nb; ++q) nc.bmax = std::max(nc.bmax, fabs(nc.b[q]));
         }
         c.cls = dalloc<uint8_t>(nn);
-        launch_node_class(c, nc, c.cls, st);
-        {
-            std::vector<uint8_t> hc(nn);
-            HIPCHK(hipMemcpyAsync(hc.data(), c.cls, nn, hipMemcpyDeviceToHost, st));
-            HIPCHK(hipStreamSynchronize(st));
-            c.ncls2 = (long)std::count(hc.begin(), hc.end(), (uint8_t)2);
-        }
+        unsigned long long* cnt = reinterpret_cast<unsigned long long*>(c.dflag + 4);
+        unsigned long long zero = 0, got = 0;
+        HIPCHK(hipMemcpyAsync(cnt, &zero, sizeof(zero), hipMemcpyHostToDevice, st));
+        launch_node_class(c, nc, c.cls, cnt, st);
+        HIPCHK(hipMemcpyAsync(&got, cnt, sizeof(got), hipMemcpyDeviceToHost, st));
+        HIPCHK(hipStreamSynchronize(st));
+        c.ncls2 = (long)got;
         c.nconst = nc;
         for (int q = 0; q < nb; ++q) {
             c.cint64[q] = nc.b[q];
@@ -1687,6 +1702,103 @@ void build_pointwise(Ctx& c, hipStream_t st)
         c.cint64[nb] = nc.v;
         c.cint32[nb] = (float)nc.v;
     }
+    tap_build(c, st);
+}
+
+// What the FFT passes read whatever the rows: twiddles, kernel spectra and the
+// pass programs.  Synchronous, once per context.
+void fft_tables(Ctx& c, hipStream_t st)
+{
+    if (c.dprog) return;
+    // twiddles and separable kernel spectra (Sec 5.2-5.3, Eq 68-79)
+    const long double twopi = 6.283185307179586476925286766559005768L;
+    for (int a = 0; a < 3; ++a) {
+        int L = c.n[a];
+        std::vector<cplx<double>> tw(L);
+        std::vector<cplx<float>> twf(L);
+        for (int k = 0; k < L; ++k) {
+            long double ang = twopi * (long double)k / (long double)L;
+            tw[k] = {(double)cosl(ang), (double)(-sinl(ang))};
+            twf[k] = {(float)tw[k].x, (float)tw[k].y};
+        }
+        c.tw64[a] = dalloc<cplx<double>>(L);
+        c.tw32[a] = dalloc<cplx<float>>(L);
+        HIPCHK(hipMemcpyAsync(c.tw64[a], tw.data(), sizeof(cplx<double>) * L, hipMemcpyHostToDevice, st));
+        HIPCHK(hipMemcpyAsync(c.tw32[a], twf.data(), sizeof(cplx<float>) * L, hipMemcpyHostToDevice, st));
+        int ne = (a < c.dim) ? 2 * c.degree + 1 : 1;
+        std::vector<cplx<double>> sp((size_t)ne * L);
+        std::vector<cplx<float>> spf((size_t)ne * L);
+        for (int e = 0; e < ne; ++e)
+            for (int k = 0; k < L; ++k) {
+                long double re = 0.0L, im = 0.0L;
+                if (a < c.dim) {
+                    for (int o = -c.m[a]; o <= c.m[a]; ++o) {
+                        long double w = bspline((long double)o / (long double)c.at[a]);
+                        long double mo = 1.0L;
+                        for (int t = 0; t < e; ++t) mo *= (long double)o;
+                        long double ang = twopi * (long double)((long)k * o % L) / (long double)L;
+                        re += mo * w * cosl(ang);
+                        im -= mo * w * sinl(ang);
+                    }
+                } else {
+                    re = 1.0L;
+                }
+                sp[(size_t)e * L + k] = {(double)re, (double)im};
+                spf[(size_t)e * L + k] = {(float)re, (float)im};
+            }
+        c.spec64[a] = dalloc<cplx<double>>(sp.size());
+        c.spec32[a] = dalloc<cplx<float>>(spf.size());
+        {
+            // t_e is even or odd in the offset with e, so T_e is real or
+            // imaginary: the register passes take Re T_0, Im T_1, Re T_2,
+            // each with the 1/L of the inverse transform folded in
+            std::vector<float> rt((size_t)3 * L, 0.0f);
+            for (int e = 0; e < 3 && e < ne; ++e)
+                for (int kk = 0; kk < L; ++kk)
+                    rt[(size_t)e * L + kk] = (float)(((e & 1) ? sp[(size_t)e * L + kk].y
+                                                              : sp[(size_t)e * L + kk].x) / L);
+            c.rtab32[a] = dalloc<float>(rt.size());
+            HIPCHK(hipMemcpyAsync(c.rtab32[a], rt.data(), sizeof(float) * rt.size(),
+                                  hipMemcpyHostToDevice, st));
+            std::vector<double> rt64((size_t)3 * L, 0.0);
+            for (int e = 0; e < 3 && e < ne; ++e)
+                for (int kk = 0; kk < L; ++kk)
+                    rt64[(size_t)e * L + kk] = ((e & 1) ? sp[(size_t)e * L + kk].y
+                                                        : sp[(size_t)e * L + kk].x) / L;
+            c.rtab64[a] = dalloc<double>(rt64.size());
+            HIPCHK(hipMemcpyAsync(c.rtab64[a], rt64.data(), sizeof(double) * rt64.size(),
+                                  hipMemcpyHostToDevice, st));
+            HIPCHK(hipStreamSynchronize(st));
+        }
+        HIPCHK(hipMemcpyAsync(c.spec64[a], sp.data(), sizeof(cplx<double>) * sp.size(), hipMemcpyHostToDevice, st));
+        HIPCHK(hipMemcpyAsync(c.spec32[a], spf.data(), sizeof(cplx<float>) * spf.size(), hipMemcpyHostToDevice, st));
+        HIPCHK(hipStreamSynchronize(st));
+    }
+    const SepPlan mom_plan = build_plan(c, c.ex2, c.nmono2);
+    {
+        // programs live in device memory: [basis p1 0..2, basis p2 0..2, moment p1 0..2]
+        std::vector<SepProg> hp(9);
+        for (int j = 0; j < 3; ++j) {
+            hp[j] = c.basis_plan.p1[j];
+            hp[3 + j] = c.basis_plan.p2[j];
+            hp[6 + j] = mom_plan.p1[j];
+        }
+        c.dprog = dalloc<SepProg>(9);
+        HIPCHK(hipMemcpy(c.dprog, hp.data(), sizeof(SepProg) * 9, hipMemcpyHostToDevice));
+        for (int j = 0; j < 3; ++j) {
+            c.basis_plan.d1[j] = c.dprog + j;
+            c.basis_plan.d2[j] = c.dprog + 3 + j;
+        }
+    }
+}
+
+// What the FFT passes of the rows in use keep besides: the records of the
+// register path and the line-constant structure.  Contexts whose products run
+// on the direct kernels build them when an option or a call first asks for FFT
+// passes.
+void fft_build(Ctx& c, hipStream_t st)
+{
+    c.fft_ready = true;
     // node classes of the register-resident K passes: interior nodes share
     // one M = V B^T B (a kernel argument), nodes outside the domain give
     // zero, and every other element gets its own record, packed lane by lane
@@ -1732,7 +1844,20 @@ void build_pointwise(Ctx& c, hipStream_t st)
             HIPCHK(hipStreamSynchronize(st));
         }
     }
-    tap_build(c, st);
+    // the line-constant middle pass, where these rows have the structure
+    sym_build(c, st);
+    HIPCHK(hipStreamSynchronize(st));
+}
+
+void fft_ensure(Ctx& c, hipStream_t st)
+{
+    if (c.fft_ready) return;
+    if (c.capturing) fail(FCRKPM_ERR_ARG, "the FFT passes cannot be set up during graph capture");
+    fft_tables(c, st);
+    fft_build(c, st);
+    // the FP64 register path's records of u^h, f^r and the gradient force,
+    // built here so that no later product allocates them
+    (void)reg_kn_ok(c, st);
 }
 
 void set_reg_variant(Ctx& c, int v)
@@ -1918,6 +2043,19 @@ void autotune(Ctx& c, hipStream_t st)
         }
     }
 }
+
+// The FFT passes of K and their autotuned choices, once per context.
+void fft_tune(Ctx& c, hipStream_t st)
+{
+    fft_ensure(c, st);
+    if (c.fft_tuned) return;
+    c.fft_tuned = true;
+    ensure_work(c, 1);
+    autotune(c, st);
+    c.tuned[0] = c.reg_layout + 2 * (c.reg_tpw - 1);
+    c.tuned[1] = c.sep_wcap[0];
+    c.tuned[2] = c.sep_wcap[1];
+}
 }  // namespace
 
 extern "C" fcrkpm_status fcrkpm_setup(const fcrkpm_grid* grid, const uint8_t* mask, int32_t kernel,
@@ -1973,10 +2111,23 @@ extern "C" fcrkpm_status fcrkpm_setup(const fcrkpm_grid* grid, const uint8_t* ma
         c.scratch = scratch_address();
 
         // masks and volumes
-        c.chi = dalloc<uint8_t>(nn);
-        c.freem = dalloc<uint8_t>(nn);
-        c.dirm = dalloc<uint8_t>(nn);
-        c.dflag = dalloc<int>(8);
+        const int ntot = c.n[0] + c.n[1] + c.n[2];
+        int* occ = nullptr;
+        {
+            Block blk;
+            blk.want(c.chi, nn);
+            blk.want(c.freem, nn);
+            blk.want(c.dirm, nn);
+            blk.want(c.dflag, 8);
+            blk.want(c.vol64, nn);
+            blk.want(c.vol32, nn);
+            blk.want(occ, ntot);
+            blk.want(c.b0_64, (size_t)c.s * nn);
+            blk.want(c.ba_64, (size_t)c.dim * c.s * nn);
+            blk.want(c.b0_32, (size_t)c.s * nn);
+            blk.want(c.ba_32, (size_t)c.dim * c.s * nn);
+            blk.alloc(c.base_block);
+        }
         HIPCHK(hipMemcpyAsync(c.chi, mask, nn, hipMemcpyDeviceToDevice, st));
         if (grid->dirichlet)
             HIPCHK(hipMemcpyAsync(c.dirm, grid->dirichlet, nn, hipMemcpyDeviceToDevice, st));
@@ -1985,12 +2136,8 @@ extern "C" fcrkpm_status fcrkpm_setup(const fcrkpm_grid* grid, const uint8_t* ma
         int init[8] = {0x7fffffff, 0x7fffffff, 0, 0, 0, 0, 0, 0};
         HIPCHK(hipMemcpyAsync(c.dflag, init, sizeof(init), hipMemcpyHostToDevice, st));
         launch_free_mask(c.chi, c.dirm, c.freem, c.dflag + 0, nn, st);
-        c.vol64 = dalloc<double>(nn);
-        c.vol32 = dalloc<float>(nn);
         launch_vol(c.chi, grid->vol, c.h[0] * c.h[1] * c.h[2], c.vol64, c.vol32, nn, st);
         // periodic-gap check on each axis (Sec 5.1, Eq 66)
-        int ntot = c.n[0] + c.n[1] + c.n[2];
-        int* occ = dalloc<int>(ntot);
         HIPCHK(hipMemsetAsync(occ, 0, sizeof(int) * ntot, st));
         launch_axis_extent(c, c.chi, occ, st);
         std::vector<int> hocc(ntot);
@@ -1998,7 +2145,6 @@ extern "C" fcrkpm_status fcrkpm_setup(const fcrkpm_grid* grid, const uint8_t* ma
         HIPCHK(hipMemcpyAsync(hocc.data(), occ, sizeof(int) * ntot, hipMemcpyDeviceToHost, st));
         HIPCHK(hipMemcpyAsync(hflag, c.dflag, sizeof(hflag), hipMemcpyDeviceToHost, st));
         HIPCHK(hipStreamSynchronize(st));
-        dfree(occ);
         if (hflag[0] != 0x7fffffff)
             fail(FCRKPM_ERR_ARG, "Dirichlet node " + std::to_string(hflag[0]) + " lies outside the domain mask");
         int off = 0;
@@ -2019,98 +2165,18 @@ extern "C" fcrkpm_status fcrkpm_setup(const fcrkpm_grid* grid, const uint8_t* ma
         }
 
         // taps of the direct kernels: t_e(o) = o^e phi(o / a~)
-        double taps[3][5][4] = {};
+        double taps[3][kTapE][4] = {};
         for (int a = 0; a < c.dim; ++a) {
             c.tap_r = std::max(c.tap_r, (int)ceil(c.at[a]) - 1);
             for (int o = 0; o < 4; ++o) {
                 long double mo = bspline((long double)o / (long double)c.at[a]);
-                for (int e = 0; e < 5; ++e, mo *= (long double)o) taps[a][e][o] = (double)mo;
+                for (int e = 0; e < kTapE; ++e, mo *= (long double)o) taps[a][e][o] = (double)mo;
             }
         }
         tap_setup(c, taps, st);
 
-        // twiddles and separable kernel spectra (Sec 5.2-5.3, Eq 68-79)
-        const long double twopi = 6.283185307179586476925286766559005768L;
-        for (int a = 0; a < 3; ++a) {
-            int L = c.n[a];
-            std::vector<cplx<double>> tw(L);
-            std::vector<cplx<float>> twf(L);
-            for (int k = 0; k < L; ++k) {
-                long double ang = twopi * (long double)k / (long double)L;
-                tw[k] = {(double)cosl(ang), (double)(-sinl(ang))};
-                twf[k] = {(float)tw[k].x, (float)tw[k].y};
-            }
-            c.tw64[a] = dalloc<cplx<double>>(L);
-            c.tw32[a] = dalloc<cplx<float>>(L);
-            HIPCHK(hipMemcpyAsync(c.tw64[a], tw.data(), sizeof(cplx<double>) * L, hipMemcpyHostToDevice, st));
-            HIPCHK(hipMemcpyAsync(c.tw32[a], twf.data(), sizeof(cplx<float>) * L, hipMemcpyHostToDevice, st));
-            int ne = (a < c.dim) ? 2 * degree + 1 : 1;
-            std::vector<cplx<double>> sp((size_t)ne * L);
-            std::vector<cplx<float>> spf((size_t)ne * L);
-            for (int e = 0; e < ne; ++e)
-                for (int k = 0; k < L; ++k) {
-                    long double re = 0.0L, im = 0.0L;
-                    if (a < c.dim) {
-                        for (int o = -c.m[a]; o <= c.m[a]; ++o) {
-                            long double w = bspline((long double)o / (long double)c.at[a]);
-                            long double mo = 1.0L;
-                            for (int t = 0; t < e; ++t) mo *= (long double)o;
-                            long double ang = twopi * (long double)((long)k * o % L) / (long double)L;
-                            re += mo * w * cosl(ang);
-                            im -= mo * w * sinl(ang);
-                        }
-                    } else {
-                        re = 1.0L;
-                    }
-                    sp[(size_t)e * L + k] = {(double)re, (double)im};
-                    spf[(size_t)e * L + k] = {(float)re, (float)im};
-                }
-            c.spec64[a] = dalloc<cplx<double>>(sp.size());
-            c.spec32[a] = dalloc<cplx<float>>(spf.size());
-            {
-                // t_e is even or odd in the offset with e, so T_e is real or
-                // imaginary: the register passes take Re T_0, Im T_1, Re T_2,
-                // each with the 1/L of the inverse transform folded in
-                std::vector<float> rt((size_t)3 * L, 0.0f);
-                for (int e = 0; e < 3 && e < ne; ++e)
-                    for (int kk = 0; kk < L; ++kk)
-                        rt[(size_t)e * L + kk] = (float)(((e & 1) ? sp[(size_t)e * L + kk].y
-                                                                  : sp[(size_t)e * L + kk].x) / L);
-                c.rtab32[a] = dalloc<float>(rt.size());
-                HIPCHK(hipMemcpyAsync(c.rtab32[a], rt.data(), sizeof(float) * rt.size(),
-                                      hipMemcpyHostToDevice, st));
-                std::vector<double> rt64((size_t)3 * L, 0.0);
-                for (int e = 0; e < 3 && e < ne; ++e)
-                    for (int kk = 0; kk < L; ++kk)
-                        rt64[(size_t)e * L + kk] = ((e & 1) ? sp[(size_t)e * L + kk].y
-                                                            : sp[(size_t)e * L + kk].x) / L;
-                c.rtab64[a] = dalloc<double>(rt64.size());
-                HIPCHK(hipMemcpyAsync(c.rtab64[a], rt64.data(), sizeof(double) * rt64.size(),
-                                      hipMemcpyHostToDevice, st));
-                HIPCHK(hipStreamSynchronize(st));
-            }
-            HIPCHK(hipMemcpyAsync(c.spec64[a], sp.data(), sizeof(cplx<double>) * sp.size(), hipMemcpyHostToDevice, st));
-            HIPCHK(hipMemcpyAsync(c.spec32[a], spf.data(), sizeof(cplx<float>) * spf.size(), hipMemcpyHostToDevice, st));
-            HIPCHK(hipStreamSynchronize(st));
-        }
         c.basis_plan = build_plan(c, c.ex, c.s);
         SepPlan mom_plan = build_plan(c, c.ex2, c.nmono2);
-        {
-            // programs live in device memory: [basis p1 0..2, basis p2 0..2, moment p1 0..2]
-            std::vector<SepProg> hp(9);
-            for (int j = 0; j < 3; ++j) {
-                hp[j] = c.basis_plan.p1[j];
-                hp[3 + j] = c.basis_plan.p2[j];
-                hp[6 + j] = mom_plan.p1[j];
-            }
-            c.dprog = dalloc<SepProg>(9);
-            HIPCHK(hipMemcpy(c.dprog, hp.data(), sizeof(SepProg) * 9, hipMemcpyHostToDevice));
-            for (int j = 0; j < 3; ++j) {
-                c.basis_plan.d1[j] = c.dprog + j;
-                c.basis_plan.d2[j] = c.dprog + 3 + j;
-                mom_plan.d1[j] = c.dprog + 6 + j;
-            }
-        }
         {
             int dev = 0, maxsh = 0;
             HIPCHK(hipGetDevice(&dev));
@@ -2123,25 +2189,29 @@ extern "C" fcrkpm_status fcrkpm_setup(const fcrkpm_grid* grid, const uint8_t* ma
         }
 
         // Alg 1: moment convolutions and per-node solves (FP64)
-        c.b0_64 = dalloc<double>((size_t)c.s * nn);
-        c.ba_64 = dalloc<double>((size_t)c.dim * c.s * nn);
-        c.b0_32 = dalloc<float>((size_t)c.s * nn);
-        c.ba_32 = dalloc<float>((size_t)c.dim * c.s * nn);
         {
-            const int k = mom_plan.k;
             const int ng = (c.nmono2 + 1) / 2;
-            cplx<double>* G = dalloc<cplx<double>>((size_t)(ng + 2 * mom_plan.maxpairs) * nn);
-            cplx<double>* S1 = G + (size_t)ng * nn;
-            cplx<double>* S2 = S1 + (size_t)mom_plan.maxpairs * nn;
-            const void* src = nullptr;
-            cplx<double>* dst = (k == 1) ? G : S1;
-            for (int j = 0; j < k; ++j) {
+            cplx<double>* G = nullptr;
+            if (tap_served(c)) {
+                G = dalloc<cplx<double>>((size_t)ng * nn);
                 ProfScope ps(c, KD_SETUP_PASS, 0.0, st);
-                launch_sep_pass<double, double>(c, c.axes[j], mom_plan.p1[j], mom_plan.d1[j],
-                                                j == 0 ? SEP_LD_CHI : SEP_LD_PAIRS, src, c.chi,
-                                                SEP_ST_PAIRS, dst, nullptr, nullptr, nullptr, st);
-                src = dst;
-                dst = (j + 2 == k) ? G : ((dst == S1) ? S2 : S1);
+                launch_tap_moments(c, G, st);
+            } else {
+                fft_tables(c, st);
+                const int k = mom_plan.k;
+                G = dalloc<cplx<double>>((size_t)(ng + 2 * mom_plan.maxpairs) * nn);
+                cplx<double>* S1 = G + (size_t)ng * nn;
+                cplx<double>* S2 = S1 + (size_t)mom_plan.maxpairs * nn;
+                const void* src = nullptr;
+                cplx<double>* dst = (k == 1) ? G : S1;
+                for (int j = 0; j < k; ++j) {
+                    ProfScope ps(c, KD_SETUP_PASS, 0.0, st);
+                    launch_sep_pass<double, double>(c, c.axes[j], mom_plan.p1[j], c.dprog + 6 + j,
+                                                    j == 0 ? SEP_LD_CHI : SEP_LD_PAIRS, src, c.chi, SEP_ST_PAIRS,
+                                                    dst, nullptr, nullptr, nullptr, st);
+                    src = dst;
+                    dst = (j + 2 == k) ? G : ((dst == S1) ? S2 : S1);
+                }
             }
             if (const char* dump = getenv("FCRKPM_DUMP")) {
                 HIPCHK(hipStreamSynchronize(st));
@@ -2165,19 +2235,12 @@ extern "C" fcrkpm_status fcrkpm_setup(const fcrkpm_grid* grid, const uint8_t* ma
         c.krows = c.dim;
         build_pointwise(c, st);
         if (const char* e = getenv("FCRKPM_SYM")) c.use_sym = *e != '0';
-        sym_build(c, st);
-        // the FP64 register path's records of u^h, f^r and the gradient force,
-        // built here so that no later product allocates them
-        (void)reg_kn_ok(c, st);
-
-        // workspace and solver buffers for one right-hand side; both grow on demand
+        // solver buffers for one right-hand side, and the workspace of the FFT
+        // passes where they serve products; both grow on demand
         HIPCHK(hipStreamSynchronize(st));
-        ensure_work(c, 1);
         ensure_rhs(c, 1);
-        autotune(c, st);
-        c.tuned[0] = c.reg_layout + 2 * (c.reg_tpw - 1);
-        c.tuned[1] = c.sep_wcap[0];
-        c.tuned[2] = c.sep_wcap[1];
+        const char* cache = getenv("FCRKPM_AUTOTUNE_CACHE");
+        if (fft_needed(c) || (cache && *cache)) fft_tune(c, st);
         HIPCHK(hipGetLastError());
         *out = h;
         h = nullptr;
@@ -2197,7 +2260,6 @@ void prepare_solve(Ctx& c, int nrhs, const double* r, const double* g, const dou
                    hipStream_t st, const double* qflux = nullptr)
 {
     ensure_rhs(c, nrhs);
-    ensure_work(c, nrhs);
     const long nn = c.nn;
     HIPCHK(hipMemsetAsync(c.dflag + 2, 0, sizeof(int), st));
     launch_check_finite(r, nn * nrhs, c.dflag + 2, st);
@@ -2486,7 +2548,6 @@ extern "C" fcrkpm_status fcrkpm_adjoint(fcrkpm_ctx* ctx, int32_t mode, int32_t n
         if (!dl_duh || !dl_dr) fail(FCRKPM_ERR_ARG, "NULL array");
         hipStream_t st = (hipStream_t)stream;
         ensure_rhs(c, nrhs);
-        ensure_work(c, nrhs);
         const long nn = c.nn;
         double* b = vec64(c, V_B);
         double* x = vec64(c, V_X);
@@ -2534,7 +2595,6 @@ extern "C" fcrkpm_status fcrkpm_transient(fcrkpm_ctx* ctx, const fcrkpm_time* tp
         hipStream_t st = (hipStream_t)stream;
         const long nn = c.nn;
         ensure_rhs(c, nrhs);
-        ensure_work(c, nrhs);
         HIPCHK(hipMemsetAsync(c.dflag + 2, 0, sizeof(int), st));
         if (r) launch_check_finite(r, nn * nrhs, c.dflag + 2, st);
         if (g) launch_check_finite(g, nn * nrhs, c.dflag + 2, st);
@@ -2639,7 +2699,6 @@ extern "C" fcrkpm_status fcrkpm_nonlinear_force(fcrkpm_ctx* ctx, double kappa, i
         if (!std::isfinite(kappa)) fail(FCRKPM_ERR_ARG, "kappa must be finite");
         hipStream_t st = (hipStream_t)stream;
         ensure_rhs(c, nrhs);
-        ensure_work(c, nrhs);
         double* u = vec64(c, V_T);
         apply_one<double>(c, FCRKPM_OP_UH, d, u, nrhs, st);
         launch_pow_scaled(u, kappa, 3, u, c.nn * nrhs, st);
@@ -2680,6 +2739,7 @@ void apply_grad(Ctx& c, const double* x, double* out, hipStream_t st)
         launch_tap<double, double>(c, kTapGrad, x, out, c.chi, nullptr, c.ba_64, nullptr, 1, st);
         return;
     }
+    fft_ensure(c, st);
     if (use_reg_path64(c) && reg_kn_ok(c, st)) {
         launch_reg_kn(c, x, out, 0.0, RK_GRAD, st);
         return;
@@ -3003,6 +3063,19 @@ extern "C" fcrkpm_status fcrkpm_get_option(fcrkpm_ctx* ctx, int32_t option, int6
     Ctx& c = ctx->c;
     return run_guarded(c.err, [&]() -> fcrkpm_status {
         if (!value) fail(FCRKPM_ERR_ARG, "NULL value");
+        switch (option) {  // what describes the FFT passes has them set up first
+            case FCRKPM_OPT_REGLAYOUT:
+            case FCRKPM_OPT_TUNE_NS0:
+            case FCRKPM_OPT_TUNE_NS1:
+            case FCRKPM_OPT_TUNE_NS2:
+            case FCRKPM_OPT_TUNE_NS3:
+            case FCRKPM_OPT_SEP_LINES32:
+            case FCRKPM_OPT_SEP_LINES64:
+            case FCRKPM_OPT_TUNE_CACHED: fft_tune(c, nullptr); break;
+            case FCRKPM_OPT_LINECONST:
+            case FCRKPM_OPT_KN_REGPATH: fft_ensure(c, nullptr); break;
+            default: break;
+        }
         switch (option) {
             case FCRKPM_OPT_GRAPHS: *value = c.use_graphs ? 1 : 0; break;
             case FCRKPM_OPT_REGPATH: *value = (c.use_regpath && reg_path_ok(c)) ? 1 : 0; break;
@@ -3027,6 +3100,18 @@ namespace {
 // An option that asks for FFT passes other than setup's choice selects them
 // instead of the direct kernels; its default gives the choice back.
 void pin_fft(Ctx& c, int bit, bool on) { c.fft_pins = on ? c.fft_pins | bit : c.fft_pins & ~bit; }
+
+// The FFT passes of every operator set built so far, so that no later product
+// has to set them up.
+void fft_all(Ctx& c)
+{
+    fft_tune(c, nullptr);
+    for (OpSet* s : {c.mass_set, c.shift_set, c.jac_set})
+        if (s) {
+            SetScope use(c, s);
+            fft_ensure(c, nullptr);
+        }
+}
 }  // namespace
 
 extern "C" fcrkpm_status fcrkpm_set_option(fcrkpm_ctx* ctx, int32_t option, int64_t value)
@@ -3034,6 +3119,10 @@ extern "C" fcrkpm_status fcrkpm_set_option(fcrkpm_ctx* ctx, int32_t option, int6
     if (!ctx) return FCRKPM_ERR_ARG;
     Ctx& c = ctx->c;
     return run_guarded(c.err, [&]() -> fcrkpm_status {
+        if (option == FCRKPM_OPT_REGLAYOUT || option == FCRKPM_OPT_SEP_LINES32 || option == FCRKPM_OPT_SEP_LINES64 ||
+            ((option == FCRKPM_OPT_REGPATH || option == FCRKPM_OPT_LINECONST || option == FCRKPM_OPT_TAPS) &&
+             value == 0))
+            fft_all(c);
         switch (option) {
             case FCRKPM_OPT_GRAPHS:
                 if (value != 0 && value != 1) fail(FCRKPM_ERR_ARG, "FCRKPM_OPT_GRAPHS takes 0 or 1");

@@ -84,6 +84,7 @@ struct OpSet {
     NodeConst nconst = {};
     void* sym = nullptr;                // line-constant records of this set's rows
     void* tap = nullptr;                // direct tap kernels: class words and records of this set's rows
+    bool fft_ready = false;             // what the FFT passes of these rows keep is built
 };
 
 struct Ctx {
@@ -181,11 +182,15 @@ struct Ctx {
     int fft_pins = 0;                   // options that ask for FFT passes (bits)
     int tuned[3] = {0, 16, 16};         // setup's register variant and lines per workgroup (FP32, FP64)
     int tap_r = 0;                      // tap radius: the largest ceil(a~) - 1 of the axes
-    double tap_t[3][5][4] = {};         // taps t_e(o) of each axis, o = 0..3
+    double tap_t[3][7][4] = {};         // taps t_e(o) of each axis, o = 0..3
     int tap_nt[2][2] = {};              // tiles along x and y, of the large and the small tile
     int tap_cus = 256;                  // compute units of the device
     int2* tap_zr[2] = {};               // first and last domain plane of each tile column
     void* tap = nullptr;                // class words and records of the K-type product in use
+    bool fft_ready = false;             // what the FFT passes of these rows keep is built
+    bool fft_tuned = false;             // ... and tuned (K)
+    uint8_t* base_block = nullptr;      // one allocation of the masks, volumes and coefficients
+    uint8_t* rhs_block = nullptr;       // ... and of the solver buffers
 };
 
 constexpr int kRedBlocks = 1024;   // reduction partials per right-hand side (at most)
@@ -322,7 +327,11 @@ struct TapCg {
     int parity;
     const int* act;
 };
-void tap_setup(Ctx& c, const double (*taps)[5][4], hipStream_t st);
+constexpr int kTapE = 7;  // exponents of the taps: 0..6 (moments of the cubic basis)
+bool tap_served(const Ctx& c);  // bases and radii that have direct kernels
+void tap_setup(Ctx& c, const double (*taps)[kTapE][4], hipStream_t st);
+// the moment convolutions F^-1[F(chi) F(H_m)], pairs of monomials [pair][nn]
+void launch_tap_moments(const Ctx& c, cplx<double>* G, hipStream_t st);
 void tap_build(Ctx& c, hipStream_t st);
 bool tap_active(const Ctx& c);
 long tap_dots(const Ctx& c, int elem_bytes);
@@ -348,7 +357,8 @@ void launch_free_mask(const uint8_t* chi, const uint8_t* dir, uint8_t* freem, in
 void launch_axis_extent(const Ctx& c, const uint8_t* chi, int* occ, hipStream_t st);
 void launch_moment_solve(const Ctx& c, const cplx<double>* G, int* bad, hipStream_t st);
 void launch_first_interior(const Ctx& c, int* ref, hipStream_t st);
-void launch_node_class(const Ctx& c, const NodeConst& ref, uint8_t* cls, hipStream_t st);
+// (n2 += the nodes of class 2)
+void launch_node_class(const Ctx& c, const NodeConst& ref, uint8_t* cls, unsigned long long* n2, hipStream_t st);
 void launch_vol(const uint8_t* chi, const double* vol_in, double hv, double* vol64, float* vol32,
                 long nn, hipStream_t st);
 void launch_mask_to_double(const uint8_t* m, double* out, long nn, hipStream_t st);

@@ -38,6 +38,15 @@
 #define FC_TAP_CG32(X) FC_TAP_KS(X, float, float, TAP_CG)
 #define FC_TAP_CG64(X) FC_TAP_KS(X, double, double, TAP_CG)
 
+// moments: the basis of twice the degree, in FP64
+#define FC_TAP_MOM1(X, DIM, DEG, R) X(double, double, DIM, DEG, R, TAP_MOM, 1)
+#define FC_TAP_MOM(X)                                                                                          \
+    FC_TAP_MOM1(X, 1, 2, 1) FC_TAP_MOM1(X, 1, 2, 2) FC_TAP_MOM1(X, 1, 2, 3) FC_TAP_MOM1(X, 1, 4, 2)             \
+    FC_TAP_MOM1(X, 1, 4, 3) FC_TAP_MOM1(X, 1, 6, 3) FC_TAP_MOM1(X, 2, 2, 1) FC_TAP_MOM1(X, 2, 2, 2)             \
+    FC_TAP_MOM1(X, 2, 2, 3) FC_TAP_MOM1(X, 2, 4, 2) FC_TAP_MOM1(X, 2, 4, 3) FC_TAP_MOM1(X, 2, 6, 3)             \
+    FC_TAP_MOM1(X, 3, 2, 1) FC_TAP_MOM1(X, 3, 2, 2) FC_TAP_MOM1(X, 3, 2, 3) FC_TAP_MOM1(X, 3, 4, 2)             \
+    FC_TAP_MOM1(X, 3, 4, 3)
+
 #define FC_TAP_EXTERN(T, U, DIM, DEG, R, MODE, ROWS) \
     extern template void tap_go<T, U, TapBasis<DIM, DEG>, R, MODE, ROWS>(const TapArgs<T>&, dim3, bool, hipStream_t);
 #define FC_TAP_BUILD(T, U, DIM, DEG, R, MODE, ROWS) \
@@ -50,4 +59,5 @@ FC_TAP_F64N(FC_TAP_EXTERN)
 FC_TAP_MIX(FC_TAP_EXTERN)
 FC_TAP_CG32(FC_TAP_EXTERN)
 FC_TAP_CG64(FC_TAP_EXTERN)
+FC_TAP_MOM(FC_TAP_EXTERN)
 }  // namespace fcrkpm

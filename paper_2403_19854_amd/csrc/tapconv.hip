@@ -19,6 +19,8 @@ struct TapSet {
     double* rec64 = nullptr;
     float m32[kTapMint] = {};
     double m64[kTapMint] = {};
+};  // per tile a bit per plane whose E level is interior throughout (large, small tile)
+    double dint[3] = {};
 };
 
 void tap_check(hipError_t e)
@@ -51,30 +53,39 @@ int tap_gx(const Ctx& c)
     return (c.n[0] + tx - 1) / tx * (tx / 2) + c.tap_r;
 }
 
-// first and last plane with a domain node per tile column
+// First and last plane with a domain node per tile column, from (nz, -1): a
+// block looks at eight planes of a column.
+constexpr int kExtentPlanes = 8;
+
+__global__ void k_tap_extent_clear(int2* __restrict__ zr, int n, int nz)
+{
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) zr[i] = int2{nz, -1};
+}
+
 __global__ __launch_bounds__(256) void k_tap_extent(const uint8_t* __restrict__ chi, int nx, int ny, int nz,
                                                     int ntx, int tx, int ty, int2* __restrict__ zr)
 {
-    __shared__ int lo, hi;
-    if (threadIdx.x == 0) {
-        lo = nz;
-        hi = -1;
-    }
-    __syncthreads();
     const int x0 = (blockIdx.x % ntx) * tx, y0 = (blockIdx.x / ntx) * ty;
-    const int w = min(tx, nx - x0), h = min(ty, ny - y0);
+    const int w = min(tx, nx - x0), h = min(ty, ny - y0), z0 = blockIdx.y * kExtentPlanes;
+    const int np = min(kExtentPlanes, nz - z0);
     int l = nz, u = -1;
-    for (long i = threadIdx.x; i < (long)w * h * nz; i += blockDim.x) {
-        const int z = (int)(i / (w * h)), k = (int)(i % (w * h));
+    for (int i = threadIdx.x; i < w * h * np; i += blockDim.x) {
+        const int z = z0 + i / (w * h), k = i % (w * h);
         if (chi[((long)z * ny + y0 + k / w) * nx + x0 + k % w]) {
             l = min(l, z);
             u = max(u, z);
         }
     }
-    atomicMin(&lo, l);
-    atomicMax(&hi, u);
-    __syncthreads();
-    if (threadIdx.x == 0) zr[blockIdx.x] = int2{lo, hi};
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        l = min(l, __shfl_xor(l, o, 64));
+        u = max(u, __shfl_xor(u, o, 64));
+    }
+    if ((threadIdx.x & 63) == 0 && u >= 0) {
+        atomicMin(&zr[blockIdx.x].x, l);
+        atomicMax(&zr[blockIdx.x].y, u);
+    }
 }
 
 // Class words and records.  A word covers two nodes along x: two bits of class
@@ -220,7 +231,7 @@ TapCut tap_cut(const Ctx& c, int mode, int nrhs, int elem)
 }  // namespace
 
 // Bases and radii with a kernel (tap_list.hpp).
-static bool tap_served(const Ctx& c) { return c.tap_r >= c.degree && c.tap_r >= 1 && c.tap_r <= kTapR; }
+bool tap_served(const Ctx& c) { return c.tap_r >= c.degree && c.tap_r >= 1 && c.tap_r <= kTapR; }
 
 bool tap_active(const Ctx& c) { return c.use_taps && !c.fft_pins && c.tap; }
 
@@ -248,7 +259,7 @@ void tap_release(Ctx& c)
 }
 
 // taps and the domain's extent per tile column (once per context)
-void tap_setup(Ctx& c, const double (*taps)[kTapE][kTapR + 1], hipStream_t st)
+void tap_setup(Ctx& c, const double (*taps)[kTapE][4], hipStream_t st)
 {
     memcpy(c.tap_t, taps, sizeof(c.tap_t));
     int dev = 0;
@@ -259,7 +270,9 @@ void tap_setup(Ctx& c, const double (*taps)[kTapE][kTapR + 1], hipStream_t st)
         const int nx = c.tap_nt[small][0] = (c.n[0] + tx - 1) / tx;
         const int ny = c.tap_nt[small][1] = (c.n[1] + ty - 1) / ty;
         c.tap_zr[small] = tap_alloc<int2>((size_t)nx * ny);
-        hipLaunchKernelGGL(k_tap_extent, dim3(nx * ny), dim3(256), 0, st, c.chi, c.n[0], c.n[1], c.n[2], nx, tx,
+        hipLaunchKernelGGL(k_tap_extent_clear, dim3((nx * ny + 255) / 256), dim3(256), 0, st, c.tap_zr[small], nx * ny,
+                           c.n[2]);
+        hipLaunchKernelGGL(k_tap_extent, dim3(nx * ny, (c.n[2] + kExtentPlanes - 1) / kExtentPlanes), dim3(256), 0, st, c.chi, c.n[0], c.n[1], c.n[2], nx, tx,
                            ty, c.tap_zr[small]);
     }
     tap_check(hipGetLastError());
@@ -326,21 +339,53 @@ void tap_build(Ctx& c, hipStream_t st)
     tap_check(hipStreamSynchronize(st));
 }
 
-template <typename T, typename Tio>
-void launch_tap(const Ctx& c, int mode, const Tio* in, Tio* out, const uint8_t* mask_in,
-                const uint8_t* mask_out, const T* rows_in, const T* vol, int nrhs, hipStream_t st, const TapCg* cg)
+// what every launch passes
+template <typename T>
+static TapArgs<T> tap_args(const Ctx& c)
 {
-    const TapSet& s = *(const TapSet*)c.tap;
     TapArgs<T> a = {};
-    a.in = in;
-    a.out = out;
-    a.mask_in = mask_in;
-    a.mask_out = mask_out;
     for (int k = 0; k < 3; ++k) {
         a.n[k] = c.n[k];
         for (int e = 0; e < kTapE; ++e)
             for (int o = 0; o <= kTapR; ++o) a.t[k][e][o] = (T)c.tap_t[k][e][o];
     }
+    a.nn = c.nn;
+    return a;
+}
+
+void launch_tap_moments(const Ctx& c, cplx<double>* G, hipStream_t st)
+{
+    TapArgs<double> a = tap_args<double>(c);
+    a.out = G;
+    a.mask_in = c.chi;
+    const TapCut cut = tap_cut_tile(c, false, 1, 8, 1);
+    a.ntx = c.tap_nt[0][0];
+    a.nty = c.tap_nt[0][1];
+    a.cz = a.cu = cut.cz;
+    a.zr = c.tap_zr[0];
+    const dim3 grid((unsigned)((long)a.ntx * a.nty * ((c.n[2] + a.cz - 1) / a.cz)));
+    bool done = false;
+#define FC_TAP_CASE(T_, TIO_, DIM, DEG, R, MODE, ROWS)                            \
+    if (!done && c.dim == DIM && 2 * c.degree == DEG && c.tap_r == R) {           \
+        tap_go<T_, TIO_, TapBasis<DIM, DEG>, R, MODE, ROWS>(a, grid, false, st);  \
+        done = true;                                                              \
+    }
+    FC_TAP_MOM(FC_TAP_CASE)
+#undef FC_TAP_CASE
+    if (!done) raise_unsupported("internal: no moment kernel for this basis");
+    tap_check(hipGetLastError());
+}
+
+template <typename T, typename Tio>
+void launch_tap(const Ctx& c, int mode, const Tio* in, Tio* out, const uint8_t* mask_in,
+                const uint8_t* mask_out, const T* rows_in, const T* vol, int nrhs, hipStream_t st, const TapCg* cg)
+{
+    const TapSet& s = *(const TapSet*)c.tap;
+    TapArgs<T> a = tap_args<T>(c);
+    a.in = in;
+    a.out = out;
+    a.mask_in = mask_in;
+    a.mask_out = mask_out;
     const TapCut cut = tap_cut(c, mode, nrhs, sizeof(T));
     a.ntx = c.tap_nt[cut.small][0];
     a.nty = c.tap_nt[cut.small][1];
@@ -372,7 +417,6 @@ void launch_tap(const Ctx& c, int mode, const Tio* in, Tio* out, const uint8_t* 
     }
     a.vol = vol;
     a.kappa = (T)c.pw_kappa;
-    a.nn = c.nn;
     a.rb = c.nn * (long)sizeof(Tio) * (mode == TAP_GRAD ? c.dim : 1);
     const dim3 grid((unsigned)((long)a.ntx * a.nty * ((c.n[2] + a.cz - 1) / a.cz)), (unsigned)nrhs);
     // the linear bases keep M, whatever the rows it was made of

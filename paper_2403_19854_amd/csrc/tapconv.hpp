@@ -35,12 +35,14 @@
 namespace fcrkpm {
 
 constexpr int kTapR = 3;          // largest tap radius
-constexpr int kTapE = 5;          // exponents 0..4 (moments of the quadratic basis)
+
 constexpr int kTapMint = kMaxNodeConst + 1;  // interior record: rows and V (wider row sets have no interior class)
 
 // K products; u^h; the loads f^r, f^q and N^T y; the gradient force.  TAP_GRAD
-// is u^h with the rows b^a (one field, its dim components nn apart).
-enum { TAP_K = SEP_PW_K, TAP_UH = SEP_PW_UH, TAP_LOAD = SEP_PW_LOAD, TAP_KN = SEP_PW_KN, TAP_GRAD = kTapGrad, TAP_CG = kTapCg };
+// is u^h with the rows b^a (one field, its dim components nn apart).  TAP_MOM
+// writes the D_q of the domain mask: the moments of Eq 49, Alg 1 (its basis has
+// twice the degree).
+enum { TAP_K = SEP_PW_K, TAP_UH = SEP_PW_UH, TAP_LOAD = SEP_PW_LOAD, TAP_KN = SEP_PW_KN, TAP_GRAD = kTapGrad, TAP_CG = kTapCg, TAP_MOM = 6 };
 
 // Monomials of degree <= DEG in DIM variables (the library's basis order), as
 // the tree the passes walk: fields after z (exponent ez), after y (ey, ez),
@@ -192,7 +194,7 @@ __device__ __forceinline__ long tap_xcd(long b, long nblocks)
 // Sizes of one variant.
 template <class B, int R, int MODE, int TX, int TY>
 struct TapGeom {
-    static constexpr bool P1 = MODE != TAP_LOAD, P2 = MODE != TAP_UH;
+    static constexpr bool P1 = MODE != TAP_LOAD, P2 = MODE != TAP_UH && MODE != TAP_MOM;
     static constexpr int RX = R, RY = B::DIM > 1 ? R : 0, RZ = B::DIM > 2 ? R : 0;
     static constexpr int HX = P2 ? RX : 0, HY = P2 ? RY : 0, HZ = P2 ? RZ : 0;
     static constexpr int XE = TX + 2 * HX, YE = TY + 2 * HY;  // where D and E are formed
@@ -278,8 +280,9 @@ struct TapMarch {
     static constexpr bool ICONST = ROWS * S <= kMaxNodeConst;  // wider row sets have no classes
     static constexpr bool A = (ROLE & 1) != 0, Bq = (ROLE & 2) != 0 && G::P2;
 
-    // x convolutions of two nodes: D[i][q] from the y-level fields
-    static __device__ __forceinline__ void x_conv(const T* sY, int yy, int gi, KP k, T (&D)[2][S])
+    // x convolutions of two nodes: put(i, q, D_q of node i) from the y-level fields
+    template <typename F>
+    static __device__ __forceinline__ void x_conv(const T* sY, int yy, int gi, KP k, F&& put)
     {
         tap_for<NY>([&](auto fc) {
             constexpr int f = decltype(fc)::value;
@@ -295,8 +298,8 @@ struct TapMarch {
                 constexpr int q = decltype(qc)::value;
                 if constexpr (B::tab.xyf[q] == f) {
                     constexpr int e = B::tab.xex[q];
-                    D[0][q] = tap_conv<R, false, e>(w, k->t[0][e]);
-                    D[1][q] = tap_conv<R, false, e>(w + 1, k->t[0][e]);
+                    put(0, q, tap_conv<R, false, e>(w, k->t[0][e]));
+                    put(1, q, tap_conv<R, false, e>(w + 1, k->t[0][e]));
                 }
             });
         });
@@ -431,13 +434,14 @@ struct TapMarch {
         std::conditional_t<CG, Tio, uint8_t> nmk[NC];
         const auto value = [&](int k) -> T {
             if constexpr (CG) return up.alpha * T(nmk[k]) + up.beta * T(nxt[k]);
+            else if constexpr (MODE == TAP_MOM) return T(nmk[k] != 0);
             else return nmk[k] ? T(nxt[k]) : T(0);
         };
         const auto fetch = [&](int z) {
             const Tio* pi = in + (long)z * nxy;
 #pragma unroll
             for (int k = 0; k < NC; ++k) {
-                nxt[k] = pi[col[k]];
+                if constexpr (MODE != TAP_MOM) nxt[k] = pi[col[k]];
                 if constexpr (CG) nmk[k] = (up.r + (long)z * nxy)[col[k]];
                 else nmk[k] = (mask_in + (long)z * nxy)[col[k]];
             }
@@ -504,8 +508,17 @@ struct TapMarch {
                         if (it < N3) {
                             const int gi = it % (XE / 2), yy = it / (XE / 2);
                             T D[2][S];
-                            if constexpr (G::P1) x_conv(sY, yy, gi, k_, D);
-                            if constexpr (MODE == TAP_UH) {
+                            if constexpr (G::P1 && MODE != TAP_MOM)
+                                x_conv(sY, yy, gi, k_, [&](int i, int q, T v) { D[i][q] = v; });
+                            if constexpr (MODE == TAP_MOM) {
+                                // pairs of monomials, as the moment solves read them; each
+                                // value leaves as it is formed (35 of them would not fit)
+                                T* o = reinterpret_cast<T*>(out) + (long)pe * nxy * 2;
+                                const bool row = y0 + yy < ny, ok[2] = {row && x0 + 2 * gi < nx, row && x0 + 2 * gi + 1 < nx};
+                                x_conv(sY, yy, gi, k_, [&](int i, int q, T v) {
+                                    if (ok[i]) (o + (long)(q / 2) * k_->nn * 2 + (q & 1))[2 * (i ? jt3[k] : it3[k])] = v;
+                                });
+                            } else if constexpr (MODE == TAP_UH) {
                                 // u = sum_p b0_p D_p (times V for V o N; Eq 94), or with
                                 // the rows b^a the implicit gradient, a field per row
                                 const T* vol = k_->vol ? k_->vol + (long)pe * nxy : nullptr;
@@ -772,7 +785,7 @@ __global__ __launch_bounds__(NT, tap_min_waves(sizeof(T), tap_lds_of<B, R, MODE,
     // planes of the chunk outside the domain's extent in this tile column are zero
     const int2 zr = kp->zr[ty * ntx + tx];
     const int zlo = min(max(za, zr.x), ze), zhi = max(zlo, min(ze, zr.y + 1));
-    if (za < zlo || zhi < ze) {
+    if (MODE != TAP_MOM && (za < zlo || zhi < ze)) {
         for (int i = tid; i < TX * TY; i += NT) {
             const int x = x0 + i % TX, y = y0 + i / TX;
             if (x < nx && y < ny) {
@@ -828,7 +841,7 @@ void tap_go(const TapArgs<T>& a, dim3 grid, bool small, hipStream_t st)
             return;
         }
     }
-    constexpr int TX = tap_tile_x(B::DIM, B::DEG, R, false), TY = tap_tile_y(B::DIM, false);
+    constexpr int TX = tap_tile_x(B::DIM, MODE == TAP_MOM ? B::DEG / 2 : B::DEG, R, false), TY = tap_tile_y(B::DIM, false);
     constexpr int NT = tap_threads(B::DIM, false);
     hipLaunchKernelGGL((k_tap<T, Tio, B, R, MODE, ROWS, TX, TY, NT>), grid, dim3(NT), 0, st, a);
 }

@@ -23,7 +23,7 @@ ROOT = os.path.dirname(HERE)
 SOURCES = ["csrc/regpass.hip", "csrc/sepconv.hip", "csrc/kernels.hip", "csrc/fcrkpm.hip",
            "csrc/fcrkpm_impl.hpp", "csrc/fft_core.hpp", "csrc/tapconv.hpp", "csrc/tap_list.hpp",
            "csrc/tapconv.hip", "csrc/tap_f32.hip", "csrc/tap_f64.hip", "csrc/tap_f64n.hip", "csrc/tap_mix.hip",
-           "csrc/tap_cg32.hip", "csrc/tap_cg64.hip"]
+           "csrc/tap_cg32.hip", "csrc/tap_cg64.hip", "csrc/tap_mom.hip"]
 COPY_BYTES = 256 << 20
 
 # demangled kernel name -> the kind name the library's sampler reports; the

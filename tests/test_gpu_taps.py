@@ -193,3 +193,39 @@ def test_uh_over_d():
                                        None, C.c_void_p(torch.cuda.current_stream().cuda_stream))
     assert st == f.OK
     assert torch.equal(d, uh)
+
+
+def test_fft_passes_are_set_up_when_first_asked_for():
+    """A context on the direct kernels prepares nothing of the FFT passes.  The
+    options that describe or choose them do, for every operator set built so
+    far, and the products on either side agree (also the allocation-free ones,
+    which must find everything in place)."""
+    f = fc()
+    h, chi, dirichlet, vol = domain((48, 48, 48), 2.5, "box")
+    g = f.Problem((48,) * 3, h, (2.5,) * 3, 1, chi, dirichlet, vol, device="cuda:0")
+    x = torch.from_numpy(np.random.default_rng(6).standard_normal(chi.shape)).to(DEV)
+    direct = {op: g.apply(op, x) for op in ("K", "M", "UH", "FR")}
+    g.set_option(f.OPT_TAPS, 0)
+    out = torch.empty_like(x)
+    for op, ref in direct.items():
+        fft = g.apply_noalloc(op, x, out) if op in ("K", "M") else g.apply(op, x)
+        assert float((fft - ref).abs().max() / ref.abs().max()) <= 1e-12, op
+    g.set_option(f.OPT_TAPS, 1)
+    for op, ref in direct.items():
+        assert torch.equal(g.apply(op, x), ref), op
+
+
+@pytest.mark.parametrize("dims,at,kind,degree", [c + (1,) for c in STIFFNESS[:6]] + OTHER_BASES[4:] + [
+    ((20, 18, 16), 3.5, "box", 2)])
+def test_coefficients(dims, at, kind, degree):
+    """b^0 and b^a from the moments that the direct kernels sum (Alg 1)."""
+    if kind == "periodic":
+        pytest.skip("the oracle's neighbourhoods do not wrap around")
+    print(f"\n[taps moments] {dims} support {at} {kind} degree {degree}", flush=True)
+    g, o, chi, free = make(dims, at, degree, kind)
+    m = chi > 0
+    # the moment solves amplify rounding by the condition of the moment
+    # matrices, up to about 1e5 for these bases and supports
+    check(g.coeffs("b0").cpu().numpy()[:, m], o.b0()[:, m], 1e-10, "b0")
+    ba = o.balpha()
+    check(g.coeffs("balpha").cpu().numpy()[:, :, m], ba[:, :, m], 1e-10, "balpha")
