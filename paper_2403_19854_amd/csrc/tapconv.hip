@@ -19,8 +19,6 @@ struct TapSet {
     double* rec64 = nullptr;
     float m32[kTapMint] = {};
     double m64[kTapMint] = {};
-};  // per tile a bit per plane whose E level is interior throughout (large, small tile)
-    double dint[3] = {};
 };
 
 void tap_check(hipError_t e)
