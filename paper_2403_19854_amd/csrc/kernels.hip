@@ -473,7 +473,7 @@ __global__ __launch_bounds__(kRedThreads) void k_cg_xr(T* __restrict__ x, T* __r
 {
     __shared__ double sh[16];
     const int j = blockIdx.y;
-    if (!act[j]) return;
+    const int live = act[j];
     const long off = j * n;
     x += off;
     r += off;
@@ -482,8 +482,9 @@ __global__ __launch_bounds__(kRedThreads) void k_cg_xr(T* __restrict__ x, T* __r
     scal += j * kScal;
     const long stride = (long)gridDim.x * blockDim.x;
     const long first = blockIdx.x * (long)blockDim.x + threadIdx.x;
-    // the partials of p.q, then the thread's first kPre chunks are loaded
-    // before the reduction, so the chunks' latency overlaps it
+    // the flag, r.r, the partials of p.q, then the thread's first kPre chunks
+    // are loaded before the reduction, so their latency overlaps it
+    const double rr = scal[parity];
     Partials pp;
     pp.load(pq_part + (long)j * kRedBlocks);
     Vec4<T> xs[kPre], rs[kPre], ps[kPre], qs[kPre];
@@ -499,8 +500,8 @@ __global__ __launch_bounds__(kRedThreads) void k_cg_xr(T* __restrict__ x, T* __r
             }
         }
     }
+    if (!live) return;
     const double pq = pp.sum(npq, sh);
-    const double rr = scal[parity];
     const bool good = pq > 0.0 && rr > 0.0;
     const T alpha = good ? T(rr / pq) : T(0);
     if (!good && blockIdx.x == 0 && threadIdx.x == 0 && rr > 0.0) scal[3] = 1.0;

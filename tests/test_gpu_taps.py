@@ -229,3 +229,40 @@ def test_coefficients(dims, at, kind, degree):
     check(g.coeffs("b0").cpu().numpy()[:, m], o.b0()[:, m], 1e-10, "b0")
     ba = o.balpha()
     check(g.coeffs("balpha").cpu().numpy()[:, :, m], ba[:, :, m], 1e-10, "balpha")
+
+
+INTERIOR = [
+    ((96, 72, 40), 2.5, "box", 1), ((72, 56, 70), 1.5, "ball", 1), ((75, 60, 36), 3.5, "box", 1),
+    ((64, 48, 40), 2.0, "periodic", 1), ((72, 56, 40), 3.0, "ball", 2), ((64, 48, 36), 3.5, "box", 2),
+    ((160, 96), 2.5, "ball", 1), ((160, 96), 3.0, "box", 2), ((128, 100), 4.0, "box", 3),
+    ((540,), 2.5, "box", 1), ((400,), 3.0, "inside", 2),
+]
+
+
+@pytest.mark.parametrize("dims,at,kind,degree", INTERIOR)
+def test_interior_planes(dims, at, kind, degree):
+    """Uniform volumes: the interior nodes share a record that needs the
+    first-degree monomials alone (waves that hold no others take it from the
+    kernel arguments).  One right-hand side and eight (they may differ in the tile), the
+    product and the fused CG, against the FP64 FFT passes."""
+    print(f"\n[taps interior] {dims} support {at} {kind} degree {degree}", flush=True)
+    f = fc()
+    h, chi, dirichlet, _ = domain(dims, at, kind)
+    vol = np.where(chi > 0, np.prod(h), 0.0)
+    g = f.Problem(dims, h, (at,) * len(dims), degree, chi, dirichlet, vol, device="cuda:0")
+    x = np.random.default_rng(7).standard_normal((8,) + chi.shape)
+    xt = torch.from_numpy(x).to(DEV)
+    rhs = torch.from_numpy(np.where(chi > dirichlet, x[0], 0.0)).to(DEV)
+    # three iterations of CG: an outlying eigenvalue (the quadratic basis in 1D
+    # has one eight times the next) makes rounding grow about 25 times in each
+    cg = lambda: g.solve(rhs, tol=1e-14, maxit=3, raise_on_noconv=False)[0].cpu().numpy()
+    g.set_option(f.OPT_TAPS, 0)
+    ref = g.apply("K", xt).cpu().numpy()
+    dref = cg()
+    g.set_option(f.OPT_TAPS, 1)
+    for dtype, tol in ((torch.float64, 1e-12), (torch.float32, 2e-5)):
+        got = g.apply("K", xt.to(dtype)).cpu().numpy()
+        check(got.astype(np.float64), ref, tol, f"K of eight {dtype}")
+        one = g.apply("K", xt[3].to(dtype)).cpu().numpy()
+        check(one.astype(np.float64), ref[3], tol, f"K of one {dtype}")
+    check(cg(), dref, 1e-10, "three iterations")
