@@ -1079,6 +1079,7 @@ struct Solver {
     int it = 0;           // iterations in the current phase
     int it_base = 0;      // iterations spent before the current phase
     int parity = 0;       // slot of r.r the next iteration reads
+    bool pending = false;  // the last block left its direction update to the next product
     int parity_of[2] = {0, 0};
     std::vector<RhsState> R;
     hipEvent_t join = nullptr;
@@ -1221,21 +1222,45 @@ struct Solver {
         set_flags(st);
     }
 
+    // the direct product takes the direction update over from the block before
+    bool carries(int nb)
+    {
+        if (nb % 2) return false;
+        if (ph == PH_F64) return tap_serves_k<double, double>(c);
+        return mode == FCRKPM_MODE_F32_REFINED && tap_serves_k<float, float>(c);
+    }
+
+    // a pending direction update, on its own (before r is replaced)
+    void settle(hipStream_t st)
+    {
+        if (!pending) return;
+        pending = false;
+        double* rr_part = c.partial + (size_t)kRedBlocks * c.cap_rhs;
+        if (ph == PH_F64)
+            launch_cg_p<double>(vec64(c, V_P), vec64(c, V_P), vec64(c, V_R), c.nn, nrhs, rr_part, c.scal, parity ^ 1,
+                                c.act, st);
+        else
+            launch_cg_p<float>(vec32(c, 2), vec32(c, 2), vec32(c, 1), c.nn, nrhs, rr_part, c.scal, parity ^ 1, c.act,
+                               st);
+    }
+
     // kCheck (or fewer) iterations of the current phase: kernel launches only,
     // so the block can be captured into a graph and replayed
     void enqueue(int nb, hipStream_t st)
     {
         int par = parity;
-        // within a block the direction update of iteration i runs in the product
-        // of iteration i+1; the block ends with it applied.  The direct product
-        // takes the direction from one array to another: it alternates between
-        // two and the block ends in the first.
+        // the direction update of iteration i runs in the product of iteration
+        // i+1, that of the last one at the block's end, or in the next block where
+        // that is sure to start with the same arrays (carries).  The direct
+        // product takes the direction from one array to another: it alternates
+        // between two and the block ends in the first.
+        const bool carry = carries(nb);
         if (ph == PH_F64) {
             const bool fused = fused_cg<double, double>(c, nrhs);
             double* v[2] = {vec64(c, V_P), vec64(c, fused ? V_T : V_P)};
             for (int i = 0; i < nb; ++i, par ^= 1)
                 cg_iteration<double>(c, vec64(c, V_X), vec64(c, V_R), v[i & 1], vec64(c, V_Q), nrhs, par, st, fused,
-                                     fused && i > 0, i == nb - 1, v[~i & 1], v[0]);
+                                     fused && (i > 0 || pending), i == nb - 1 && !carry, v[~i & 1], v[0]);
             return;
         }
         const bool fused = mode == FCRKPM_MODE_F32_REFINED && fused_cg<float, float>(c, nrhs);
@@ -1243,7 +1268,7 @@ struct Solver {
         for (int i = 0; i < nb; ++i, par ^= 1) {
             if (mode == FCRKPM_MODE_F32_REFINED)
                 cg_iteration<float, float>(c, vec32(c, 0), vec32(c, 1), v[i & 1], vec32(c, 3), nrhs, par, st, fused,
-                                           i > 0, i == nb - 1, v[~i & 1], v[0]);
+                                           i > 0 || pending, i == nb - 1 && !carry, v[~i & 1], v[0]);
             else
                 cg_iteration<double, float>(c, vec64(c, V_T), vec64(c, V_R), vec64(c, V_P),
                                             vec64(c, V_Q), nrhs, par, st);
@@ -1253,6 +1278,7 @@ struct Solver {
     // bookkeeping of an enqueued block
     void advance(int nb)
     {
+        pending = carries(nb);
         it += nb;
         parity ^= (nb & 1);
         for (auto& s : R)
@@ -1265,8 +1291,8 @@ struct Solver {
 
     void post(int slot, hipStream_t st)
     {
-        HIPCHK(hipMemcpyAsync(c.hscal + (size_t)slot * kScal * c.cap_rhs, c.scal,
-                              sizeof(double) * kScal * nrhs, hipMemcpyDeviceToHost, st));
+        launch_cg_post(c.partial + (size_t)kRedBlocks * c.cap_rhs, pending ? red_blocks(c.nn) : 0, c.scal, parity,
+                       nrhs, c.act, c.hscal + (size_t)slot * kScal * c.cap_rhs, st);
         parity_of[slot] = parity;
     }
 
@@ -1309,6 +1335,7 @@ struct Solver {
         if (!any_want && !last) return;
         const long nn = c.nn;
         if (ph == PH_REFINED) {
+            settle(st);
             for (int j = 0; j < nrhs; ++j) {
                 RhsState& s = R[j];
                 if (!s.active) continue;
@@ -1557,7 +1584,11 @@ void run_solvers_on(const std::vector<Solver*>& all, bool graphs, hipStream_t st
             int nb = kCheck;
             for (Solver* s : act) nb = std::min(nb, s->phase_maxit() - s->it);
             nb = std::max(nb, 1);
-            if (graphs && nb == kCheck) {
+            // a graph is kept for the blocks that repeat: not for the first one
+            // after a start, which has no update to take over
+            bool repeats = nb == kCheck;
+            for (Solver* s : act) repeats = repeats && (s->pending || !s->carries(nb));
+            if (graphs && repeats) {
                 std::vector<std::pair<Solver*, int>> key;
                 for (Solver* s : act) key.emplace_back(s, (int)s->ph * 2 + s->parity);
                 if (key != gkey || !ge) {

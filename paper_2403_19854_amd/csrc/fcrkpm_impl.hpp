@@ -402,6 +402,8 @@ void launch_cg_xr(T* x, T* r, const T* p, const T* q, long n, int nrhs, const do
 template <typename T>
 void launch_cg_p(T* p, const T* p_old, const T* r, long n, int nrhs, const double* rr_part, double* scal,
                  int parity, const int* act, hipStream_t st);
+void launch_cg_post(const double* rr_part, int nb, double* scal, int idx, int nrhs, const int* act, double* host,
+                    hipStream_t st);
 void launch_set_scalar(double* scal, int idx, double v, int nrhs, hipStream_t st);
 void launch_set_flag(int* act, int j, int v, hipStream_t st);
 template <typename T>

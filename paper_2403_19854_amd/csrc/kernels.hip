@@ -619,6 +619,34 @@ void launch_cg_p(T* p, const T* p_old, const T* r, long n, int nrhs, const doubl
                        rr_part, scal, parity, act);
 }
 
+// The end of a block of iterations: the new r.r from its partials (nb of them,
+// 0: none is due) into scal[idx], and the scalars to pinned host memory.  One
+// launch in place of the direction update (which the next product does) and a
+// copy: 2.4 us against 8 at 48^3.
+__global__ __launch_bounds__(kRedThreads) void k_cg_post(const double* __restrict__ rr_part, int nb, double* scal,
+                                                         int idx, const int* __restrict__ act,
+                                                         double* __restrict__ host)
+{
+    __shared__ double sh[16];
+    const int j = blockIdx.x, t = threadIdx.x;
+    const bool due = nb > 0 && act[j];
+    scal += j * kScal;
+    double v = t < kScal ? scal[t] : 0.0;
+    if (due) {
+        Partials pp;
+        pp.load(rr_part + (long)j * kRedBlocks);
+        const double rr = pp.sum(nb, sh);
+        if (t == idx) scal[t] = v = rr;
+    }
+    if (t < kScal) host[j * kScal + t] = v;
+}
+
+void launch_cg_post(const double* rr_part, int nb, double* scal, int idx, int nrhs, const int* act, double* host,
+                    hipStream_t st)
+{
+    hipLaunchKernelGGL(k_cg_post, dim3(nrhs), dim3(kRedThreads), 0, st, rr_part, nb, scal, idx, act, host);
+}
+
 template void launch_dot_partial<double>(const double*, const double*, long, int, double*,
                                          const int*, hipStream_t);
 template void launch_dot_partial<float>(const float*, const float*, long, int, double*,

@@ -266,3 +266,47 @@ def test_interior_planes(dims, at, kind, degree):
         one = g.apply("K", xt[3].to(dtype)).cpu().numpy()
         check(one.astype(np.float64), ref[3], tol, f"K of one {dtype}")
     check(cg(), dref, 1e-10, "three iterations")
+
+
+@pytest.mark.parametrize("dims,at", [((30, 24, 20), 2.5), ((72, 64, 48), 2.0), ((90, 80), 2.5), ((300,), 2.5)])
+@pytest.mark.parametrize("maxit", [1, 7, 8, 9, 16, 22])
+def test_cg_blocks(dims, at, maxit):
+    """CG runs in blocks of eight iterations whose last direction update the next
+    block takes over; a shorter block ends the solve.  The iterates are those of
+    the FFT passes whatever the count (one right-hand side of the batch is done
+    at the start).  How much rounding grows from iteration to iteration depends
+    on the spectrum (1D has an outlying eigenvalue): the bar is four times what
+    noise of a few roundings in each product makes of plain CG in the precision
+    of the mode."""
+    print(f"\n[taps blocks] {dims} {maxit} iterations", flush=True)
+    f = fc()
+    h, chi, dirichlet, _ = domain(dims, at, "box")
+    vol = np.where(chi > 0, np.prod(h), 0.0)
+    g = f.Problem(dims, h, (at,) * len(dims), 1, chi, dirichlet, vol, device="cuda:0")
+    r = np.where(chi > dirichlet, np.random.default_rng(8).standard_normal(chi.shape), 0.0)
+    rt = torch.from_numpy(np.stack([r, 0.0 * r, 2.0 * r])).to(DEV)
+
+    def plain(eps, dtype):
+        gen = torch.Generator(device=DEV).manual_seed(9)
+        x, res = torch.zeros_like(rt[0], dtype=dtype), rt[0].to(dtype)
+        p, rr = res.clone(), (res * res).sum()
+        for _ in range(maxit):
+            q = g.apply("K", p)
+            q += eps * q.abs().max() * (q != 0) * torch.randn(q.shape, generator=gen, device=DEV, dtype=q.dtype)
+            alpha = rr / (p * q).sum()
+            x, res = x + alpha * p, res - alpha * q
+            p, rr = res + (res * res).sum() / rr * p, (res * res).sum()
+        return x.double()
+
+    g.set_option(f.OPT_TAPS, 0)
+    exact = plain(0.0, torch.float64)
+    for mode, eps, dtype in (("f64", 4e-15, torch.float64), ("f32_refined", 1e-6, torch.float32)):
+        g.set_option(f.OPT_TAPS, 0)
+        bar = 10 * eps + 4 * float((plain(eps, dtype) - exact).abs().max() / exact.abs().max())
+        d = {}
+        for taps in (0, 1):
+            g.set_option(f.OPT_TAPS, taps)
+            d[taps] = g.solve(rt, tol=1e-14, maxit=maxit, mode=mode, raise_on_noconv=False)[0].cpu().numpy()
+        assert np.all(d[1][1] == 0.0)
+        check(d[1][0], d[0][0], bar, f"{mode}")
+        np.testing.assert_array_equal(d[1][2], 2.0 * d[1][0])
