@@ -79,16 +79,20 @@ void launch_axis_extent(const Ctx& c, const uint8_t* chi, int* occ, hipStream_t 
 __device__ __forceinline__ bool full_support(const uint8_t* __restrict__ chi, long I, int n0, int n1,
                                              int n2, int m0, int m1, int m2)
 {
-    const int i0 = (int)(I % n0);
-    const long r = I / n0;
-    const int i1 = (int)(r % n1), i2 = (int)(r / n1);
+    // (a box holds fewer than 2^31 nodes)
+    const uint32_t r = (uint32_t)I / (uint32_t)n0;
+    const int i0 = (int)((uint32_t)I - r * n0), i2 = (int)(r / (uint32_t)n1), i1 = (int)(r - (uint32_t)i2 * n1);
+    // the offsets wrap at most once (the support fits the box); a row's values
+    // are read together and tested once
+    const auto wrap = [](int i, int n) { return i < 0 ? i + n : i >= n ? i - n : i; };
     for (int o2 = -m2; o2 <= m2; ++o2) {
-        const int j2 = (i2 + o2 + n2) % n2;
+        const int j2 = wrap(i2 + o2, n2);
         for (int o1 = -m1; o1 <= m1; ++o1) {
-            const int j1 = (i1 + o1 + n1) % n1;
-            const long row = ((long)j2 * n1 + j1) * n0;
-            for (int o0 = -m0; o0 <= m0; ++o0)
-                if (!chi[row + (i0 + o0 + n0) % n0]) return false;
+            const uint8_t* row = chi + ((long)j2 * n1 + wrap(i1 + o1, n1)) * n0;
+            bool all = true;
+#pragma unroll 4
+            for (int o0 = -m0; o0 <= m0; ++o0) all = all & (row[wrap(i0 + o0, n0)] != 0);
+            if (!all) return false;
         }
     }
     return true;
@@ -97,14 +101,17 @@ __device__ __forceinline__ bool full_support(const uint8_t* __restrict__ chi, lo
 __global__ void k_first_interior(const uint8_t* __restrict__ chi, int n0, int n1, int n2, int m0,
                                  int m1, int m2, long nn, int* ref)
 {
-    // one atomic per wave: with one per interior node this took 118 us at 80^3
+    // one atomic per wave
     int first = 0x7fffffff;
     for (long I = blockIdx.x * (long)blockDim.x + threadIdx.x; I < nn;
-         I += (long)gridDim.x * blockDim.x)
+         I += (long)gridDim.x * blockDim.x) {
+        // (a node found meanwhile ends the search beyond it)
+        if (I > *(volatile int*)ref) break;
         if (chi[I] && full_support(chi, I, n0, n1, n2, m0, m1, m2)) {
             first = (int)I;
             break;
         }
+    }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) first = min(first, __shfl_xor(first, o, 64));
     if ((threadIdx.x & 63) == 0 && first != 0x7fffffff) atomicMin(ref, first);
@@ -112,7 +119,9 @@ __global__ void k_first_interior(const uint8_t* __restrict__ chi, int n0, int n1
 
 void launch_first_interior(const Ctx& c, int* ref, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_first_interior, dim3(ew_blocks(c.nn)), dim3(256), 0, st, c.chi, c.n[0],
+    // a round of 256 blocks covers 65536 nodes, so most of a box is never looked
+    // at (80^3: 118 -> 45 us)
+    hipLaunchKernelGGL(k_first_interior, dim3(std::min(ew_blocks(c.nn), 256u)), dim3(256), 0, st, c.chi, c.n[0],
                        c.n[1], c.n[2], c.m[0], c.m[1], c.m[2], c.nn, ref);
 }
 
@@ -136,13 +145,20 @@ __global__ void k_node_class(const uint8_t* __restrict__ chi, const double* __re
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) count += __shfl_xor(count, o, 64);
-    if ((threadIdx.x & 63) == 0 && count) atomicAdd(nclass2, (unsigned long long)count);
+    // one atomic per block of at most 1024: one per wave were 5000 on an address
+    // (80^3: 106 -> 50 us)
+    __shared__ unsigned sum;
+    if (threadIdx.x == 0) sum = 0;
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0 && count) atomicAdd(&sum, count);
+    __syncthreads();
+    if (threadIdx.x == 0 && sum) atomicAdd(nclass2, (unsigned long long)sum);
 }
 
 void launch_node_class(const Ctx& c, const NodeConst& ref, uint8_t* cls, unsigned long long* n2,
                        hipStream_t st)
 {
-    hipLaunchKernelGGL(k_node_class, dim3(ew_blocks(c.nn)), dim3(256), 0, st, c.chi, c.ba_64,
+    hipLaunchKernelGGL(k_node_class, dim3(std::min(ew_blocks(c.nn), 1024u)), dim3(256), 0, st, c.chi, c.ba_64,
                        c.vol64, c.krows * c.s, ref, c.n[0], c.n[1], c.n[2], c.m[0], c.m[1], c.m[2],
                        c.nn, cls, n2);
 }
@@ -622,7 +638,7 @@ void launch_cg_p(T* p, const T* p_old, const T* r, long n, int nrhs, const doubl
 // The end of a block of iterations: the new r.r from its partials (nb of them,
 // 0: none is due) into scal[idx], and the scalars to pinned host memory.  One
 // launch in place of the direction update (which the next product does) and a
-// copy: 2.4 us against 8 at 48^3.
+// copy, 4.1 and 3.3 us: 48^3 FP32 20.4 -> 19.9 us an iteration, 300^2 13.9 -> 13.5.
 __global__ __launch_bounds__(kRedThreads) void k_cg_post(const double* __restrict__ rr_part, int nb, double* scal,
                                                          int idx, const int* __restrict__ act,
                                                          double* __restrict__ host)

@@ -25,6 +25,15 @@
 //
 // Every buffer is written in one half and read in the other, so one copy of
 // each and two barriers per plane suffice.
+//
+// What bounds it: the vector pipes on large boxes (256^3 FP32: 224 lane
+// operations per node issued, 72% of the issue slots; about 145 of them are taps
+// with the halo of a 32 x 16 tile and the run-in of a chunk; LDS active 49% of
+// the time), the chain of steps on small ones (32^3: 7 steps of about 0.6 us
+// after 2-3 us of launch and first loads).  A K product, linear basis, R = 2,
+// against the five FFT passes: 32^3 FP32 9.5 us (28.8), 128^3 FP32 31 (55) and
+// FP64 46 (107), 256^3 FP32 132 (362), 32 right-hand sides of 96^3 214 (552);
+// quadratic ball of 128^3, R = 2, FP32 60 (181).
 #pragma once
 #include <hip/hip_runtime.h>
 
