@@ -145,13 +145,15 @@ fcrkpm_status fcrkpm_setup(const fcrkpm_grid* grid, const uint8_t* mask, int32_t
  *
  *   op      FCRKPM_OP_*
  *   dtype   FCRKPM_F64 (in/out are double*) or FCRKPM_F32 (float*): the
- *           precision of the FFT products and pointwise arithmetic
+ *           precision of the convolutions and pointwise arithmetic
  *   nrhs    number of fields; field j starts at j * (nodes) in `in` and `out`
  *   in,out  device arrays; must not overlap
  *
  * The kernel is a tensor product (Eq 6), so every 3D spectral product of
  * Alg 2-4 is separable: instead of the paper's 3D transforms (2(s+1) per
- * field for K, s+1 for FR, UH, NT, VN) each operator runs as line passes.  In
+ * field for K, s+1 for FR, UH, NT, VN) each operator runs axis by axis.  Where
+ * the kernel reaches at most 3 nodes (ceil(support) - 1) one launch sums all of
+ * it directly (FCRKPM_OPT_TAPS); beyond, each operator runs as FFT line passes.  In
  * 3D: part-1 passes along x and y (d -> its x-convolutions -> their
  * y-convolutions), one middle pass along z (the part-1 z-convolutions, the
  * pointwise stage and the part-2 z-convolutions, without leaving the chip),
@@ -167,9 +169,10 @@ fcrkpm_status fcrkpm_apply(fcrkpm_ctx* ctx, int32_t op, int32_t dtype, int32_t n
  * fcrkpm_apply_noalloc -- fcrkpm_apply for callers that cannot allocate device
  * memory (work under HIP graph capture, tight serving loops, harnesses that
  * forbid hipMalloc): the same operators, arguments, results and errors, but
- * the passes keep their intermediate fields in a static scratch array of
+ * the FFT passes keep their intermediate fields in a static scratch array of
  * 64 MiB that every GPU the library runs on holds until the process ends,
- * instead of the context's workspace.  The call allocates nothing.
+ * instead of the context's workspace.  The call allocates nothing.  (The direct
+ * sums of short supports need no scratch; the limit below holds for every call.)
  *
  * Scratch need: 2 x (pair fields of the widest intermediate set) x nodes x
  * nrhs complex values, 8 bytes each in FP32 and 16 in FP64 -- for the linear
@@ -473,11 +476,15 @@ enum {
                                  DFT-6 first stage), 1 = 8 lanes; at 256 points
                                  layout 0 = 16 lanes x 16 points, 1 = 32 lanes x 8 points;
                                  tiles = 1 or 2 tiles per workgroup (64 and 128 points; the
-                                 second tile's loads overlap the first tile's work).  Setup
-                                 times a K product with each variant and keeps the fastest.
+                                 second tile's loads overlap the first tile's work).  The
+                                 library times a K product with each variant and keeps the
+                                 fastest: at setup where FFT passes serve the products (or
+                                 FCRKPM_AUTOTUNE_CACHE is set), else when the FFT passes are
+                                 first asked for: the first read or set of an option that
+                                 describes them, OPT_TAPS 0 (synchronous).
                                  FP64 products use the 16-lane layout at 80 and 96 points and
                                  the 32-lane one at 256. */
-    FCRKPM_OPT_TUNE_NS0 = 4, /* read only: setup's time of one K product with variant 0, ns */
+    FCRKPM_OPT_TUNE_NS0 = 4, /* read only: the time of one K product with variant 0, ns */
     FCRKPM_OPT_TUNE_NS1 = 5, /* read only: the same with variant 1 (0 where not timed) */
     FCRKPM_OPT_TUNE_NS2 = 6, /* read only: the same with variant 2 */
     FCRKPM_OPT_TUNE_NS3 = 7, /* read only: the same with variant 3 */
@@ -490,9 +497,9 @@ enum {
                                 stage at every node.  Reads 1 only where setup found the
                                 structure. */
     FCRKPM_OPT_SEP_LINES32 = 9,  /* LDS-tiled passes, FP32: most lines per workgroup (16, 8, 4) */
-    FCRKPM_OPT_SEP_LINES64 = 10, /* the same for FP64.  Setup times K products with each on the
-                                    precisions that run on these passes and keeps the fastest. */
-    FCRKPM_OPT_TUNE_CACHED = 11, /* read only: 1 if setup took its tuning choices from the file
+    FCRKPM_OPT_SEP_LINES64 = 10, /* the same for FP64.  K products are timed with each on the
+                                    precisions that run on these passes, the fastest is kept. */
+    FCRKPM_OPT_TUNE_CACHED = 11, /* read only: 1 if the tuning choices came from the file
                                     named by FCRKPM_AUTOTUNE_CACHE (keyed by device, box, basis
                                     and support) instead of timing; new choices are appended to
                                     that file */
