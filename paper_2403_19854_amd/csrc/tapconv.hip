@@ -352,6 +352,16 @@ void tap_build(Ctx& c, hipStream_t st)
     tap_check(hipStreamSynchronize(st));
 }
 
+// Workgroups of a row of the grid, a multiple of eight so that tap_xcd orders
+// every grid: those beyond the last chunk start past the last plane and find
+// nothing to do (without: 8 right-hand sides of 80^3 FP32 56.1 us against 51.4, of
+// 48^3 FP64 34.7 against 30.4, 32 of 96^3 FP64 455 against 434).
+static unsigned tap_grid(const Ctx& c, int ntx, int nty, int cz)
+{
+    const long n = (long)ntx * nty * ((c.n[2] + cz - 1) / cz);
+    return (unsigned)((n + 7) / 8 * 8);
+}
+
 // what every launch passes
 template <typename T>
 static TapArgs<T> tap_args(const Ctx& c)
@@ -376,7 +386,7 @@ void launch_tap_moments(const Ctx& c, cplx<double>* G, hipStream_t st)
     a.nty = c.tap_nt[0][1];
     a.cz = a.cu = cut.cz;
     a.zr = c.tap_zr[0];
-    const dim3 grid((unsigned)((long)a.ntx * a.nty * ((c.n[2] + a.cz - 1) / a.cz)));
+    const dim3 grid(tap_grid(c, a.ntx, a.nty, a.cz));
     bool done = false;
 #define FC_TAP_CASE(T_, TIO_, DIM, DEG, R, MODE, ROWS)                            \
     if (!done && c.dim == DIM && 2 * c.degree == DEG && c.tap_r == R) {           \
@@ -431,7 +441,7 @@ void launch_tap(const Ctx& c, int mode, const Tio* in, Tio* out, const uint8_t* 
     a.vol = vol;
     a.kappa = (T)c.pw_kappa;
     a.rb = c.nn * (long)sizeof(Tio) * (mode == TAP_GRAD ? c.dim : 1);
-    const dim3 grid((unsigned)((long)a.ntx * a.nty * ((c.n[2] + a.cz - 1) / a.cz)), (unsigned)nrhs);
+    const dim3 grid(tap_grid(c, a.ntx, a.nty, a.cz), (unsigned)nrhs);
     // the linear bases keep M, whatever the rows it was made of
     const int rows = mode == TAP_K || mode == TAP_CG ? (c.degree > 1 ? c.krows : c.dim) : mode == TAP_KN || mode == TAP_GRAD ? c.dim : 1;
     const int kmode = mode == TAP_GRAD ? TAP_UH : mode;
