@@ -614,25 +614,17 @@ void tap_k(Ctx& c, const Tio* in, Tio* out, const uint8_t* mask, int nrhs, hipSt
     launch_tap<T, Tio>(c, cg ? kTapCg : SEP_PW_K, in, out, mask, mask, nullptr, nullptr, nrhs, st, cg);
 }
 
-// Whether a K-type product runs on the direct kernels.  They do at most half
-// the work of the FFT passes for radii 1 and 2; at R = 3 the linear basis on a
-// 128^3 box is faster on the FP32 register path (60.6 us against 70.8; 64^3:
-// 35.5 against 28.0, and FP64 356 against 82.6).
-template <typename T, typename Tio>
-bool tap_serves_k(const Ctx& c)
-{
-    if (!tap_active(c)) return false;
-    if (std::is_same_v<T, float> && std::is_same_v<Tio, float> && c.degree == 1 && c.tap_r == 3 && c.n[0] == 128)
-        return !use_reg_path(c, 1);
-    return true;
-}
-
 // slots per right-hand side of the p.q partials of a last pass or a direct
 // product with more workgroups than kRedBlocks
 long wide_slots(const Ctx& c) { return std::max(reg_dot_slots(c), tap_dot_slots(c)); }
 
-// Whether any K product of this context runs on FFT passes.
-bool fft_needed(const Ctx& c) { return !tap_serves_k<float, float>(c) || !tap_serves_k<double, double>(c); }
+// Whether the K-type product in use runs on FFT passes.  The direct kernels
+// serve every basis, radius and precision that has one (tap_served: a rule on
+// the geometry alone): no box or type measured faster on the FFT passes.  The
+// closest is the FP32 linear product with R = 3 on the 128-point register path:
+// 49.1 us direct against 58.7, 116 against 169 for four right-hand sides, 78
+// against 98 an iteration of CG (128^3).
+bool fft_needed(const Ctx& c) { return !tap_active(c); }
 
 void build_pointwise(Ctx& c, hipStream_t st);
 void fft_tables(Ctx& c, hipStream_t st);
@@ -730,12 +722,11 @@ constexpr int OP_KN = 100;
 template <typename T, typename Tio>
 bool tap_apply(Ctx& c, int op, const Tio* in, Tio* out, int nrhs, hipStream_t st)
 {
+    if (!tap_active(c)) return false;
     if (op == FCRKPM_OP_K || op == FCRKPM_OP_K_FULL || (op == OP_KN && c.pw_kappa == 0.0)) {
-        if (!tap_serves_k<T, Tio>(c)) return false;
         tap_k<T, Tio>(c, in, out, op == FCRKPM_OP_K ? c.freem : c.chi, nrhs, st);
         return true;
     }
-    if (!tap_active(c)) return false;
     if constexpr (std::is_same_v<T, Tio>) {
         const double nn = (double)c.nn * nrhs, rt = sizeof(T);
         switch (op) {
@@ -952,7 +943,7 @@ template <typename T, typename TP>
 bool fused_cg(Ctx& c, int nrhs)
 {
     if constexpr (!std::is_same_v<T, TP>) return false;
-    else if (tap_serves_k<T, T>(c)) return true;
+    else if (tap_active(c)) return true;
     else return std::is_same_v<T, float> && use_reg_path(c, nrhs);
 }
 
@@ -971,7 +962,7 @@ void cg_iteration(Ctx& c, T* x, T* r, T* p, T* q, int nrhs, int parity, hipStrea
     double* rr_part = c.partial + (size_t)kRedBlocks * c.cap_rhs;
     int npq = red_blocks(c.nn);
     bool direct = false;
-    if constexpr (std::is_same_v<T, TP>) direct = tap_serves_k<T, T>(c);
+    if constexpr (std::is_same_v<T, TP>) direct = tap_active(c);
     if (direct) {
         // the direct product leaves the p.q partials (in the wide slots, summed
         // to one, when they outnumber kRedBlocks)
@@ -1226,8 +1217,8 @@ struct Solver {
     bool carries(int nb)
     {
         if (nb % 2) return false;
-        if (ph == PH_F64) return tap_serves_k<double, double>(c);
-        return mode == FCRKPM_MODE_F32_REFINED && tap_serves_k<float, float>(c);
+        if (ph == PH_F64) return tap_active(c);
+        return mode == FCRKPM_MODE_F32_REFINED && tap_active(c);
     }
 
     // a pending direction update, on its own (before r is replaced)
@@ -1264,7 +1255,7 @@ struct Solver {
             return;
         }
         const bool fused = mode == FCRKPM_MODE_F32_REFINED && fused_cg<float, float>(c, nrhs);
-        float* v[2] = {vec32(c, 2), vec32(c, fused && tap_serves_k<float, float>(c) ? 4 : 2)};
+        float* v[2] = {vec32(c, 2), vec32(c, fused && tap_active(c) ? 4 : 2)};
         for (int i = 0; i < nb; ++i, par ^= 1) {
             if (mode == FCRKPM_MODE_F32_REFINED)
                 cg_iteration<float, float>(c, vec32(c, 0), vec32(c, 1), v[i & 1], vec32(c, 3), nrhs, par, st, fused,
