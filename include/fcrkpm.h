@@ -476,16 +476,16 @@ enum {
                                  DFT-6 first stage), 1 = 8 lanes; at 256 points
                                  layout 0 = 16 lanes x 16 points, 1 = 32 lanes x 8 points;
                                  tiles = 1 or 2 tiles per workgroup (64 and 128 points; the
-                                 second tile's loads overlap the first tile's work).  The
-                                 library times a K product with each variant and keeps the
-                                 fastest: at setup where FFT passes serve the products (or
-                                 FCRKPM_AUTOTUNE_CACHE is set), else when the FFT passes are
-                                 first asked for: the first read or set of an option that
-                                 describes them, OPT_TAPS 0 (synchronous).
+                                 second tile's loads overlap the first tile's work).  Setup
+                                 times a K product with each variant and keeps the fastest
+                                 where FFT passes serve the products (or
+                                 FCRKPM_AUTOTUNE_CACHE is set); else it takes the variant
+                                 that is the fastest on an MI355X.
                                  FP64 products use the 16-lane layout at 80 and 96 points and
                                  the 32-lane one at 256. */
-    FCRKPM_OPT_TUNE_NS0 = 4, /* read only: the time of one K product with variant 0, ns */
-    FCRKPM_OPT_TUNE_NS1 = 5, /* read only: the same with variant 1 (0 where not timed) */
+    FCRKPM_OPT_TUNE_NS0 = 4, /* read only: setup's time of one K product with variant 0, ns
+                                (0 where not timed, as for the next three) */
+    FCRKPM_OPT_TUNE_NS1 = 5, /* read only: the same with variant 1 */
     FCRKPM_OPT_TUNE_NS2 = 6, /* read only: the same with variant 2 */
     FCRKPM_OPT_TUNE_NS3 = 7, /* read only: the same with variant 3 */
     FCRKPM_OPT_LINECONST = 8, /* 1 (default): where every z line of the box has a constant
@@ -494,12 +494,14 @@ enum {
                                 the register path's middle pass applies that constant in the
                                 spectral domain and corrects the end nodes directly (the same
                                 sums as Alg 2, regrouped); 0: the middle pass with a pointwise
-                                stage at every node.  Reads 1 only where setup found the
-                                structure. */
+                                stage at every node.  Reads 1 only where the rows have the
+                                structure; where direct sums serve the products the first
+                                read looks for it (synchronous). */
     FCRKPM_OPT_SEP_LINES32 = 9,  /* LDS-tiled passes, FP32: most lines per workgroup (16, 8, 4) */
-    FCRKPM_OPT_SEP_LINES64 = 10, /* the same for FP64.  K products are timed with each on the
-                                    precisions that run on these passes, the fastest is kept. */
-    FCRKPM_OPT_TUNE_CACHED = 11, /* read only: 1 if the tuning choices came from the file
+    FCRKPM_OPT_SEP_LINES64 = 10, /* the same for FP64.  Setup times K products with each on the
+                                    precisions that run on these passes, where it times, and
+                                    keeps the fastest; else 16. */
+    FCRKPM_OPT_TUNE_CACHED = 11, /* read only: 1 if setup took its tuning choices from the file
                                     named by FCRKPM_AUTOTUNE_CACHE (keyed by device, box, basis
                                     and support) instead of timing; new choices are appended to
                                     that file */
@@ -512,7 +514,8 @@ enum {
                                     above that asks for FFT passes other than setup's choice
                                     (OPT_REGPATH 0, OPT_LINECONST 0, another OPT_REGLAYOUT or
                                     OPT_SEP_LINES*), run the FFT passes; reads 1 if direct sums
-                                    serve this context's K products */
+                                    serve this context's products.  Setting an option that runs
+                                    FFT passes prepares them (synchronous, allocates) */
 };
 /* Set an option; FCRKPM_ERR_ARG for an unknown option or a value out of range. */
 fcrkpm_status fcrkpm_set_option(fcrkpm_ctx* ctx, int32_t option, int64_t value);

@@ -1806,7 +1806,8 @@ void fft_tables(Ctx& c, hipStream_t st)
             hp[6 + j] = mom_plan.p1[j];
         }
         c.dprog = dalloc<SepProg>(9);
-        HIPCHK(hipMemcpy(c.dprog, hp.data(), sizeof(SepProg) * 9, hipMemcpyHostToDevice));
+        HIPCHK(hipMemcpyAsync(c.dprog, hp.data(), sizeof(SepProg) * 9, hipMemcpyHostToDevice, st));
+        HIPCHK(hipStreamSynchronize(st));
         for (int j = 0; j < 3; ++j) {
             c.basis_plan.d1[j] = c.dprog + j;
             c.basis_plan.d2[j] = c.dprog + 3 + j;
@@ -1886,6 +1887,17 @@ void set_reg_variant(Ctx& c, int v)
 {
     c.reg_layout = v & 1;
     c.reg_tpw = (v >> 1) + 1;
+}
+
+// The register variant of a box that is not timed: what timing picks on an
+// MI355X, 16 lanes a line at 128 points (61 us a K product against 84 with 8)
+// and 32 at 256, the first layout elsewhere.
+int default_reg_variant(const Ctx& c)
+{
+    if (!reg_path_ok(c) && !reg_gpq_ok(c)) return 0;
+    if (const char* e = getenv("FCRKPM_REGLAYOUT"))
+        if (*e >= '0' && *e <= '3' && reg_variant_ok(c, *e - '0')) return *e - '0';
+    return c.n[0] >= 128 ? 1 : 0;
 }
 
 void tune_reg_layout(Ctx& c, hipStream_t st)
@@ -2049,8 +2061,7 @@ void autotune(Ctx& c, hipStream_t st)
     }
     if (const char* e = getenv("FCRKPM_REGLAYOUT")) {
         if (*e >= '0' && *e <= '3' && reg_variant_ok(c, *e - '0')) {
-            set_reg_variant(c, *e - '0');
-            tune_sep_tiles(c, st);
+            tune_sep_tiles(c, st);  // the forced variant is in place
             return;
         }
     }
@@ -2064,19 +2075,6 @@ void autotune(Ctx& c, hipStream_t st)
             fclose(f);
         }
     }
-}
-
-// The FFT passes of K and their autotuned choices, once per context.
-void fft_tune(Ctx& c, hipStream_t st)
-{
-    fft_ensure(c, st);
-    if (c.fft_tuned) return;
-    c.fft_tuned = true;
-    ensure_work(c, 1);
-    autotune(c, st);
-    c.tuned[0] = c.reg_layout + 2 * (c.reg_tpw - 1);
-    c.tuned[1] = c.sep_wcap[0];
-    c.tuned[2] = c.sep_wcap[1];
 }
 }  // namespace
 
@@ -2262,7 +2260,15 @@ extern "C" fcrkpm_status fcrkpm_setup(const fcrkpm_grid* grid, const uint8_t* ma
         HIPCHK(hipStreamSynchronize(st));
         ensure_rhs(c, 1);
         const char* cache = getenv("FCRKPM_AUTOTUNE_CACHE");
-        if (fft_needed(c) || (cache && *cache)) fft_tune(c, st);
+        set_reg_variant(c, default_reg_variant(c));
+        if (fft_needed(c) || (cache && *cache)) {
+            fft_ensure(c, st);
+            ensure_work(c, 1);
+            autotune(c, st);
+        }
+        c.tuned[0] = c.reg_layout + 2 * (c.reg_tpw - 1);
+        c.tuned[1] = c.sep_wcap[0];
+        c.tuned[2] = c.sep_wcap[1];
         HIPCHK(hipGetLastError());
         *out = h;
         h = nullptr;
@@ -3079,24 +3085,43 @@ extern "C" fcrkpm_status fcrkpm_solve_nonlinear(fcrkpm_ctx* ctx, int32_t mode, d
     });
 }
 
+namespace {
+// Synchronous work of a call that takes no stream, on a stream of its own and
+// in the relaxed capture mode: a capture that the caller has under way on
+// another stream goes on undisturbed.
+struct Aside {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    hipStream_t st = nullptr;
+    Aside()
+    {
+        HIPCHK(hipThreadExchangeStreamCaptureMode(&mode));
+        const hipError_t e = hipStreamCreateWithFlags(&st, hipStreamNonBlocking);
+        if (e == hipSuccess) return;
+        (void)hipThreadExchangeStreamCaptureMode(&mode);
+        throw HipFail{e, "hipStreamCreateWithFlags"};
+    }
+    ~Aside()
+    {
+        (void)hipStreamSynchronize(st);
+        (void)hipStreamDestroy(st);
+        (void)hipThreadExchangeStreamCaptureMode(&mode);
+    }
+    Aside(const Aside&) = delete;
+    Aside& operator=(const Aside&) = delete;
+};
+}  // namespace
+
 extern "C" fcrkpm_status fcrkpm_get_option(fcrkpm_ctx* ctx, int32_t option, int64_t* value)
 {
     if (!ctx) return FCRKPM_ERR_ARG;
     Ctx& c = ctx->c;
     return run_guarded(c.err, [&]() -> fcrkpm_status {
         if (!value) fail(FCRKPM_ERR_ARG, "NULL value");
-        switch (option) {  // what describes the FFT passes has them set up first
-            case FCRKPM_OPT_REGLAYOUT:
-            case FCRKPM_OPT_TUNE_NS0:
-            case FCRKPM_OPT_TUNE_NS1:
-            case FCRKPM_OPT_TUNE_NS2:
-            case FCRKPM_OPT_TUNE_NS3:
-            case FCRKPM_OPT_SEP_LINES32:
-            case FCRKPM_OPT_SEP_LINES64:
-            case FCRKPM_OPT_TUNE_CACHED: fft_tune(c, nullptr); break;
-            case FCRKPM_OPT_LINECONST:
-            case FCRKPM_OPT_KN_REGPATH: fft_ensure(c, nullptr); break;
-            default: break;
+        // these two ask for a property of the FFT passes' records: their first
+        // read builds them
+        if ((option == FCRKPM_OPT_LINECONST || option == FCRKPM_OPT_KN_REGPATH) && !c.fft_ready) {
+            Aside own;
+            fft_ensure(c, own.st);
         }
         switch (option) {
             case FCRKPM_OPT_GRAPHS: *value = c.use_graphs ? 1 : 0; break;
@@ -3123,16 +3148,18 @@ namespace {
 // instead of the direct kernels; its default gives the choice back.
 void pin_fft(Ctx& c, int bit, bool on) { c.fft_pins = on ? c.fft_pins | bit : c.fft_pins & ~bit; }
 
-// The FFT passes of every operator set built so far, so that no later product
-// has to set them up.
+// The FFT passes of every operator set built so far and their workspace, so
+// that no later product has to set them up.
 void fft_all(Ctx& c)
 {
-    fft_tune(c, nullptr);
+    Aside own;
+    fft_ensure(c, own.st);
     for (OpSet* s : {c.mass_set, c.shift_set, c.jac_set})
         if (s) {
             SetScope use(c, s);
-            fft_ensure(c, nullptr);
+            fft_ensure(c, own.st);
         }
+    ensure_work(c, 1);
 }
 }  // namespace
 

@@ -188,7 +188,6 @@ struct Ctx {
     int2* tap_zr[2] = {};               // first and last domain plane of each tile column
     void* tap = nullptr;                // class words and records of the K-type product in use
     bool fft_ready = false;             // what the FFT passes of these rows keep is built
-    bool fft_tuned = false;             // ... and tuned (K)
     uint8_t* base_block = nullptr;      // one allocation of the masks, volumes and coefficients
     uint8_t* rhs_block = nullptr;       // ... and of the solver buffers
 };

@@ -3053,12 +3053,12 @@ bool kn_build(const Ctx& c, hipStream_t st)
     // b^0 at the box centre gives its scale (interior node of a cube-like domain)
     const long centre = (long)(c.n[0] / 2) + (long)c.n[0] * ((c.n[1] / 2) + (long)c.n[1] * (c.n[2] / 2));
     double b0c[4] = {0, 0, 0, 0};
-    for (int q = 0; q < 4; ++q)
-        if (hipMemcpy(&b0c[q], c.b0_64 + (size_t)q * c.nn + centre, sizeof(double), hipMemcpyDeviceToHost) !=
-            hipSuccess) {
-            (void)hipGetLastError();
-            return false;
-        }
+    if (hipMemcpy2DAsync(b0c, sizeof(double), c.b0_64 + centre, sizeof(double) * c.nn, sizeof(double), 4,
+                         hipMemcpyDeviceToHost, st) != hipSuccess ||
+        hipStreamSynchronize(st) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
     double b0scale = 0.0;
     for (int q = 0; q < 4; ++q) b0scale = std::max(b0scale, fabs(b0c[q]));
     if (!kn_records<1>(c, c.b0_64, b0scale, c.nconst.v, s->b0pidx, s->b0rec, st)) {

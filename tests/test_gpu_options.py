@@ -56,3 +56,50 @@ def test_kernels_do_not_depend_on_options_read(n, at, degree):
         assert kd == ["tap_k_f32"] and torch.equal(again, k), opt
     assert torch.equal(cg(), d)
     g.close()
+
+
+def test_reading_an_option_builds_nothing():
+    """What setup stored is returned as it is: no device memory is taken, and
+    the values that were read give the choice back when they are set."""
+    f = fc()
+    p = W.cube(3, 128, 2.5, 1)
+    g = f.Problem.from_workload(p, device=DEV)
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    stored = [f.OPT_GRAPHS, f.OPT_REGPATH, f.OPT_REGLAYOUT, f.OPT_TUNE_NS0, f.OPT_TUNE_NS1, f.OPT_TUNE_NS2,
+              f.OPT_TUNE_NS3, f.OPT_SEP_LINES32, f.OPT_SEP_LINES64, f.OPT_TUNE_CACHED, f.OPT_TAPS]
+    value = {opt: g.get_option(opt) for opt in stored}
+    assert torch.cuda.mem_get_info()[0] == free
+    assert value[f.OPT_TUNE_NS1] == 0 and value[f.OPT_SEP_LINES32] == 16 and value[f.OPT_TAPS] == 1
+    for opt, other in ((f.OPT_REGLAYOUT, 1 - value[f.OPT_REGLAYOUT]), (f.OPT_SEP_LINES32, 8), (f.OPT_SEP_LINES64, 4)):
+        g.set_option(opt, other)
+        assert g.get_option(f.OPT_TAPS) == 0 and g.get_option(opt) == other
+        g.set_option(opt, value[opt])
+        assert g.get_option(f.OPT_TAPS) == 1 and g.get_option(opt) == value[opt]
+    g.close()
+
+
+def test_options_read_during_a_capture():
+    """A capture goes on while options are read, also those whose first read
+    builds records."""
+    f = fc()
+    p = W.cube(3, 64, 2.5, 1)
+    g = f.Problem.from_workload(p, device=DEV)
+    x = torch.from_numpy(np.random.default_rng(6).standard_normal(p.shape)).to(DEV)
+    ref = g.apply("K", x)
+    a, b = torch.zeros_like(x), torch.zeros_like(x)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        g.apply("K", x, out=a)
+        values = [g.get_option(opt) for opt in options(f)]
+        g.apply("K", a, out=b)
+    assert values == [g.get_option(opt) for opt in options(f)]
+    second = g.apply("K", ref)
+    for _ in range(3):
+        a.zero_(), b.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(a, ref) and torch.equal(b, second)
+        x.add_(0.0)
+    g.close()
