@@ -3168,49 +3168,56 @@ extern "C" fcrkpm_status fcrkpm_set_option(fcrkpm_ctx* ctx, int32_t option, int6
     if (!ctx) return FCRKPM_ERR_ARG;
     Ctx& c = ctx->c;
     return run_guarded(c.err, [&]() -> fcrkpm_status {
-        if (option == FCRKPM_OPT_REGLAYOUT || option == FCRKPM_OPT_SEP_LINES32 || option == FCRKPM_OPT_SEP_LINES64 ||
-            ((option == FCRKPM_OPT_REGPATH || option == FCRKPM_OPT_LINECONST || option == FCRKPM_OPT_TAPS) &&
-             value == 0))
-            fft_all(c);
+        const int lines = option == FCRKPM_OPT_SEP_LINES64 ? 1 : 0;
+        bool pin = value == 0;  // asks for FFT passes other than setup's choice
         switch (option) {
             case FCRKPM_OPT_GRAPHS:
                 if (value != 0 && value != 1) fail(FCRKPM_ERR_ARG, "FCRKPM_OPT_GRAPHS takes 0 or 1");
                 c.use_graphs = value == 1;
-                break;
+                return FCRKPM_OK;
             case FCRKPM_OPT_REGPATH:
                 if (value != 0 && value != 1) fail(FCRKPM_ERR_ARG, "FCRKPM_OPT_REGPATH takes 0 or 1");
-                c.use_regpath = value == 1;
-                pin_fft(c, 1, value == 0);
                 break;
             case FCRKPM_OPT_TAPS:
                 if (value != 0 && value != 1) fail(FCRKPM_ERR_ARG, "FCRKPM_OPT_TAPS takes 0 or 1");
-                c.use_taps = value == 1;
                 break;
             case FCRKPM_OPT_REGLAYOUT:
                 if (!((reg_path_ok(c) || reg_gpq_ok(c)) ? reg_variant_ok(c, (int)value) : value == 0))
                     fail(FCRKPM_ERR_ARG, "FCRKPM_OPT_REGLAYOUT out of range for this box");
-                set_reg_variant(c, (int)value);
-                pin_fft(c, 2, value != c.tuned[0]);
+                pin = value != c.tuned[0];
                 break;
             case FCRKPM_OPT_LINECONST:
                 if (value != 0 && value != 1) fail(FCRKPM_ERR_ARG, "FCRKPM_OPT_LINECONST takes 0 or 1");
-                c.use_sym = value == 1;
-                pin_fft(c, 4, value == 0);
                 break;
             case FCRKPM_OPT_SEP_LINES32:
             case FCRKPM_OPT_SEP_LINES64:
                 if (value != 16 && value != 8 && value != 4)
                     fail(FCRKPM_ERR_ARG, "lines per workgroup of the LDS-tiled passes: 16, 8 or 4");
-                if (option == FCRKPM_OPT_SEP_LINES32) {
-                    c.sep_wcap[0] = (int)value;
-                    pin_fft(c, 8, value != c.tuned[1]);
-                } else {
-                    c.sep_wcap[1] = (int)value;
-                    pin_fft(c, 16, value != c.tuned[2]);
-                }
+                pin = value != c.tuned[1 + lines];
                 break;
             default:
                 fail(FCRKPM_ERR_ARG, "unknown option");
+        }
+        if (pin) fft_all(c);
+        switch (option) {
+            case FCRKPM_OPT_REGPATH:
+                c.use_regpath = value == 1;
+                pin_fft(c, 1, pin);
+                break;
+            case FCRKPM_OPT_TAPS:
+                c.use_taps = value == 1;
+                break;
+            case FCRKPM_OPT_REGLAYOUT:
+                set_reg_variant(c, (int)value);
+                pin_fft(c, 2, pin);
+                break;
+            case FCRKPM_OPT_LINECONST:
+                c.use_sym = value == 1;
+                pin_fft(c, 4, pin);
+                break;
+            default:
+                c.sep_wcap[lines] = (int)value;
+                pin_fft(c, 8 << lines, pin);
         }
         return FCRKPM_OK;
     });

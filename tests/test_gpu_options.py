@@ -103,3 +103,20 @@ def test_options_read_during_a_capture():
         assert torch.equal(a, ref) and torch.equal(b, second)
         x.add_(0.0)
     g.close()
+
+
+def test_a_refused_value_builds_nothing():
+    """A value out of range is refused before anything is prepared for it."""
+    f = fc()
+    p = W.cube(3, 128, 2.5, 1)
+    g = f.Problem.from_workload(p, device=DEV)
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    for opt, bad in ((f.OPT_REGLAYOUT, 2), (f.OPT_REGLAYOUT, 7), (f.OPT_REGLAYOUT, -1), (f.OPT_SEP_LINES32, 5),
+                     (f.OPT_SEP_LINES64, 0), (f.OPT_TAPS, 2), (f.OPT_REGPATH, -1), (f.OPT_LINECONST, 3),
+                     (f.OPT_GRAPHS, 2), (f.OPT_TUNE_NS0, 0), (99, 0)):
+        with pytest.raises(f.FcrkpmError):
+            g.set_option(opt, bad)
+    assert torch.cuda.mem_get_info()[0] == free
+    assert g.get_option(f.OPT_TAPS) == 1 and g.get_option(f.OPT_GRAPHS) == 1
+    g.close()
