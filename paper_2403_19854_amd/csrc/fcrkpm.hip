@@ -143,7 +143,10 @@ T* dalloc(size_t count)
     void* p = nullptr;
     if (count == 0) count = 1;
     hipError_t e = hipMalloc(&p, count * sizeof(T));
-    if (e != hipSuccess) fail(FCRKPM_ERR_OOM, "device allocation of " + std::to_string(count * sizeof(T)) + " bytes failed");
+    if (e != hipSuccess) {
+        (void)hipGetLastError();  // a later call does not report it again
+        fail(FCRKPM_ERR_OOM, "device allocation of " + std::to_string(count * sizeof(T)) + " bytes failed");
+    }
     return reinterpret_cast<T*>(p);
 }
 
@@ -190,17 +193,9 @@ void free_set(OpSet*& s)
     s = nullptr;
 }
 
-void release(Ctx& c)
+// What fft_tables and fft_build make.
+void fft_tables_release(Ctx& c)
 {
-    sym_release(c);
-    tap_release(c);
-    free_set(c.mass_set);
-    free_set(c.shift_set);
-    free_set(c.jac_set);
-    dfree(c.base_block);
-    dfree(c.cls);
-    dfree(c.area64);
-    dfree(c.area32);
     for (int a = 0; a < 3; ++a) {
         dfree(c.tw64[a]);
         dfree(c.tw32[a]);
@@ -209,18 +204,37 @@ void release(Ctx& c)
         dfree(c.rtab32[a]);
         dfree(c.rtab64[a]);
     }
+    dfree(c.dprog);
+}
+
+void fft_release(Ctx& c)
+{
+    for (int l = 0; l < 2; ++l) {
+        dfree(c.nbits[l]);
+        dfree(c.noff[l]);
+        dfree(c.nrec[l]);
+    }
+    sym_release(c);
+    c.fft_ready = false;
+}
+
+void release(Ctx& c)
+{
+    tap_release(c);
+    free_set(c.mass_set);
+    free_set(c.shift_set);
+    free_set(c.jac_set);
+    dfree(c.base_block);
+    dfree(c.cls);
+    dfree(c.area64);
+    dfree(c.area32);
+    fft_tables_release(c);
     dfree(c.work64);
     dfree(c.work32);
     dfree(c.rhs_block);
-    dfree(c.nbits[0]);
-    dfree(c.nbits[1]);
-    dfree(c.noff[0]);
-    dfree(c.noff[1]);
-    dfree(c.nrec[0]);
-    dfree(c.nrec[1]);
+    fft_release(c);
     if (c.aux) (void)hipStreamDestroy(c.aux);
     c.aux = nullptr;
-    dfree(c.dprog);
     if (c.hscal) (void)hipHostFree(c.hscal);
     c.hscal = nullptr;
     if (c.prof) {
@@ -628,7 +642,7 @@ bool fft_needed(const Ctx& c) { return !tap_active(c); }
 
 void build_pointwise(Ctx& c, hipStream_t st);
 void fft_tables(Ctx& c, hipStream_t st);
-void fft_build(Ctx& c, hipStream_t st);
+bool fft_build(Ctx& c, hipStream_t st);
 void fft_ensure(Ctx& c, hipStream_t st);
 
 // Exchanges the pointwise data of the K-type product in use with `s`.
@@ -683,7 +697,8 @@ OpSet* make_set(Ctx& c, double ck, double cm, hipStream_t st, const double* wnod
         build_pointwise(c, st);
         if (fft_needed(c)) {
             fft_tables(c, st);
-            fft_build(c, st);
+            (void)fft_build(c, st);
+            c.fft_ready = true;
         }
         HIPCHK(hipStreamSynchronize(st));
     } catch (...) {
@@ -1647,7 +1662,10 @@ void run_solvers_on(const std::vector<Solver*>& all, bool graphs, hipStream_t st
 
 [[noreturn]] void fcrkpm::raise_hip(hipError_t e, const char* what)
 {
-    if (e == hipErrorOutOfMemory) fail(FCRKPM_ERR_OOM, std::string("device allocation failed: ") + what);
+    if (e == hipErrorOutOfMemory) {
+        (void)hipGetLastError();
+        fail(FCRKPM_ERR_OOM, std::string("device allocation failed: ") + what);
+    }
     throw HipFail{e, what};
 }
 
@@ -1728,10 +1746,24 @@ void build_pointwise(Ctx& c, hipStream_t st)
 }
 
 // What the FFT passes read whatever the rows: twiddles, kernel spectra and the
-// pass programs.  Synchronous, once per context.
+// pass programs.  Synchronous, once per context; nothing is left of a build
+// that fails.
+void fft_tables_make(Ctx& c, hipStream_t st);
+
 void fft_tables(Ctx& c, hipStream_t st)
 {
     if (c.dprog) return;
+    try {
+        fft_tables_make(c, st);
+    } catch (...) {
+        (void)hipStreamSynchronize(st);
+        fft_tables_release(c);
+        throw;
+    }
+}
+
+void fft_tables_make(Ctx& c, hipStream_t st)
+{
     // twiddles and separable kernel spectra (Sec 5.2-5.3, Eq 68-79)
     const long double twopi = 6.283185307179586476925286766559005768L;
     for (int a = 0; a < 3; ++a) {
@@ -1817,11 +1849,11 @@ void fft_tables(Ctx& c, hipStream_t st)
 
 // What the FFT passes of the rows in use keep besides: the records of the
 // register path and the line-constant structure.  Contexts whose products run
-// on the direct kernels build them when an option or a call first asks for FFT
-// passes.
-void fft_build(Ctx& c, hipStream_t st)
+// on the direct kernels build them when an option that runs FFT passes is set.
+// The line-constant structure is an extra that may be absent for want of
+// memory: false then.
+bool fft_build(Ctx& c, hipStream_t st)
 {
-    c.fft_ready = true;
     // node classes of the register-resident K passes: interior nodes share
     // one M = V B^T B (a kernel argument), nodes outside the domain give
     // zero, and every other element gets its own record, packed lane by lane
@@ -1868,19 +1900,30 @@ void fft_build(Ctx& c, hipStream_t st)
         }
     }
     // the line-constant middle pass, where these rows have the structure
-    sym_build(c, st);
+    const bool whole = sym_build(c, st);
     HIPCHK(hipStreamSynchronize(st));
+    return whole;
 }
 
+// All of it, or nothing: a context goes on as it was where the build fails
+// (out of memory, say) and a later call starts from the beginning.
 void fft_ensure(Ctx& c, hipStream_t st)
 {
     if (c.fft_ready) return;
     if (c.capturing) fail(FCRKPM_ERR_ARG, "the FFT passes cannot be set up during graph capture");
     fft_tables(c, st);
-    fft_build(c, st);
-    // the FP64 register path's records of u^h, f^r and the gradient force,
-    // built here so that no later product allocates them
-    (void)reg_kn_ok(c, st);
+    try {
+        const bool whole = fft_build(c, st);
+        // the FP64 register path's records of u^h, f^r and the gradient force,
+        // built here so that no later product allocates them
+        (void)reg_kn_ok(c, st);
+        if (!whole || sym_oom(c)) fail(FCRKPM_ERR_OOM, "device allocation failed: line-constant records");
+    } catch (...) {
+        (void)hipStreamSynchronize(st);
+        fft_release(c);
+        throw;
+    }
+    c.fft_ready = true;
 }
 
 void set_reg_variant(Ctx& c, int v)

@@ -263,8 +263,10 @@ bool reg_gpq_ok(const Ctx& c);
 // analyses the coefficient rows in use (K's) and keeps the state in c.sym
 // when the geometry allows it; sym_active tells whether the current product
 // can use it; sym_release frees it.
-void sym_build(Ctx& c, hipStream_t st);
+bool sym_build(Ctx& c, hipStream_t st);
 bool sym_active(const Ctx& c);
+// the gradient's or u^h's line records are missing because memory ran out
+bool sym_oom(const Ctx& c);
 void sym_release(Ctx& c);
 void sym_release_state(void*& sym);
 // algorithmic bytes of one launch of that middle pass per right-hand side

@@ -2248,6 +2248,7 @@ struct SymState {
     double tol = 0.0;            // the records' equality tolerance (M's scale)
     // the gradient nonlinearity's records (B_L, C_L = V_L B_L), built on first use
     int kn = 0;                  // 0 not tried, 1 built, -1 unavailable
+    bool kn_oom = false;         // ... because device memory ran out
     int* knpidx = nullptr;
     double* knrec = nullptr;
     int* b0pidx = nullptr;       // the same for the single row b^0 (u^h, f^r)
@@ -2812,20 +2813,20 @@ double sym_pass_bytes(const Ctx& c, int elem_bytes)
 // line of the box is constant off the correction nodes (the nodes within
 // floor(a~) of the two ends of the domain's z extent, and those outside it);
 // leaves c.sym empty otherwise, and the middle pass with records per element
-// is used.  Synchronous.
-void sym_build(Ctx& c, hipStream_t st)
+// is used; false where that is because device memory ran out.  Synchronous.
+bool sym_build(Ctx& c, hipStream_t st)
 {
     sym_release(c);
     if (!c.use_sym || c.degree != 1 || c.krows < 1 || !(reg_path_ok(c) || reg_gpq_ok(c)) ||
         c.nconst.bmax < 0.0)
-        return;
+        return true;
     const int L = c.n[2], m = c.m[2];
-    if (L > 256 || m < 1 || m > 3) return;
+    if (L > 256 || m < 1 || m > 3) return true;
     const long nlines = (long)c.n[0] * c.n[1], npairs = nlines / 2;
     // z extent of the domain
     const int ntot = c.n[0] + c.n[1] + c.n[2];
     int* occ = nullptr;
-    if (!sym_alloc(occ, ntot)) return;
+    if (!sym_alloc(occ, ntot)) return false;
     std::vector<int> hocc(ntot);
     (void)hipMemsetAsync(occ, 0, sizeof(int) * ntot, st);
     launch_axis_extent(c, c.chi, occ, st);
@@ -2838,26 +2839,26 @@ void sym_build(Ctx& c, hipStream_t st)
             if (zlo < 0) zlo = z;
             zhi = z;
         }
-    if (zlo < 0) return;
+    if (zlo < 0) return true;
     SymTab tab{};
     tab.m = m;
     int zref = -1;
     for (int z = 0; z < L; ++z) {
         if (z < zlo + m || z > zhi - m) {
-            if (tab.nc == kSymC) return;
+            if (tab.nc == kSymC) return true;
             tab.cz[tab.nc++] = z;
         } else if (zref < 0) {
             zref = z;
         }
     }
-    if (zref < 0) return;
+    if (zref < 0) return true;
     std::vector<char> inw(L, 0);
     for (int i = 0; i < tab.nc; ++i)
         for (int o = -m; o <= m; ++o) inw[(tab.cz[i] + o + L) % L] = 1;
     for (int z = 0; z < 256; ++z) tab.widx[z] = -1;
     for (int z = 0; z < L; ++z)
         if (inw[z]) {
-            if (tab.nw == kSymW) return;
+            if (tab.nw == kSymW) return true;
             tab.widx[z] = (signed char)tab.nw;
             tab.wz[tab.nw++] = z;
         }
@@ -2876,7 +2877,7 @@ void sym_build(Ctx& c, hipStream_t st)
             for (int al = 0; al < c.krows; ++al) acc += c.nconst.b[al * 4 + p] * c.nconst.b[al * 4 + q];
             mscale = std::max(mscale, fabs(c.nconst.v * acc));
         }
-    if (!(mscale > 0.0)) return;
+    if (!(mscale > 0.0)) return true;
     const double tol = 1e-11 * mscale;
 
     SymState* s = new SymState();
@@ -2884,9 +2885,10 @@ void sym_build(Ctx& c, hipStream_t st)
     double* lrec = nullptr;
     int* czl = nullptr;
     int* flag = nullptr;
-    bool ok = sym_alloc(s->tab, 1) && sym_alloc(s->pidx, npairs) && sym_alloc(s->rec, (size_t)(npairs + 1) * kSymRec) &&
-              sym_alloc(s->rec64, (size_t)(npairs + 1) * kSymRec) &&
-              sym_alloc(lrec, (size_t)nlines * (10 + 10 * kSymC)) && sym_alloc(czl, kSymC) && sym_alloc(flag, 2);
+    const bool fits = sym_alloc(s->tab, 1) && sym_alloc(s->pidx, npairs) && sym_alloc(s->rec, (size_t)(npairs + 1) * kSymRec) &&
+                      sym_alloc(s->rec64, (size_t)(npairs + 1) * kSymRec) &&
+                      sym_alloc(lrec, (size_t)nlines * (10 + 10 * kSymC)) && sym_alloc(czl, kSymC) && sym_alloc(flag, 2);
+    bool ok = fits;
     if (ok) {
         int hflag[2] = {0, 0};
         (void)hipMemcpyAsync(s->tab, &tab, sizeof(SymTab), hipMemcpyHostToDevice, st);
@@ -2910,7 +2912,10 @@ void sym_build(Ctx& c, hipStream_t st)
     s->tol = tol;
     c.sym = s;
     if (!ok) sym_release(c);
+    return fits;
 }
+
+bool sym_oom(const Ctx& c) { return c.sym && ((const SymState*)c.sym)->kn_oom; }
 
 // ------------------------------------------------ gradient nonlinearity, u^h, f^r: records and launch
 // Line records (FP64) for ROWS coefficient rows: B_L (row-major [a][q]) and
@@ -3008,7 +3013,7 @@ bool kn_records(const Ctx& c, const double* rows, double bscale, double vscale, 
                 hipStream_t st)
 {
     typedef KnRec<ROWS> KR;
-    const SymState& s = *(const SymState*)c.sym;
+    SymState& s = *(SymState*)c.sym;
     const SymTab& tab = s.htab;
     const long nlines = (long)c.n[0] * c.n[1], npairs = nlines / 2;
     if (!(bscale > 0.0) || !(vscale > 0.0)) return false;
@@ -3016,8 +3021,10 @@ bool kn_records(const Ctx& c, const double* rows, double bscale, double vscale, 
     double* lrec = nullptr;
     int* czl = nullptr;
     int* flag = nullptr;
-    bool ok = sym_alloc(pidx, npairs) && sym_alloc(recs, (size_t)(npairs + 1) * KR::REC) &&
-              sym_alloc(lrec, (size_t)nlines * KR::LINE) && sym_alloc(czl, kSymC) && sym_alloc(flag, 1);
+    const bool fits = sym_alloc(pidx, npairs) && sym_alloc(recs, (size_t)(npairs + 1) * KR::REC) &&
+                      sym_alloc(lrec, (size_t)nlines * KR::LINE) && sym_alloc(czl, kSymC) && sym_alloc(flag, 1);
+    bool ok = fits;
+    s.kn_oom = !fits;
     if (ok) {
         int hflag = 0;
         (void)hipMemcpyAsync(czl, tab.cz, sizeof(int) * kSymC, hipMemcpyHostToDevice, st);

@@ -120,3 +120,67 @@ def test_a_refused_value_builds_nothing():
     assert torch.cuda.mem_get_info()[0] == free
     assert g.get_option(f.OPT_TAPS) == 1 and g.get_option(f.OPT_GRAPHS) == 1
     g.close()
+
+
+def fill_memory():
+    """Tensors of 16 MB, and a large first one, that hold all device memory (the
+    figure that the runtime reports as free is not all that it can still give)."""
+    take = lambda nbytes: torch.empty(nbytes, dtype=torch.uint8, device=DEV)
+    hold = [take(torch.cuda.mem_get_info()[0] - (4 << 30))]
+    try:
+        for _ in range(4096):
+            hold.append(take(16 << 20))
+    except torch.OutOfMemoryError:
+        return hold
+    raise AssertionError("device memory has no end")
+
+
+@pytest.mark.parametrize("uniform", [True, False])
+def test_preparing_fft_passes_without_memory(uniform):
+    """Out of device memory while the FFT passes are prepared: an error, the
+    direct products go on, and a later attempt is as good as a first one.  The
+    margins let the build stop at the register path's records, at the line
+    records and at the workspace (201 MB)."""
+    f = fc()
+    p = W.cube(3, 128, 2.5, 1)
+    vol = p.vol if uniform else p.vol * np.random.default_rng(8).uniform(0.5, 1.5, p.shape)
+    make = lambda: f.Problem(p.dims, p.h, p.at, p.degree, p.chi, p.dirichlet, vol, device=DEV)
+    x = torch.from_numpy(np.random.default_rng(9).standard_normal(p.shape)).to(DEV)
+    x32 = x.float()
+    outs = lambda: [torch.zeros_like(x32), torch.zeros_like(x), torch.zeros_like(x), torch.zeros_like(x)]
+
+    def run(g, out):
+        for op, v, o in zip(("K", "K", "UH", "FR"), (x32, x, x, x), out):
+            g.apply(op, v, out=o)
+
+    fft, direct = outs(), outs()
+    g = make()
+    g.set_option(f.OPT_TAPS, 0)
+    run(g, fft)
+    g.close()
+    g = make()
+    run(g, direct)
+    margins = (64, 176) if uniform else (64, 128, 304)
+    got = [outs() for _ in margins]
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    hold, freed = fill_memory(), 0
+    for margin, out in zip(margins, got):
+        print(f"\n[options] {margin} MB free", flush=True)
+        del hold[-((margin - freed) // 16):]
+        freed = margin
+        torch.cuda.empty_cache()
+        with pytest.raises(f.FcrkpmError, match="FCRKPM_ERR_OOM"):
+            g.set_option(f.OPT_TAPS, 0)
+        assert g.get_option(f.OPT_TAPS) == 1
+        run(g, out)
+    del hold
+    torch.cuda.empty_cache()
+    for out in got:
+        assert all(torch.equal(a, b) for a, b in zip(out, direct))
+    g.set_option(f.OPT_TAPS, 0)
+    out = outs()
+    run(g, out)
+    assert all(torch.equal(a, b) for a, b in zip(out, fft))
+    assert g.get_option(f.OPT_LINECONST) == g.get_option(f.OPT_KN_REGPATH) == int(uniform)
+    g.close()
