@@ -762,8 +762,6 @@ bool tap_apply(Ctx& c, int op, const Tio* in, Tio* out, int nrhs, hipStream_t st
                 return true;
             }
             case FCRKPM_OP_FQ:
-                if (!c.area64) return false;  // refused below
-                [[fallthrough]];
             case FCRKPM_OP_FR:
             case FCRKPM_OP_NT: {
                 const T* w = op == FCRKPM_OP_FR ? vol_of<T>(c) : op == FCRKPM_OP_FQ ? area_of<T>(c) : nullptr;
@@ -782,6 +780,7 @@ bool tap_apply(Ctx& c, int op, const Tio* in, Tio* out, int nrhs, hipStream_t st
 template <typename T, typename Tio = T>
 void apply_one(Ctx& c, int op, const Tio* in, Tio* out, int nrhs, hipStream_t st)
 {
+    if (op == FCRKPM_OP_FQ && !c.area64) fail(FCRKPM_ERR_ARG, "no boundary areas: call fcrkpm_set_boundary first");
     if (tap_apply<T, Tio>(c, op, in, out, nrhs, st)) return;
     fft_ensure(c, st);
     ensure_work(c, nrhs);
@@ -862,8 +861,6 @@ void apply_one(Ctx& c, int op, const Tio* in, Tio* out, int nrhs, hipStream_t st
                 }
                 // f^q is the load pass of f^r with the boundary areas A in place
                 // of V (Eq A.5, Alg A.1)
-                if (op == FCRKPM_OP_FQ && !c.area64)
-                    fail(FCRKPM_ERR_ARG, "no boundary areas: call fcrkpm_set_boundary first");
                 const T* vol = (op == FCRKPM_OP_FR || op == FCRKPM_OP_VN) ? vol_of<T>(c)
                                : op == FCRKPM_OP_FQ                      ? area_of<T>(c)
                                                                          : nullptr;

@@ -122,6 +122,25 @@ def test_a_refused_value_builds_nothing():
     g.close()
 
 
+def test_a_refused_flux_load_builds_nothing():
+    """f^q without boundary areas is refused at once, also by the call that
+    allocates nothing."""
+    f = fc()
+    p = W.cube(3, 64, 2.5, 1)
+    g = f.Problem.from_workload(p, device="cuda:0")
+    x = torch.ones(p.shape, dtype=torch.float64, device=DEV)
+    x32, out = x.float(), torch.empty_like(x)
+    out32 = out.float()
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    for v, o in ((x, out), (x32, out32)):
+        for call in (g.apply, g.apply_noalloc):
+            with pytest.raises(f.FcrkpmError, match="no boundary areas"):
+                call("FQ", v, out=o)
+    assert torch.cuda.mem_get_info()[0] == free
+    g.close()
+
+
 def fill_memory():
     """Tensors of 16 MB, and a large first one, that hold all device memory (the
     figure that the runtime reports as free is not all that it can still give)."""
