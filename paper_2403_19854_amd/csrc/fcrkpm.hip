@@ -2808,6 +2808,7 @@ void apply_grad(Ctx& c, const double* x, double* out, hipStream_t st)
         return;
     }
     fft_ensure(c, st);
+    ensure_work(c, 1);
     if (use_reg_path64(c) && reg_kn_ok(c, st)) {
         launch_reg_kn(c, x, out, 0.0, RK_GRAD, st);
         return;
@@ -2858,7 +2859,6 @@ extern "C" fcrkpm_status fcrkpm_solve_nonlinear_cg(fcrkpm_ctx* ctx, int32_t kind
         const long nn = c.nn;
         const int dim = c.dim;
         ensure_rhs(c, 1);
-        ensure_work(c, 1);
         HIPCHK(hipMemsetAsync(c.dflag + 2, 0, sizeof(int), st));
         launch_check_finite(r, nn, c.dflag + 2, st);
         if (g) launch_check_finite(g, nn, c.dflag + 2, st);
@@ -3038,7 +3038,6 @@ extern "C" fcrkpm_status fcrkpm_solve_nonlinear(fcrkpm_ctx* ctx, int32_t mode, d
         hipStream_t st = (hipStream_t)stream;
         const long nn = c.nn;
         ensure_rhs(c, 1);
-        ensure_work(c, 1);
         HIPCHK(hipMemsetAsync(c.dflag + 2, 0, sizeof(int), st));
         launch_check_finite(r, nn, c.dflag + 2, st);
         if (g) launch_check_finite(g, nn, c.dflag + 2, st);
@@ -3284,7 +3283,6 @@ extern "C" fcrkpm_status fcrkpm_get_coeffs(fcrkpm_ctx* ctx, int32_t which, doubl
                 // M^l = chi o F^-1[sum_p F(chi o V o b^0_p) o F(conj H_p)] (Eq C.13,
                 // Alg C.2): the load vector of r = 1
                 ensure_rhs(c, 1);
-                ensure_work(c, 1);
                 double* one = vec64(c, V_T);
                 launch_mask_to_double(c.chi, one, c.nn, st);
                 apply_one<double>(c, FCRKPM_OP_FR, one, out, 1, st);

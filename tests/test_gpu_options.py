@@ -141,6 +141,32 @@ def test_a_refused_flux_load_builds_nothing():
     g.close()
 
 
+def test_direct_contexts_hold_no_workspace():
+    """The nonlinear solvers and the lumped mass on the direct kernels leave a
+    context with the device memory that setup gave it."""
+    f = fc()
+    p = W.cube(3, 96, 2.5, 1)
+    r = torch.from_numpy(p.r).to(DEV)
+
+    def calls(g):
+        yield g.coeffs("lumped")
+        for kind in ("cubic", "gradient"):
+            yield g.solve_nonlinear_cg(r, 1.0, kind=kind, maxit=2, raise_on_noconv=False)[:2]
+        yield g.solve_nonlinear(r, 1.0, maxnewton=1, maxit=8, raise_on_noconv=False)[:2]
+
+    g = f.Problem.from_workload(p, device=DEV)
+    kept = list(calls(g))  # the kernels are loaded and torch holds its blocks
+    del kept
+    g.close()
+    g = f.Problem.from_workload(p, device=DEV)
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    for _ in calls(g):
+        torch.cuda.synchronize()
+        assert torch.cuda.mem_get_info()[0] == free
+    g.close()
+
+
 def fill_memory():
     """Tensors of 16 MB, and a large first one, that hold all device memory (the
     figure that the runtime reports as free is not all that it can still give)."""
