@@ -834,16 +834,21 @@ __global__ __launch_bounds__(NT, tap_min_waves(sizeof(T), tap_lds_of<B, R, MODE,
     const int ty = b % nty;
     const int x0 = tx * TX, y0 = ty * TY;
     const int za = (b / nty) * kp->cz, ze = min(za + kp->cz, kp->n[2]);
-    // planes of the chunk outside the domain's extent in this tile column are zero
+    // planes of the chunk outside the domain's extent in this tile column are
+    // zero, in every field of the result (the implicit gradient has ROWS of them)
+    constexpr int NF = MODE == TAP_UH ? ROWS : 1;
     const int2 zr = kp->zr[ty * ntx + tx];
     const int zlo = min(max(za, zr.x), ze), zhi = max(zlo, min(ze, zr.y + 1));
     if (MODE != TAP_MOM && (za < zlo || zhi < ze)) {
         for (int i = tid; i < TX * TY; i += NT) {
             const int x = x0 + i % TX, y = y0 + i / TX;
             if (x < nx && y < ny) {
-                Tio* o = out + (long)y * nx + x;
-                for (int z = za; z < zlo; ++z) o[(long)z * nxy] = Tio(0);
-                for (int z = zhi; z < ze; ++z) o[(long)z * nxy] = Tio(0);
+#pragma unroll
+                for (int f = 0; f < NF; ++f) {
+                    Tio* o = out + f * kp->nn + (long)y * nx + x;
+                    for (int z = za; z < zlo; ++z) o[(long)z * nxy] = Tio(0);
+                    for (int z = zhi; z < ze; ++z) o[(long)z * nxy] = Tio(0);
+                }
             }
         }
     }
