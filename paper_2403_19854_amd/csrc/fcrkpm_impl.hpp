@@ -152,8 +152,8 @@ struct Ctx {
     double* v64 = nullptr;              // 6 FP64 vectors of cap_rhs fields
     float* v32 = nullptr;               // 5 FP32 vectors of cap_rhs fields
     double* partial = nullptr;          // reduction partials (2 x cap_rhs x kRedBlocks)
-    double* partial_wide = nullptr;     // p.q partials of a last pass with more workgroups
-                                        // than kRedBlocks (cap_rhs x reg_dot_slots)
+    double* partial_wide = nullptr;     // p.q partials of a last pass or a direct product with more
+                                        // workgroups than kRedBlocks (cap_rhs x wide_slots)
     double* scal = nullptr;             // device scalars (cap_rhs x kScal)
     double* hscal = nullptr;            // pinned host mirror (2 poll slots + 1 read slot)
     int* act = nullptr;                 // per right-hand side: still iterating

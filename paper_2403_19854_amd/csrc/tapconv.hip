@@ -254,7 +254,8 @@ long tap_dots(const Ctx& c, int elem)
     return (long)c.tap_nt[u.small][0] * c.tap_nt[u.small][1] * ((c.n[2] + u.cz - 1) / u.cz);
 }
 
-long tap_dot_slots(const Ctx& c) { return c.tap ? std::max(tap_dots(c, 4), tap_dots(c, 8)) : 0; }
+// (a rule on the geometry, the same for every operator set of a context)
+long tap_dot_slots(const Ctx& c) { return tap_served(c) ? std::max(tap_dots(c, 4), tap_dots(c, 8)) : 0; }
 
 void tap_release_set(void*& s)
 {
