@@ -618,13 +618,14 @@ void reg_k(Ctx& c, const float* in, float* out, const uint8_t* mask, int nrhs, h
 }
 
 // The K-type product on the direct tap kernels; with cg the one of a CG
-// iteration, which reads r in place of the mask and also writes p.
+// iteration, which reads r in place of the mask and also writes p.  (Its class
+// words and records serve all right-hand sides.)
 template <typename T, typename Tio>
 void tap_k(Ctx& c, const Tio* in, Tio* out, const uint8_t* mask, int nrhs, hipStream_t st,
            const TapCg* cg = nullptr)
 {
     const double bytes = (double)c.nn * (2 * sizeof(Tio) + (cg ? 2 * sizeof(Tio) + 1 : 2));
-    ProfScope ps(c, kind_of<T>(KD_TAP_K), bytes * nrhs, st);
+    ProfScope ps(c, kind_of<T>(KD_TAP_K), bytes * nrhs + tap_word_bytes(c) + tap_rec_bytes(c, sizeof(T)), st);
     launch_tap<T, Tio>(c, cg ? kTapCg : SEP_PW_K, in, out, mask, mask, nullptr, nullptr, nrhs, st, cg);
 }
 
@@ -749,7 +750,7 @@ bool tap_apply(Ctx& c, int op, const Tio* in, Tio* out, int nrhs, hipStream_t st
                 if constexpr (std::is_same_v<T, double>) {
                     // only nodes that are not interior read their rows
                     ProfScope ps(c, kind_of<T>(KD_TAP_K),
-                                 nn * (2 * rt + 2) + (double)c.ncls2 * (c.dim * c.s + 1) * rt * nrhs, st);
+                                 nn * (2 * rt + 2) + tap_word_bytes(c) + (double)c.ncls2 * (c.dim * c.s + 1) * rt, st);
                     launch_tap<T, Tio>(c, SEP_PW_KN, in, out, c.chi, c.chi, c.ba_64, c.vol64, nrhs, st);
                     return true;
                 }

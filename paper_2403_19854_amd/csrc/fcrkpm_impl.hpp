@@ -337,6 +337,10 @@ void tap_build(Ctx& c, hipStream_t st);
 bool tap_active(const Ctx& c);
 long tap_dots(const Ctx& c, int elem_bytes);
 long tap_dot_slots(const Ctx& c);
+// bytes of the class words and of the records that a product of this precision
+// reads
+double tap_word_bytes(const Ctx& c);
+double tap_rec_bytes(const Ctx& c, int elem_bytes);
 void tap_release(Ctx& c);
 void tap_release_set(void*& s);
 template <typename T, typename Tio>

@@ -19,6 +19,7 @@ struct TapSet {
     double* rec64 = nullptr;
     float m32[kTapMint] = {};
     double m64[kTapMint] = {};
+    double words_bytes = 0.0, rec_bytes[2] = {};  // of the arrays (records: FP32, FP64)
 };
 
 void tap_check(hipError_t e)
@@ -257,6 +258,9 @@ long tap_dots(const Ctx& c, int elem)
 // (a rule on the geometry, the same for every operator set of a context)
 long tap_dot_slots(const Ctx& c) { return tap_served(c) ? std::max(tap_dots(c, 4), tap_dots(c, 8)) : 0; }
 
+double tap_word_bytes(const Ctx& c) { return ((const TapSet*)c.tap)->words_bytes; }
+double tap_rec_bytes(const Ctx& c, int elem) { return ((const TapSet*)c.tap)->rec_bytes[elem == 8]; }
+
 void tap_release_set(void*& s)
 {
     tap_free((TapSet*)s);
@@ -335,6 +339,9 @@ void tap_build(Ctx& c, hipStream_t st)
         return;
     }
     n += 2;  // records 0 and 1: a node outside the domain (zero) and the interior nodes'
+    s->words_bytes = (double)total * sizeof(uint32_t);
+    s->rec_bytes[0] = (double)n * rp32 * sizeof(float);
+    s->rec_bytes[1] = (double)n * rp64 * sizeof(double);
     s->rec32 = tap_alloc<float>((size_t)n * rp32);
     s->rec64 = tap_alloc<double>((size_t)n * rp64);
     std::vector<float> h32((size_t)2 * rp32, 0.0f);
