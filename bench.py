@@ -4,7 +4,7 @@
 One step = the whole path on one synthetic input already resident in HBM:
 setup (kernel spectra, moment convolutions and per-node moment solves, Alg 1),
 load vector (Alg 4), CG on the stiffness operator (Alg 2 inside Alg 5; FP32
-FFT matvecs inside FP64 iterative refinement by default) and the field u^h
+matvecs inside FP64 iterative refinement by default) and the field u^h
 (Alg 3).  The headline value is CG matvecs per second over the timed steps
 (every K product counts: FP32 inner and FP64 outer); DOF/s multiplies by the
 free unknowns.
@@ -47,9 +47,10 @@ def parse():
                     help="counter probe: setup, a refined solve capped at N CG iterations "
                          "(direct launches), then a 256 MiB device copy that calibrates the "
                          "memory counters; prints one line and exits")
-    ap.add_argument("--probe-variant", type=int, default=1,
-                    help="register-path variant for --probe (layout + 2 (tiles - 1)); the "
-                         "default is the one setup's autotuner picks for 128^3 on MI355X")
+    ap.add_argument("--probe-variant", type=int, default=None,
+                    help="--probe on the FFT passes with this register-path variant (layout + "
+                         "2 (tiles - 1); 1 is what timing picks at 128^3 and 256^3 on MI355X) "
+                         "instead of the library's choice")
     ap.add_argument("--mode", default=None, choices=["f32_refined", "f64"],
                     help="default: f64 for c1 and c2 (plain FP64 configurations), else f32_refined")
     ap.add_argument("--tol", type=float, default=1e-12)
@@ -111,7 +112,6 @@ def main():
                                    raise_on_noconv=False)
         else:
             d, uh, info = pb.solve(r, mode=mode, tol=a.tol, maxit=a.maxit, want_uh=True)
-        info["layout"] = pb.get_option(fcrkpm.OPT_REGLAYOUT)
         prof = None
         if profile:
             pb.profile(False)
@@ -147,6 +147,8 @@ def main():
                for k, (n, w, by) in prof_acc.items()}
     dom = max(kernels, key=lambda k: kernels[k]["est_total_ms"])
     dk = kernels[dom]
+    variant = register_variant(kernels, lambda: fcrkpm.Problem(wl.dims, wl.h, wl.at, wl.degree, chi, dirm, vol,
+                                                               device=dev))
     achieved = dk["bytes_per_launch"] / (dk["mean_ms"] * 1e-3) / 1e9
     m = wl.chi > 0
     uh_err = float(np.linalg.norm((uh.cpu().numpy() - wl.u_exact)[m]) /
@@ -181,11 +183,11 @@ def main():
                   "matvecs_f64": infos[-1]["matvecs_f64"],
                   "true_rel_res": infos[-1]["true_rel_res"],
                   "fallback_used": infos[-1]["fallback_used"],
-                  "register_variant": infos[-1]["layout"],
+                  "register_variant": variant,
                   "uh_rel_l2_vs_exact": uh_err},
-        "roofline": {"bound": "hbm", "kernel": dom, "achieved": achieved, "peak": HBM_PEAK_GBS,
+        "roofline": {"bound": bound_of(dom), "kernel": dom, "achieved": achieved, "peak": HBM_PEAK_GBS,
                      "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
-                     "traffic": traffic.load(wl.name, dom, infos[-1]["layout"]),
+                     "traffic": traffic.load(wl.name, dom, variant),
                      "mean_ms": dk["mean_ms"], "bytes_per_launch": dk["bytes_per_launch"]},
         "kernels": kernels,
         "gpu_clocks": clocks,
@@ -223,6 +225,29 @@ def main():
         if a.fixed_iters:
             out["solve"]["oracle_rel_res"] = out["cpu_baseline"].pop("oracle_rel_res")
     print(json.dumps(out), flush=True)
+
+
+def register_variant(kernels, problem):
+    """Variant of the register path that the sampled kernels ran on (from a
+    context of the same problem, outside any timing); None where no FFT pass
+    ran."""
+    from paper_2403_19854_amd import fcrkpm
+
+    if not any(k.startswith("sep_part1") for k in kernels):
+        return None
+    pb = problem()
+    try:
+        return pb.get_option(fcrkpm.OPT_REGLAYOUT)
+    finally:
+        pb.close()
+
+
+def bound_of(kernel):
+    """What bounds a kernel kind by its counters (profiles/): a direct product
+    of a CG iteration at 128^3 neither fills the vector pipes (40% of the issue
+    slots) nor the memory (4.8 TB/s past the L2): the steps of its march wait
+    on each other.  Every other kind streams its fields."""
+    return "latency" if kernel.startswith("tap_k") else "hbm"
 
 
 def cpu_baseline(a, wl, gpu_iters=None, d_fixed=None):
@@ -557,6 +582,20 @@ def gpu_clocks():
     return clk or None
 
 
+def probe_path(pb, variant=None):
+    """The kernels a probe measures: the library's own choice, or the FFT passes
+    with a given register variant (counter collection would distort a timing
+    of the variants, so it is named)."""
+    from paper_2403_19854_amd import fcrkpm
+
+    if variant is not None:
+        pb.set_option(fcrkpm.OPT_TAPS, 0)
+        pb.set_option(fcrkpm.OPT_REGLAYOUT, variant)
+    if pb.get_option(fcrkpm.OPT_TAPS):
+        return {"path": "direct", "layout": None}
+    return {"path": "fft", "layout": pb.get_option(fcrkpm.OPT_REGLAYOUT)}
+
+
 def probe(a, wl):
     """A short run for counter collection (see paper_2403_19854_amd/traffic.py)."""
     import torch
@@ -566,13 +605,7 @@ def probe(a, wl):
     dev = torch.device("cuda:0")
     pb = fcrkpm.Problem.from_workload(wl, device=dev)
     pb.set_graphs(False)
-    # counter collection distorts setup's variant timing: measure the variant
-    # an ordinary run picks (--probe-variant), where the box has it
-    try:
-        pb.set_option(fcrkpm.OPT_REGLAYOUT, a.probe_variant)
-    except fcrkpm.FcrkpmError:
-        pass
-    layout = pb.get_option(fcrkpm.OPT_REGLAYOUT)
+    path = probe_path(pb, a.probe_variant)
     r = torch.from_numpy(wl.r).to(dev)
     _, _, info = pb.solve(r, mode=a.mode, tol=1e-300, maxit=a.probe, want_uh=False,
                           raise_on_noconv=False)
@@ -581,7 +614,7 @@ def probe(a, wl):
     dst = torch.empty_like(src)
     dst.copy_(src)
     torch.cuda.synchronize()
-    print(json.dumps({"probe": wl.name, "cg_iterations": info["iters"], "layout": layout,
+    print(json.dumps({"probe": wl.name, "cg_iterations": info["iters"], **path,
                       "calibration_copy_bytes": 4 * src.numel()}), flush=True)
     pb.close()
 

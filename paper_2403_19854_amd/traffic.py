@@ -32,7 +32,12 @@ COPY_BYTES = 256 << 20
 _PASS = r"k_rpass<[^,]+(?:, \d+>)?, [^,]+, \d, "
 _T32 = r"(, (true|false))?(, float)?>"
 _T64 = r", (true|false), double>"
+# a direct product: k_tap<T, Tio, basis, radius, mode, ...>, modes 0 (plain) and
+# 5 (with the direction update and dot partials of CG)
+_TAP = r"k_tap<%s, %s, [^<>]*<\d, \d>, \d, [05], "
 _KINDS = [
+    (_TAP % ("float", "float"), "tap_k_f32"),
+    (_TAP % ("double", "double"), "tap_k_f64"),
     (r"k_rmid2?<", "sep_mid_k_f32"),
     (r"k_smid<.*, float>", "sep_mid_k_f32"),
     (r"k_smid<.*, double>", "sep_mid_k_f64"),

@@ -48,3 +48,42 @@ def test_gpu_clocks_parsing(monkeypatch):
         raise FileNotFoundError("rocm-smi")
     monkeypatch.setattr(subprocess, "run", missing)
     assert bench.gpu_clocks() is None
+
+
+class FakeProblem:
+    """Options of a context, and what was asked of it."""
+
+    def __init__(self, taps, layout):
+        from paper_2403_19854_amd import fcrkpm as f
+        self.f, self.values, self.sets, self.closed = f, {f.OPT_TAPS: taps, f.OPT_REGLAYOUT: layout}, [], False
+
+    def get_option(self, opt):
+        return self.values[opt]
+
+    def set_option(self, opt, value):
+        self.sets.append((opt, value))
+        self.values[opt] = value
+
+    def close(self):
+        self.closed = True
+
+
+def test_register_variant_is_that_of_a_path_that_ran():
+    pb = FakeProblem(0, 3)
+    assert bench.register_variant({"tap_k_f32": {}, "tap_uh_f64": {}}, lambda: 1 / 0) is None
+    assert bench.register_variant({"sep_part1_x_f32": {}, "sep_mid_k_f32": {}}, lambda: pb) == 3
+    assert pb.closed and not pb.sets
+
+
+def test_probe_path_is_the_one_named():
+    pb = FakeProblem(1, 1)
+    assert bench.probe_path(pb) == {"path": "direct", "layout": None}
+    assert not pb.sets
+    f = pb.f
+    assert bench.probe_path(pb, 1) == {"path": "fft", "layout": 1}
+    assert pb.sets == [(f.OPT_TAPS, 0), (f.OPT_REGLAYOUT, 1)]
+
+
+def test_bounds_of_the_kernel_kinds():
+    assert [bench.bound_of(k) for k in ("tap_k_f32", "tap_k_f64", "tap_load_f64", "sep_mid_k_f32")] == \
+        ["latency", "latency", "hbm", "hbm"]

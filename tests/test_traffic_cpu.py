@@ -109,3 +109,19 @@ def test_templated_kernel_names(tmp_path):
     assert traffic.load("wl", "sep_mid_k_f32", 1, path=str(out)) == want
     assert traffic.load("wl", "sep_mid_k_f32", 3, path=str(out)) == want
     assert traffic.load("wl", "sep_mid_k_f32", 0, path=str(out)) is None
+
+
+def test_direct_products_have_kinds_without_a_variant(tmp_path):
+    tap = "void fcrkpm::k_tap<%s, %s, fcrkpm::TapBasis<3, 1>, 2, %d, 3, 32, 16, 512>(fcrkpm::TapArgs<%s>)"
+    f32, plain = tap % ("float", "float", 5, "float"), tap % ("float", "float", 0, "float")
+    f64, uh = tap % ("double", "double", 5, "double"), tap % ("double", "double", 1, "double")
+    copy = ("__amd_rocclr_copyBuffer", traffic.COPY_BYTES / 1024)
+    for name, scale in (("f.csv", 2.0), ("w.csv", 1.0)):
+        _csv(tmp_path / name, "FETCH_SIZE" if name == "f.csv" else "WRITE_SIZE",
+             [copy, (plain, 7.0 * scale), (f32, 10.0 * scale), (f32, 12.0 * scale), (f64, 30.0 * scale), (uh, 1.0)])
+    out = tmp_path / "t.json"
+    d = traffic.summarize(str(tmp_path / "f.csv"), str(tmp_path / "w.csv"), str(out), "wl", "cmd")
+    assert set(d["kinds"]) == {"tap_k_f32", "tap_k_f64"}
+    k = d["kinds"]["tap_k_f32"]
+    assert k["dispatches"] == 2 and k["layout"] is None and k["bytes_per_launch"] == 33.0 * 1024
+    assert traffic.load("wl", "tap_k_f32", None, path=str(out)) == 33.0 * 1024
