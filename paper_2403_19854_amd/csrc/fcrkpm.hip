@@ -1693,15 +1693,10 @@ fcrkpm_status run_guarded(std::string& err, const std::function<fcrkpm_status()>
 }  // namespace
 
 namespace {
-// Autotuner of the register-resident K passes: time a few FP32 K products
-// with each variant -- line layout (8 or 16 lanes) times tiles per workgroup
-// (1 or 2) -- on this device and keep the fastest.  FCRKPM_REGLAYOUT=v in the
-// environment forces variant v = layout + 2 (tiles - 1).
 // Node classes and the pointwise data of the K-type product whose coefficient
 // rows c.ba_64 (c.krows of them) are in place: classes 0 outside the domain,
-// 1 interior, 2 other; the interior constants; and the register-path bits and
-// records.  The quadratic register records hold the rows b^a themselves, so
-// they serve K alone.
+// 1 interior, 2 other; the interior constants; and the class words and records
+// of the direct kernels.
 void build_pointwise(Ctx& c, hipStream_t st)
 {
     const long nn = c.nn;
@@ -1846,7 +1841,8 @@ void fft_tables_make(Ctx& c, hipStream_t st)
 }
 
 // What the FFT passes of the rows in use keep besides: the records of the
-// register path and the line-constant structure.  Contexts whose products run
+// register path and the line-constant structure.  (The quadratic register
+// records hold the rows b^a themselves, so they serve K alone.)  Contexts whose products run
 // on the direct kernels build them when an option that runs FFT passes is set.
 // The line-constant structure is an extra that may be absent for want of
 // memory: false then.
@@ -1941,6 +1937,10 @@ int default_reg_variant(const Ctx& c)
     return c.n[0] >= 128 ? 1 : 0;
 }
 
+// Autotuner of the register-resident K passes: time a few FP32 K products
+// with each variant -- line layout (8 or 16 lanes) times tiles per workgroup
+// (1 or 2) -- on this device and keep the fastest.  FCRKPM_REGLAYOUT=v in the
+// environment forces variant v = layout + 2 (tiles - 1).
 void tune_reg_layout(Ctx& c, hipStream_t st)
 {
     if (!use_reg_path(c, 1)) return;

@@ -194,7 +194,11 @@ int tap_lds(const Ctx& c, bool small)
 // tile 1.15-1.25, 1.2-1.5, 1.3-1.6, 1.5-1.7 for r = 1 to 4 (a quarter of the
 // columns, so it pays only where the large tile leaves CUs idle: 32^3 10.1 us
 // against 11.9, 48^3 FP64 15.9 against 17.5; 128^3 39.7 against 32.1).  In FP64:
-// 1.9-2.4, 2.8-3.1; 1.35-1.8, 1.55-2.0, 1.85-2.2, 2.2-2.4.
+// 1.9-2.4, 2.8-3.1; 1.35-1.8, 1.55-2.0, 1.85-2.2, 2.2-2.4.  The other radii and
+// bases take the same constants: of 56 products on 3D boxes (radii 1 to 3, linear
+// and quadratic, both types) 46 are within 5% of the best of all cuts; the
+// quadratic basis is the furthest off (R = 3 FP32, 128^3 143 us where the best is
+// 111; R = 2 FP64, 64^3 44 and 37).
 struct TapCut {
     bool small;
     int cz;

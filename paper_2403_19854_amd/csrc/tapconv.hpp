@@ -26,14 +26,16 @@
 // Every buffer is written in one half and read in the other, so one copy of
 // each and two barriers per plane suffice.
 //
-// What bounds it: the vector pipes on large boxes (256^3 FP32: 224 lane
-// operations per node issued, 72% of the issue slots; about 145 of them are taps
+// What bounds it: on large boxes the vector pipes (256^3 FP32: 224 lane
+// operations per node issued, 73% of the issue slots; about 145 of them are taps
 // with the halo of a 32 x 16 tile and the run-in of a chunk; LDS active 49% of
-// the time), the chain of steps on small ones (32^3: 7 steps of about 0.6 us
-// after 2-3 us of launch and first loads).  A K product, linear basis, R = 2,
-// against the five FFT passes: 32^3 FP32 9.5 us (28.8), 128^3 FP32 31 (55) and
-// FP64 46 (107), 256^3 FP32 132 (362), 32 right-hand sides of 96^3 214 (552);
-// quadratic ball of 128^3, R = 2, FP32 60 (181).
+// the time) and the lines fetched past the L2 (1.12 GB, seven times what is
+// unique, at 8.5 TB/s from the Infinity Cache); on small ones the chain of steps
+// (32^3: 7 steps of about 0.6 us after 2-3 us of launch and first loads).  K
+// products back to back, linear basis, R = 2, against the five FFT passes: 32^3
+// FP32 9.4 us (28.8), 128^3 FP32 30 (55) and FP64 46 (107), 256^3 FP32 132 (362),
+// 32 right-hand sides of 96^3 212 (552); quadratic ball of 128^3, R = 2, FP32 60
+// (181).
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -195,9 +197,9 @@ __device__ __forceinline__ int tap_wrap(int i, int n)
 }
 
 // Workgroup b runs on XCD b % 8: neighbouring tiles go to one XCD, whose L2 then
-// serves part of their halos (K in FP32, bytes fetched and time without and with
-// this order: 128^3 164 -> 84 MB, 37 -> 31 us; 256^3 792 -> 545 MB, 140 -> 131 us;
-// 32 right-hand sides of 96^3 257 -> 213 us).
+// serves part of their halos (K in FP32, bytes fetched past the L2 and time,
+// without and with this order: 128^3 337 -> 173 MB, 37 -> 30 us; 256^3 1626 -> 1117
+// MB, 140 -> 132 us; 32 right-hand sides of 96^3 1450 -> 476 MB, 257 -> 212 us).
 __device__ __forceinline__ long tap_xcd(long b, long nblocks)
 {
     if (nblocks % 8 != 0) return b;
@@ -888,7 +890,7 @@ constexpr int tap_tile_x(int dim, int degree, int r, bool small)
 constexpr int tap_tile_y(int dim, bool small) { return dim == 1 ? 1 : small ? 8 : 16; }
 constexpr int tap_threads(int dim, bool small) { return dim == 1 || small ? 256 : 512; }
 
-// instantiated in tap_f32.hip and tap_f64.hip
+// instantiated in the tap_*.hip files, a list of tap_list.hpp each
 template <typename T, typename Tio, class B, int R, int MODE, int ROWS>
 void tap_go(const TapArgs<T>& a, dim3 grid, bool small, hipStream_t st)
 {
