@@ -1707,15 +1707,17 @@ void build_pointwise(Ctx& c, hipStream_t st)
         int big = 0x7fffffff, ref = 0;
         HIPCHK(hipMemcpyAsync(c.dflag + 3, &big, sizeof(int), hipMemcpyHostToDevice, st));
         launch_first_interior(c, c.dflag + 3, st);
-        HIPCHK(hipMemcpyAsync(&ref, c.dflag + 3, sizeof(int), hipMemcpyDeviceToHost, st));
-        HIPCHK(hipStreamSynchronize(st));
         const int nb = c.krows * c.s;
+        double vals[kMaxNodeConst + 1];
+        launch_node_values(c, c.dflag + 3, c.dvals, st);
+        HIPCHK(hipMemcpyAsync(&ref, c.dflag + 3, sizeof(int), hipMemcpyDeviceToHost, st));
+        HIPCHK(hipMemcpyAsync(vals, c.dvals, sizeof(double) * (nb + 1), hipMemcpyDeviceToHost, st));
+        HIPCHK(hipStreamSynchronize(st));
         NodeConst nc = {};
         nc.bmax = -1.0;  // no interior node: every domain node is class 2
         if (ref != 0x7fffffff) {
-            HIPCHK(hipMemcpy2D(nc.b, sizeof(double), c.ba_64 + ref, sizeof(double) * nn, sizeof(double), nb,
-                               hipMemcpyDeviceToHost));
-            HIPCHK(hipMemcpy(&nc.v, c.vol64 + ref, sizeof(double), hipMemcpyDeviceToHost));
+            memcpy(nc.b, vals, sizeof(double) * nb);
+            nc.v = vals[nb];
             nc.bmax = 0.0;
             for (int q = 0; q < nb; ++q) nc.bmax = std::max(nc.bmax, fabs(nc.b[q]));
         }
@@ -2180,6 +2182,7 @@ extern "C" fcrkpm_status fcrkpm_setup(const fcrkpm_grid* grid, const uint8_t* ma
             blk.want(c.freem, nn);
             blk.want(c.dirm, nn);
             blk.want(c.dflag, 8);
+            blk.want(c.dvals, kMaxNodeConst + 1);
             blk.want(c.vol64, nn);
             blk.want(c.vol32, nn);
             blk.want(occ, ntot);

@@ -162,6 +162,7 @@ struct Ctx {
     bool capturing = false;             // a graph capture is recording this context's work
     hipStream_t aux = nullptr;          // stream of this problem inside a batched solve
     int* dflag = nullptr;               // device int flags
+    double* dvals = nullptr;            // kMaxNodeConst + 1 values of a node
     void* prof = nullptr;               // kernel-duration sampler (measurement only)
     bool prof_on = false;
     int prof_rhs = 1;                   // right-hand sides of the launch being sampled
@@ -362,6 +363,8 @@ void launch_free_mask(const uint8_t* chi, const uint8_t* dir, uint8_t* freem, in
 void launch_axis_extent(const Ctx& c, const uint8_t* chi, int* occ, hipStream_t st);
 void launch_moment_solve(const Ctx& c, const cplx<double>* G, int* bad, hipStream_t st);
 void launch_first_interior(const Ctx& c, int* ref, hipStream_t st);
+// the rows in use and V of node *ref: krows * s + 1 values
+void launch_node_values(const Ctx& c, const int* ref, double* out, hipStream_t st);
 // (n2 += the nodes of class 2)
 void launch_node_class(const Ctx& c, const NodeConst& ref, uint8_t* cls, unsigned long long* n2, hipStream_t st);
 void launch_vol(const uint8_t* chi, const double* vol_in, double hv, double* vol64, float* vol32,

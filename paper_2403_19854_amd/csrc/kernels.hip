@@ -125,6 +125,24 @@ void launch_first_interior(const Ctx& c, int* ref, hipStream_t st)
                        c.n[1], c.n[2], c.m[0], c.m[1], c.m[2], c.nn, ref);
 }
 
+// The coefficient rows and the volume of node *ref, side by side (out of range:
+// there is none).  A strided copy to the host would do, but with a profiler
+// attached such a copy has returned success and no data here.
+__global__ void k_node_values(const double* __restrict__ ba, const double* __restrict__ vol, const int* __restrict__ ref,
+                              int nb, long nn, double* __restrict__ out)
+{
+    const int q = threadIdx.x;
+    const long I = *ref;
+    if (I >= nn) return;
+    if (q < nb) out[q] = ba[q * nn + I];
+    else if (q == nb) out[q] = vol[I];
+}
+
+void launch_node_values(const Ctx& c, const int* ref, double* out, hipStream_t st)
+{
+    hipLaunchKernelGGL(k_node_values, dim3(1), dim3(64), 0, st, c.ba_64, c.vol64, ref, c.krows * c.s, c.nn, out);
+}
+
 __global__ void k_node_class(const uint8_t* __restrict__ chi, const double* __restrict__ ba,
                              const double* __restrict__ vol, int nb, NodeConst ref, int n0, int n1,
                              int n2, int m0, int m1, int m2, long nn, uint8_t* __restrict__ cls,

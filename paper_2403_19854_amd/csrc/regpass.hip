@@ -3060,9 +3060,12 @@ bool kn_build(const Ctx& c, hipStream_t st)
     // b^0 at the box centre gives its scale (interior node of a cube-like domain)
     const long centre = (long)(c.n[0] / 2) + (long)c.n[0] * ((c.n[1] / 2) + (long)c.n[1] * (c.n[2] / 2));
     double b0c[4] = {0, 0, 0, 0};
-    if (hipMemcpy2DAsync(b0c, sizeof(double), c.b0_64 + centre, sizeof(double) * c.nn, sizeof(double), 4,
-                         hipMemcpyDeviceToHost, st) != hipSuccess ||
-        hipStreamSynchronize(st) != hipSuccess) {
+    bool got = true;
+    for (int q = 0; q < 4; ++q)
+        got = got && hipMemcpyAsync(&b0c[q], c.b0_64 + (size_t)q * c.nn + centre, sizeof(double),
+                                    hipMemcpyDeviceToHost, st) == hipSuccess;
+    got = hipStreamSynchronize(st) == hipSuccess && got;
+    if (!got) {
         (void)hipGetLastError();
         return false;
     }
