@@ -245,7 +245,7 @@ def register_variant(kernels, problem):
 def bound_of(kernel):
     """What bounds a kernel kind by its counters (profiles/): a direct product
     of a CG iteration at 128^3 neither fills the vector pipes (40% of the issue
-    slots) nor the memory (4.8 TB/s past the L2): the steps of its march wait
+    slots) nor the memory (1.8 TB/s past the L2): the steps of its march wait
     on each other.  Every other kind streams its fields."""
     return "latency" if kernel.startswith("tap_k") else "hbm"
 

@@ -26,16 +26,15 @@
 // Every buffer is written in one half and read in the other, so one copy of
 // each and two barriers per plane suffice.
 //
-// What bounds it: on large boxes the vector pipes (256^3 FP32: 224 lane
-// operations per node issued, 73% of the issue slots; about 145 of them are taps
+// What bounds it: the vector pipes on large boxes (256^3 FP32: 219 lane
+// operations per node issued, 71% of the issue slots; about 145 of them are taps
 // with the halo of a 32 x 16 tile and the run-in of a chunk; LDS active 49% of
-// the time) and the lines fetched past the L2 (1.12 GB, seven times what is
-// unique, at 8.5 TB/s from the Infinity Cache); on small ones the chain of steps
-// (32^3: 7 steps of about 0.6 us after 2-3 us of launch and first loads).  K
-// products back to back, linear basis, R = 2, against the five FFT passes: 32^3
-// FP32 9.4 us (28.8), 128^3 FP32 30 (55) and FP64 46 (107), 256^3 FP32 132 (362),
-// 32 right-hand sides of 96^3 212 (552); quadratic ball of 128^3, R = 2, FP32 60
-// (181).
+// the time; 208 MB fetched, a third more than what is unique), the chain of steps
+// on small ones (32^3: 7 steps of about 0.6 us after 2-3 us of launch and first
+// loads).  K products back to back, linear basis, R = 2, against the five FFT
+// passes: 32^3 FP32 9.4 us (28.8), 128^3 FP32 30 (55) and FP64 46 (107), 256^3
+// FP32 131 (362), 32 right-hand sides of 96^3 211 (552); quadratic ball of 128^3,
+// R = 2, FP32 60 (181).
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -197,9 +196,9 @@ __device__ __forceinline__ int tap_wrap(int i, int n)
 }
 
 // Workgroup b runs on XCD b % 8: neighbouring tiles go to one XCD, whose L2 then
-// serves part of their halos (K in FP32, bytes fetched past the L2 and time,
-// without and with this order: 128^3 337 -> 173 MB, 37 -> 30 us; 256^3 1626 -> 1117
-// MB, 140 -> 132 us; 32 right-hand sides of 96^3 1450 -> 476 MB, 257 -> 212 us).
+// serves most of their halos (K in FP32, bytes fetched past the L2 and time,
+// without and with this order: 128^3 152 -> 34 MB, 37 -> 30 us; 256^3 597 -> 208 MB,
+// 140 -> 131 us; 32 right-hand sides of 96^3 784 -> 217 MB, 257 -> 211 us).
 __device__ __forceinline__ long tap_xcd(long b, long nblocks)
 {
     if (nblocks % 8 != 0) return b;
