@@ -500,7 +500,7 @@ enum {
     FCRKPM_OPT_SEP_LINES32 = 9,  /* LDS-tiled passes, FP32: most lines per workgroup (16, 8, 4) */
     FCRKPM_OPT_SEP_LINES64 = 10, /* the same for FP64.  Setup times K products with each on the
                                     precisions that run on these passes, where it times, and
-                                    keeps the fastest; else 16. */
+                                    keeps the fastest; else 16, in 2D 4. */
     FCRKPM_OPT_TUNE_CACHED = 11, /* read only: 1 if setup took its tuning choices from the file
                                     named by FCRKPM_AUTOTUNE_CACHE (keyed by device, box, basis
                                     and support) instead of timing; new choices are appended to

@@ -1844,10 +1844,10 @@ void fft_tables_make(Ctx& c, hipStream_t st)
 
 // What the FFT passes of the rows in use keep besides: the records of the
 // register path and the line-constant structure.  (The quadratic register
-// records hold the rows b^a themselves, so they serve K alone.)  Contexts whose products run
-// on the direct kernels build them when an option that runs FFT passes is set.
-// The line-constant structure is an extra that may be absent for want of
-// memory: false then.
+// records hold the rows b^a themselves, so they serve K alone.)  Contexts on
+// the direct kernels build them when an option that runs FFT passes is set.
+// False where memory ran out for the line-constant structure, which the passes
+// can do without.
 bool fft_build(Ctx& c, hipStream_t st)
 {
     // node classes of the register-resident K passes: interior nodes share
@@ -2305,6 +2305,11 @@ extern "C" fcrkpm_status fcrkpm_setup(const fcrkpm_grid* grid, const uint8_t* ma
         ensure_rhs(c, 1);
         const char* cache = getenv("FCRKPM_AUTOTUNE_CACHE");
         set_reg_variant(c, default_reg_variant(c));
+        // lines per workgroup of boxes that are not timed: 2D boxes have few lines
+        // (K in FP32, 128 x 96: 39 us with 4, 51 with 16; 300 x 280 the same), in 1D
+        // and 3D 16 lines are within 1% of the best but for the smallest (32^3
+        // quadratic 113 us, 105 with 8)
+        if (c.dim == 2) c.sep_wcap[0] = c.sep_wcap[1] = 4;
         if (fft_needed(c) || (cache && *cache)) {
             fft_ensure(c, st);
             ensure_work(c, 1);

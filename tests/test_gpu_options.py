@@ -21,6 +21,21 @@ def options(f):
     return [getattr(f, k) for k in sorted(dir(f)) if k.startswith("OPT_")]
 
 
+def test_lines_of_a_box_that_is_not_timed():
+    """The stored default is the choice that gives the direct kernels back."""
+    f = fc()
+    h, chi = (1.0 / 96, 1.0 / 72), np.ones((72, 96), np.uint8)
+    chi[-3:], chi[:, -3:] = 0, 0
+    g = f.Problem((96, 72), h, (2.5, 2.5), 1, chi, None, None, device=DEV)
+    for opt in (f.OPT_SEP_LINES32, f.OPT_SEP_LINES64):
+        assert g.get_option(opt) == 4
+        g.set_option(opt, 16)
+        assert g.get_option(opt) == 16 and g.get_option(f.OPT_TAPS) == 0
+        g.set_option(opt, 4)
+        assert g.get_option(f.OPT_TAPS) == 1
+    g.close()
+
+
 @pytest.mark.parametrize("n,at,degree", [(128, 3.5, 1), (64, 3.5, 2)])
 def test_kernels_do_not_depend_on_options_read(n, at, degree):
     """The kernel of a product follows from the geometry alone, also on the
